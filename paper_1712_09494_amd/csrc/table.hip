@@ -42,6 +42,7 @@ hipError_t vec_query(const DevTable&, const uint64_t*, uint64_t, uint8_t*, uint3
 hipError_t vec_dump(const uint64_t*, uint64_t, const uint64_t*, uint64_t*, uint64_t, unsigned long long*, uint32_t,
                     uint32_t, hipStream_t);
 hipError_t fill_words(uint64_t*, uint64_t, uint64_t, hipStream_t);
+hipError_t clear_words(uint64_t*, uint64_t, uint64_t, hipStream_t);
 hipError_t zero_words(uint32_t*, uint64_t, hipStream_t);
 hipError_t compact_words(const uint64_t*, uint64_t, uint64_t*, uint64_t, unsigned long long*, uint32_t,
                          hipStream_t);
@@ -236,10 +237,9 @@ int alloc_storage(ht_table* t) {
 
 int clear_async(ht_table* t, hipStream_t s) {
   KernelTimer kt("clear", s);
-  HT_HIP(fill_words(t->dev.slots, t->nslots, kEmpty, s));
-  HT_HIP(fill_words(t->dev.stash, t->dev.stash_slots, kEmpty, s));
-  HT_HIP(fill_words(t->dev.overflow, t->dev.overflow_slots, kEmpty, s));
-  HT_HIP(zero_words(reinterpret_cast<uint32_t*>(t->dev.ctr), sizeof(Counters) / 4, s));
+  // slots | stash | overflow list | counters, each padded to 256 bytes (alloc_storage)
+  const uint64_t nfill = (uint64_t)(reinterpret_cast<uint64_t*>(t->dev.ctr) - t->dev.slots);
+  HT_HIP(clear_words(t->dev.slots, nfill, align_up(sizeof(Counters), 256) / 8, s));
   return HT_OK;
 }
 
