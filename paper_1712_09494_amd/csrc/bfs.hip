@@ -11,22 +11,30 @@
 // for p = 0..15 each local target in list order, then for each synchronising
 // action the (p-edge, q-edge) pair when both exist; at most 68 successors.
 //
-// Split levels (the batch interface of Sec. 5): successors are written in
-// two passes (count per state, exclusive scan of the counts, write at the
-// scanned offsets), so each state's successors sit contiguously in frontier
-// order; the batch is find-or-put as one call and the keys flagged new are
-// selected in batch order.  Scan and selection are the three-pass kernels of
-// compact.hip.
+// All bookkeeping is per group of 64 consecutive frontier states (one wave): a
+// group's number of successors (or of new ones), and an exclusive scan of
+// those.  Places within a group come from a wave scan of the lanes' counts, so
+// no per-state counts or offsets are stored.
 //
-// Fused levels (bucketed tables; successor generation and hash table access
-// in one kernel, as GPUexplore does, Sec. 3.2 and 7): a lane takes a frontier
-// state, generates its successors in registers in the same order, and
-// find-or-puts each with the one-lane bucket probe, recording in a 68-bit
-// mask which of them were new and counting them; after an exclusive scan of
-// the counts a second pass regenerates the successors and writes the new ones
-// at the scanned offsets.  The successor batch is never stored: a level moves
-// the frontier, the masks and the new states instead of writing the batch,
-// reading it for the find-or-put and again for the selection.
+// Split levels (the batch interface of Sec. 5): a counting pass and the scan,
+// then the level goes through in slices of consecutive groups: a slice's
+// successors are written to one buffer in frontier order, find-or-put as one
+// call, and the keys flagged new are appended to the next frontier in batch
+// order (the selection of compact.hip).  A slice bounds the buffers to about
+// half a GB whatever the level's size; a whole level at once took 12.2 GB for
+// the 715 M successors of the 7-level workload's last level, and allocating
+// memory that has been used before costs about 30 ms per GB (it is cleared
+// first): 395 ms for an exploration whose kernels run 25 ms.  The last level's
+// new states are counted and not written: there is no level to read them.
+//
+// Fused levels (successor generation and hash table access in one kernel, as
+// GPUexplore does, Sec. 3.2 and 7): a lane takes a frontier state, generates
+// its successors in registers in the same order, and find-or-puts each with
+// the one-lane bucket probe (Cuckoo: probes and places it, listing those whose
+// candidates are all taken for an evict pass), recording in a 68-bit mask
+// which of them were new; after the scan of the new counts a second pass
+// regenerates the successors and writes the new ones.  The successor batch is
+// never stored: a level moves the frontier, the masks and the new states.
 #include <algorithm>
 #include <cstring>
 #include <vector>
@@ -39,8 +47,9 @@ namespace ht {
 hipError_t zero_words(uint32_t*, uint64_t, hipStream_t);
 hipError_t scan_exclusive(const unsigned long long*, unsigned long long*, uint64_t, unsigned long long*,
                           unsigned long long*, uint32_t, hipStream_t);
-hipError_t select_flagged(const uint64_t*, const uint8_t*, uint64_t, uint64_t*, unsigned long long*,
-                          unsigned long long*, uint32_t, hipStream_t);
+hipError_t select_count(const uint8_t*, uint64_t, unsigned long long*, unsigned long long*, uint32_t, hipStream_t);
+hipError_t select_write(const uint64_t*, const uint8_t*, uint64_t, uint64_t*, const unsigned long long*, uint32_t,
+                        hipStream_t);
 }  // namespace ht
 
 using namespace ht;
@@ -57,18 +66,36 @@ struct BfsModelDev {
 
 __device__ __forceinline__ uint32_t local_of(uint64_t st, uint32_t p) { return (uint32_t)(st >> (4 * p)) & 15u; }
 
+// Number of successors of `st`.
+__device__ __forceinline__ uint32_t successor_count(const BfsModelDev& m, uint64_t st) {
+  uint32_t c = 0;
+#pragma unroll
+  for (uint32_t p = 0; p < 16; ++p) c += m.lcnt[p][local_of(st, p)];
+#pragma unroll
+  for (uint32_t a = 0; a < 4; ++a)
+    c += (m.pe[a][local_of(st, m.sp[a])] >= 0 && m.qe[a][local_of(st, m.sq[a])] >= 0) ? 1u : 0u;
+  return c;
+}
+
+// Inclusive prefix sum of `v` over the wave.
+__device__ __forceinline__ uint32_t wave_inclusive32(uint32_t v) {
+  const int lane = lane_id();
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint32_t o = shfl32(v, lane >= off ? lane - off : lane);
+    if (lane >= off) v += o;
+  }
+  return v;
+}
+
+// Successors of each group of 64 frontier states.
 __global__ __launch_bounds__(kBlock) void bfs_count_kernel(BfsModelDev m, const uint64_t* __restrict__ f, uint64_t nf,
-                                                           unsigned long long* __restrict__ cnt) {
+                                                           unsigned long long* __restrict__ gcnt) {
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < nf; i += stride) {
-    const uint64_t st = f[i];
-    uint32_t c = 0;
-#pragma unroll
-    for (uint32_t p = 0; p < 16; ++p) c += m.lcnt[p][local_of(st, p)];
-#pragma unroll
-    for (uint32_t a = 0; a < 4; ++a)
-      c += (m.pe[a][local_of(st, m.sp[a])] >= 0 && m.qe[a][local_of(st, m.sq[a])] >= 0) ? 1u : 0u;
-    cnt[i] = c;
+  for (uint64_t i0 = (uint64_t)blockIdx.x * kBlock + (threadIdx.x & ~63u); i0 < nf; i0 += stride) {
+    const uint64_t i = i0 + lane_id();
+    const uint32_t incl = wave_inclusive32(i < nf ? successor_count(m, f[i]) : 0u);
+    if (lane_id() == kWave - 1) gcnt[i0 / kWave] = incl;
   }
 }
 
@@ -90,35 +117,40 @@ __device__ __forceinline__ void for_each_successor(const BfsModelDev& m, uint64_
   }
 }
 
-// Writing a level's successors (all of them, or those a mask marks) at the
-// states' scanned offsets, staged through LDS so that the stores coalesce:
-// a block takes a tile of kBlock consecutive states, whose outputs form one
+// Writing successors (all of them, or those a mask marks) at their scanned
+// places, staged through LDS so that the stores coalesce: a block takes a tile
+// of kBlock consecutive states (four groups), whose outputs form one
 // contiguous range; each thread places its state's successors that fall in
 // the current window of kWriteWin positions, then the block copies the
 // window out in consecutive words.  A thread per state storing its own
 // successors one after another wrote 8-byte words to 64 unrelated places per
 // instruction: 7.7 ms for the 5.7 GB batch of the 7-level workload's last
-// level.
+// level, 2.6 ms staged.  The tiles cover groups g0 .. g1-1 of the frontier's
+// nf states; goff (one entry more than there are groups) is the scan of the
+// groups' counts, and out[0] receives the first output of group g0.
 constexpr uint32_t kWriteWin = 2048;
 
 template <bool MASKED>
 __device__ __forceinline__ void write_tiles(const BfsModelDev& m, const uint64_t* __restrict__ f, uint64_t nf,
-                                            const unsigned long long* __restrict__ cnt,
-                                            const unsigned long long* __restrict__ off,
+                                            uint64_t g0, uint64_t g1, const unsigned long long* __restrict__ goff,
                                             const uint64_t* __restrict__ mask, uint64_t* __restrict__ out) {
+  constexpr uint64_t kTileGroups = kBlock / kWave;
   __shared__ uint64_t win[kWriteWin];
   const uint32_t tid = threadIdx.x;
-  for (uint64_t i0 = (uint64_t)blockIdx.x * kBlock; i0 < nf; i0 += (uint64_t)gridDim.x * kBlock) {
-    const uint64_t last = (i0 + kBlock < nf ? i0 + kBlock : nf) - 1;
-    const uint64_t base = off[i0];
-    const uint64_t end = off[last] + cnt[last];
-    const uint64_t i = i0 + tid;
-    const bool live = i < nf;
+  const uint64_t zero = goff[g0];
+  for (uint64_t t0 = g0 + (uint64_t)blockIdx.x * kTileGroups; t0 < g1; t0 += (uint64_t)gridDim.x * kTileGroups) {
+    const uint64_t base = goff[t0] - zero;
+    const uint64_t end = goff[t0 + kTileGroups < g1 ? t0 + kTileGroups : g1] - zero;
+    const uint64_t g = t0 + tid / kWave;
+    const uint64_t i = t0 * kWave + tid;
+    const bool live = g < g1 && i < nf;
     const uint64_t st = live ? f[i] : 0ull;
-    const uint64_t mine = live ? off[i] : 0ull;
-    const uint64_t myend = live ? mine + cnt[i] : 0ull;
     const uint64_t m0 = MASKED && live ? mask[2 * i] : ~0ull;
     const uint64_t m1 = MASKED && live ? mask[2 * i + 1] : ~0ull;
+    const uint32_t c = !live ? 0u : MASKED ? (uint32_t)(__popcll(m0) + __popcll(m1)) : successor_count(m, st);
+    const uint32_t incl = wave_inclusive32(c);
+    const uint64_t myend = (g < g1 ? goff[g] - zero : end) + incl;
+    const uint64_t mine = myend - c;
     for (uint64_t w = base; w < end; w += kWriteWin) {
       if (live && mine < w + kWriteWin && myend > w) {
         uint64_t o = mine;
@@ -140,56 +172,62 @@ __device__ __forceinline__ void write_tiles(const BfsModelDev& m, const uint64_t
   }
 }
 
-// Split pass: every successor, written at the state's scanned offset (cnt:
-// successors per state, off: their exclusive scan).
+// Split pass: every successor of groups g0 .. g1-1.
 __global__ __launch_bounds__(kBlock) void bfs_write_kernel(BfsModelDev m, const uint64_t* __restrict__ f, uint64_t nf,
-                                                           const unsigned long long* __restrict__ cnt,
-                                                           const unsigned long long* __restrict__ off,
+                                                           uint64_t g0, uint64_t g1,
+                                                           const unsigned long long* __restrict__ goff,
                                                            uint64_t* __restrict__ out) {
-  write_tiles<false>(m, f, nf, cnt, off, nullptr, out);
+  write_tiles<false>(m, f, nf, g0, g1, goff, nullptr, out);
 }
 
 // Fused pass: find-or-put of every successor of the frontier; per state the
-// mask of new successors (bit k = successor k; two words) and their count;
-// the number of successors generated is added to *generated.
+// mask of new successors (bit k = successor k; two words; not written when
+// mask is NULL), per group of 64 states their number, and the number of
+// successors generated added to *generated.
 __global__ __launch_bounds__(kBlock) void bfs_fused_kernel(BfsModelDev m, DevTable t, const uint64_t* __restrict__ f,
-                                                           uint64_t nf, unsigned long long* __restrict__ cnt,
+                                                           uint64_t nf, unsigned long long* __restrict__ gcnt,
                                                            uint64_t* __restrict__ mask,
                                                            unsigned long long* __restrict__ generated) {
   const uint64_t first = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
+  const int lane = lane_id();
   unsigned long long placed = 0, gen = 0;
-  for (uint64_t i = first; i < nf; i += stride) {
+  for (uint64_t i0 = first - lane; i0 < nf; i0 += stride) {
+    const uint64_t i = i0 + lane;
     uint64_t m0 = 0, m1 = 0;
     uint32_t k = 0, nnew = 0;
-    for_each_successor(m, f[i], [&](uint64_t succ) {
-      const uint32_t r = lane_find_or_put<false>(t, succ);
-      if (r) {                     // 1 = stored, 2 = kept on the overflow list: new either way
-        if (k < 64) m0 |= 1ull << k;
-        else m1 |= 1ull << (k - 64);
-        ++nnew;
+    if (i < nf) {
+      for_each_successor(m, f[i], [&](uint64_t succ) {
+        const uint32_t r = lane_find_or_put<false>(t, succ);
+        if (r) {                   // 1 = stored, 2 = kept on the overflow list: new either way
+          if (k < 64) m0 |= 1ull << k;
+          else m1 |= 1ull << (k - 64);
+          ++nnew;
+        }
+        placed += r == 1;
+        ++k;
+      });
+      if (mask) {
+        mask[2 * i] = m0;
+        mask[2 * i + 1] = m1;
       }
-      placed += r == 1;
-      ++k;
-    });
-    cnt[i] = nnew;
-    mask[2 * i] = m0;
-    mask[2 * i + 1] = m1;
+    }
     gen += k;
+    const uint32_t incl = wave_inclusive32(nnew);
+    if (lane == kWave - 1) gcnt[i0 / kWave] = incl;
   }
   wave_count(t.ctr->size, placed, (uint32_t)(first / kWave));
   const unsigned long long g = wave_sum(gen);
-  if (lane_id() == 0 && g) add_agent(generated, g);
+  if (lane == 0 && g) add_agent(generated, g);
 }
 
-// Second fused pass: the successors marked new, written at the scanned
-// offsets (cnt: new successors per state, off: their exclusive scan).
+// Second fused pass: the successors marked new, at the scanned places.
 __global__ __launch_bounds__(kBlock) void bfs_fused_write_kernel(BfsModelDev m, const uint64_t* __restrict__ f,
-                                                                 uint64_t nf, const uint64_t* __restrict__ mask,
-                                                                 const unsigned long long* __restrict__ cnt,
-                                                                 const unsigned long long* __restrict__ off,
+                                                                 uint64_t nf, uint64_t ngroups,
+                                                                 const uint64_t* __restrict__ mask,
+                                                                 const unsigned long long* __restrict__ goff,
                                                                  uint64_t* __restrict__ out) {
-  write_tiles<true>(m, f, nf, cnt, off, mask, out);
+  write_tiles<true>(m, f, nf, 0, ngroups, goff, mask, out);
 }
 
 // Successors of one state, one per call, in model order (the same order as
@@ -272,32 +310,34 @@ __device__ __forceinline__ uint32_t cuckoo_probe_key(const DevTable& t, uint64_t
   return pend ? kListed : res;
 }
 
-// Fused Cuckoo pass 1: a wave takes groups of 64 frontier states, one per
-// lane, and steps through their successors together; each successor is probed
-// and placed as above, new ones marked in the state's mask and counted, and
-// those with every candidate taken listed as (key, state << 7 | successor
-// number) in the group's region of the scratch list, which starts at the
-// group's first successor offset (a group never lists more keys than it has
-// successors).
+// Fused Cuckoo pass 1: a wave takes groups g0 .. g1-1 of 64 frontier states,
+// one state per lane, and steps through their successors together; each
+// successor is probed and placed as above, new ones marked in the state's mask
+// (not kept when mask is NULL) and counted per group, and those with every
+// candidate taken listed as (key, state << 7 | successor number) in the
+// group's region of the scratch list, which starts at the group's first
+// successor offset, counted from group g0's (a group never lists more keys
+// than it has successors).
 __global__ __launch_bounds__(kBlock) void bfs_cuckoo_probe_kernel(BfsModelDev m, DevTable t,
                                                                   const uint64_t* __restrict__ f, uint64_t nf,
+                                                                  uint64_t g0, uint64_t g1,
                                                                   const unsigned long long* __restrict__ soff,
-                                                                  CuckooScratch s, uint32_t* __restrict__ gcnt,
-                                                                  unsigned long long* __restrict__ cnt,
+                                                                  CuckooScratch s, uint32_t* __restrict__ lcnt,
+                                                                  unsigned long long* __restrict__ gnew,
                                                                   uint64_t* __restrict__ mask) {
   const int lane = lane_id();
   const uint64_t wave =
       __builtin_amdgcn_readfirstlane((uint32_t)(((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave));
   const uint64_t nwaves = (uint64_t)gridDim.x * (kBlock / kWave);
-  const uint64_t ngroups = (nf + kWave - 1) / kWave;
+  const uint64_t zero = soff[g0];
   const uint32_t sc = t.ctr->stash_count;
   const uint32_t oc = t.ctr->overflow_count;
   unsigned long long placed = 0;
-  for (uint64_t g = wave; g < ngroups; g += nwaves) {
+  for (uint64_t g = g0 + wave; g < g1; g += nwaves) {
     const uint64_t i = g * kWave + lane;
     const bool live = i < nf;
     SuccIter it{live ? f[i] : 0ull};
-    const uint64_t begin = soff[g * kWave];
+    const uint64_t begin = soff[g] - zero;
     uint64_t m0 = 0, m1 = 0;
     uint32_t k = 0, nnew = 0, nlist = 0;
     for (;;) {
@@ -309,7 +349,6 @@ __global__ __launch_bounds__(kBlock) void bfs_cuckoo_probe_kernel(BfsModelDev m,
         if (k < 64) m0 |= 1ull << k;
         else m1 |= 1ull << (k - 64);
         ++nnew;
-        ++placed;
       }
       const bool l = has && r == kListed;
       const uint64_t mm = ballot(l);
@@ -321,34 +360,41 @@ __global__ __launch_bounds__(kBlock) void bfs_cuckoo_probe_kernel(BfsModelDev m,
       nlist += (uint32_t)__popcll(mm);
       k += has ? 1u : 0u;
     }
-    if (live) {
-      cnt[i] = nnew;
+    if (mask && live) {
       mask[2 * i] = m0;
       mask[2 * i + 1] = m1;
     }
-    if (lane == 0) gcnt[g] = nlist;
+    placed += nnew;
+    const uint32_t incl = wave_inclusive32(nnew);
+    if (lane == kWave - 1) {
+      gnew[g] = incl;
+      lcnt[g - g0] = nlist;
+    }
   }
   wave_count(t.ctr->size, placed, (uint32_t)wave);
 }
 
 // Fused Cuckoo pass 2: the listed keys, deduplicated in the scratch set; each
-// winner marks its successor new in the state's mask and count and runs the
-// eviction chain from h_1 (then the stash), as the single-table evict kernel
-// does.  The scratch-set slot a winner took replaces its list entry's meta.
-__global__ __launch_bounds__(kBlock) void bfs_cuckoo_evict_kernel(DevTable t, uint64_t nf,
+// winner marks its successor new in the state's mask, is added to its group's
+// count (the wave that serves a group is the only one to write it) and runs
+// the eviction chain from h_1 (then the stash), as the single-table evict
+// kernel does.  The scratch-set slot a winner took replaces its list entry's
+// meta.
+__global__ __launch_bounds__(kBlock) void bfs_cuckoo_evict_kernel(DevTable t, uint64_t g0, uint64_t g1,
                                                                   const unsigned long long* __restrict__ soff,
-                                                                  CuckooScratch s, const uint32_t* __restrict__ gcnt,
-                                                                  unsigned long long* __restrict__ cnt,
+                                                                  CuckooScratch s, const uint32_t* __restrict__ lcnt,
+                                                                  unsigned long long* __restrict__ gnew,
                                                                   uint64_t* __restrict__ mask) {
   const int lane = lane_id();
   const uint64_t wave =
       __builtin_amdgcn_readfirstlane((uint32_t)(((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave));
   const uint64_t nwaves = (uint64_t)gridDim.x * (kBlock / kWave);
-  const uint64_t ngroups = (nf + kWave - 1) / kWave;
+  const uint64_t zero = soff[g0];
   unsigned long long nnew = 0, nevict = 0;
-  for (uint64_t g = wave; g < ngroups; g += nwaves) {
-    const uint64_t begin = soff[g * kWave];
-    const uint32_t c = gcnt[g];
+  for (uint64_t g = g0 + wave; g < g1; g += nwaves) {
+    const uint64_t begin = soff[g] - zero;
+    const uint32_t c = lcnt[g - g0];
+    unsigned long long mine = 0;
     for (uint32_t e = lane; e < c; e += kWave) {
       const uint64_t k = s.wkey[begin + e];
       const uint64_t meta = s.wmeta[begin + e];
@@ -367,16 +413,21 @@ __global__ __launch_bounds__(kBlock) void bfs_cuckoo_evict_kernel(DevTable t, ui
       if (!winner) continue;
       const uint64_t i = meta >> 7;
       const uint32_t kb = (uint32_t)(meta & 127);
-      __hip_atomic_fetch_or(&mask[2 * i + (kb >> 6)], 1ull << (kb & 63), __ATOMIC_RELAXED,
-                            __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_fetch_add(&cnt[i], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (mask)
+        __hip_atomic_fetch_or(&mask[2 * i + (kb >> 6)], 1ull << (kb & 63), __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_AGENT);
       uint64_t y = k;
       uint32_t steps = 0;
       const uint64_t h1 = hidx<false>(t, y, 0);
       const bool placed = (t.flags & kFlagLookahead) ? cuckoo_chain<false, true>(t, y, h1, nevict, steps)
                                                       : cuckoo_chain<false, false>(t, y, h1, nevict, steps);
       if (!placed) stash_put(t, y);
-      ++nnew;
+      ++mine;
+    }
+    if (c) {
+      nnew += mine;
+      mine = wave_sum(mine);
+      if (lane == 0) gnew[g] += mine;
     }
   }
   wave_count(t.ctr->size, nnew, (uint32_t)wave);
@@ -384,17 +435,17 @@ __global__ __launch_bounds__(kBlock) void bfs_cuckoo_evict_kernel(DevTable t, ui
 }
 
 // Fused Cuckoo pass 3: empty the scratch-set slots the evict pass took.
-__global__ __launch_bounds__(kBlock) void bfs_cuckoo_scrub_kernel(uint64_t nf,
+__global__ __launch_bounds__(kBlock) void bfs_cuckoo_scrub_kernel(uint64_t g0, uint64_t g1,
                                                                   const unsigned long long* __restrict__ soff,
-                                                                  CuckooScratch s, const uint32_t* __restrict__ gcnt) {
+                                                                  CuckooScratch s, const uint32_t* __restrict__ lcnt) {
   const int lane = lane_id();
   const uint64_t wave =
       __builtin_amdgcn_readfirstlane((uint32_t)(((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave));
   const uint64_t nwaves = (uint64_t)gridDim.x * (kBlock / kWave);
-  const uint64_t ngroups = (nf + kWave - 1) / kWave;
-  for (uint64_t g = wave; g < ngroups; g += nwaves) {
-    const uint64_t begin = soff[g * kWave];
-    const uint32_t c = gcnt[g];
+  const uint64_t zero = soff[g0];
+  for (uint64_t g = g0 + wave; g < g1; g += nwaves) {
+    const uint64_t begin = soff[g] - zero;
+    const uint32_t c = lcnt[g - g0];
     for (uint32_t e = lane; e < c; e += kWave) {
       const uint64_t p = s.wmeta[begin + e];
       if (p != ~0ull) s.dset[p] = kEmpty;
@@ -406,14 +457,27 @@ __global__ __launch_bounds__(kBlock) void bfs_cuckoo_scrub_kernel(uint64_t nf,
 struct Buf {
   void* p = nullptr;
   size_t bytes = 0;
-  int ensure(size_t need) {
+  // Room for `need` bytes; the first `keep` bytes of the old contents stay
+  // (copied on stream s, which is waited for).
+  int ensure(size_t need, size_t keep = 0, hipStream_t s = nullptr) {
     if (need <= bytes) return HT_OK;
-    if (p) (void)hipFree(p);
+    void* old = p;
+    if (!keep) {
+      if (old) (void)hipFree(old);
+      old = nullptr;
+    }
     p = nullptr;
     bytes = 0;
     hipError_t e = hipMalloc(&p, need);
+    if (e == hipSuccess && old) {
+      e = hipMemcpyAsync(p, old, keep, hipMemcpyDeviceToDevice, s);
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
+    if (old) (void)hipFree(old);
     if (e != hipSuccess) {
       (void)hipGetLastError();
+      if (p) (void)hipFree(p);
+      p = nullptr;
       return fail(HT_ENOMEM, "hipMalloc in breadth-first exploration failed");
     }
     bytes = need;
@@ -424,22 +488,91 @@ struct Buf {
   }
 };
 
-// Events of one exploration, destroyed on every return path.
-struct Events {
-  hipEvent_t e[8] = {};
-  ~Events() {
-    for (auto& x : e)
-      if (x) (void)hipEventDestroy(x);
+}  // namespace
+
+// Buffers of an exploration, kept with the table for its next one while they
+// are small (kKeepBytes) and given back with it.
+struct ht_explore_ws {
+  int device = 0;
+  Buf frontier, next, batch, flags, gcounts, goffsets, gnews, tmp, nsel, masks, lists;
+  size_t bytes() const {
+    size_t n = 0;
+    for (const Buf* b : {&frontier, &next, &batch, &flags, &gcounts, &goffsets, &gnews, &tmp, &nsel, &masks, &lists})
+      n += b->bytes;
+    return n;
   }
 };
 
-}  // namespace
-
-// Device time between two recorded events, in ms.
-static double span_ms(hipEvent_t a, hipEvent_t b) {
-  float ms = 0.f;
-  return hipEventElapsedTime(&ms, a, b) == hipSuccess ? (double)ms : 0.0;
+void ht_rt::free_explore(ht_table* t) {
+  delete t->explore;
+  t->explore = nullptr;
 }
+
+namespace {
+
+constexpr size_t kKeepBytes = 1ull << 30;
+
+// The table's exploration buffers for one call: those it kept, if they lie on
+// the current device, else new ones.  Afterwards they stay with the table
+// when they are small and the call went well.
+struct ExploreHold {
+  ht_table* t;
+  bool keep = false;
+  explicit ExploreHold(ht_table* table) : t(table) {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    if (t->explore && t->explore->device != dev) free_explore(t);
+    if (!t->explore) {
+      t->explore = new ht_explore_ws();
+      t->explore->device = dev;
+    }
+  }
+  ~ExploreHold() {
+    if (!keep || t->explore->bytes() > kKeepBytes) free_explore(t);
+  }
+};
+
+// Device time of the spans of work between host round trips: pairs of events
+// recorded on the stream, kept for the next level, destroyed on every return
+// path.
+struct Spans {
+  std::vector<hipEvent_t> ev;
+  size_t used = 0;
+  hipError_t mark(hipStream_t s) {
+    if (used == ev.size()) {
+      hipEvent_t e = nullptr;
+      const hipError_t rc = hipEventCreate(&e);
+      if (rc != hipSuccess) return rc;
+      ev.push_back(e);
+    }
+    return hipEventRecord(ev[used++], s);
+  }
+  // Sum in ms; the stream's work is done.  The next level starts over.
+  double total() {
+    double ms = 0.0;
+    for (size_t i = 0; i + 1 < used; i += 2) {
+      float x = 0.f;
+      if (hipEventElapsedTime(&x, ev[i], ev[i + 1]) == hipSuccess) ms += (double)x;
+    }
+    used = 0;
+    return ms;
+  }
+  ~Spans() {
+    for (auto& x : ev) (void)hipEventDestroy(x);
+  }
+};
+
+// Groups of 64 states per slice.  Split: 16384 groups have about 50 M
+// successors (at most 71 M), half a GB of batch and flags.  The 7-level
+// workload's split bucketed levels, device time and whole call: 4096 groups
+// 28.4 and 31.1 ms, 8192 26.4 and 28.2, 16384 25.4 and 27.7, 32768 24.9 and
+// 28.9 (its buffers no longer stay with the table), whole levels 24.3 and
+// 28.1 before memory has to be cleared, 395 after.  Fused Cuckoo: four groups
+// for each wave of the probe grid (at most 1.7 GB of lists).
+constexpr uint64_t kSplitGroups = 16384;
+constexpr uint64_t kCuckooTurns = 4;
+
+}  // namespace
 
 extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_t initial, uint32_t levels,
                                  uint32_t mode, uint64_t* batch_sizes, uint64_t* new_counts, double* fop_ms,
@@ -460,142 +593,178 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
   for (int p = 0; p < 16; ++p)
     for (int q = 0; q < 16; ++q)
       if (m.lcnt[p][q] > 4) return fail(HT_EINVAL, "more than 4 local transitions");
-  Buf frontier, next, batch, flags, counts, offsets, tmp, nsel, masks, gcounts, noffsets;
+  ExploreHold hold(t);
+  ht_explore_ws& ws = *t->explore;
+  Buf &frontier = ws.frontier, &next = ws.next, &batch = ws.batch, &flags = ws.flags, &gcounts = ws.gcounts,
+      &goffsets = ws.goffsets, &gnews = ws.gnews, &tmp = ws.tmp, &nsel = ws.nsel, &masks = ws.masks, &lists = ws.lists;
   const uint32_t grid = max_blocks(t);
   rc = frontier.ensure(8);
-  if (!rc) rc = nsel.ensure(16);
+  if (!rc) rc = nsel.ensure(8);
   if (!rc) rc = tmp.ensure((grid + 1) * 8ull);   // block totals of the scans and the selection
   if (rc) return rc;
   auto* wk = static_cast<unsigned long long*>(tmp.p);
+  auto* ns = static_cast<unsigned long long*>(nsel.p);
   HT_HIP(hipMemcpyAsync(frontier.p, &initial, 8, hipMemcpyHostToDevice, s));
   rc = do_find_or_put(t, static_cast<uint64_t*>(frontier.p), 1, nullptr, s);
   if (rc) return rc;
   const DevTable dt = launch_view(t);
   uint64_t nf = 1;
-  // A level runs as up to three spans of device work with a host round trip
-  // between them (reading sizes, growing buffers): ev[0..1], ev[2..3],
-  // ev[4..5]; ev[6..7] bracket the find-or-put (or the fused passes).
-  Events evs;
-  hipEvent_t* ev = evs.e;
-  for (int i = 0; i < 8; ++i) HT_HIP(hipEventCreate(&ev[i]));
+  Spans all, fop;
+  std::vector<unsigned long long> bounds;
   for (uint32_t L = 0; L < levels && nf && rc == HT_OK; ++L) {
-    rc = counts.ensure(nf * 8);
-    if (!rc) rc = offsets.ensure(nf * 8);
-    if (!rc && fused) rc = masks.ensure(nf * 16);
-    if (!rc && ck) rc = noffsets.ensure(nf * 8);
-    if (!rc && ck) rc = gcounts.ensure((nf + kWave - 1) / kWave * 4);
+    const bool last = L + 1 == levels;     // no next level: new states are counted, not written
+    const uint64_t ng = (nf + kWave - 1) / kWave;
+    rc = gcounts.ensure(ng * 8);
+    if (!rc) rc = goffsets.ensure((ng + 1) * 8);
+    if (!rc && fused && !last) rc = masks.ensure(nf * 16);
+    if (!rc && ck) rc = gnews.ensure(ng * 8);
     if (rc) break;
-    auto* cnt = static_cast<unsigned long long*>(counts.p);
-    auto* off = static_cast<unsigned long long*>(offsets.p);
+    auto* gcnt = static_cast<unsigned long long*>(gcounts.p);
+    auto* goff = static_cast<unsigned long long*>(goffsets.p);
     auto* fr = static_cast<const uint64_t*>(frontier.p);
-    auto* ns = static_cast<unsigned long long*>(nsel.p);
-    auto* mk = static_cast<uint64_t*>(masks.p);
+    auto* mk = last ? nullptr : static_cast<uint64_t*>(masks.p);
     const uint32_t g1 = (uint32_t)std::min<uint64_t>((nf + kBlock - 1) / kBlock, grid);
+    const uint32_t gsc = (uint32_t)std::min<uint64_t>((ng + 1023) / 1024, grid);
+    uint64_t nb = 0, nnew = 0;
+    // first span: successor counts (split, fused Cuckoo) or the fused bucketed pass, then a scan
     if (fused && !ck) HT_HIP(zero_words(reinterpret_cast<uint32_t*>(ns), 2, s));
-    double lms = 0.0;
-    // span 1: successor counts (split, fused Cuckoo) or the fused bucketed pass, then a scan
-    HT_HIP(hipEventRecord(ev[0], s));
+    HT_HIP(all.mark(s));
     if (fused && !ck) {
-      HT_HIP(hipEventRecord(ev[6], s));
+      HT_HIP(fop.mark(s));
       // the grid of the one-lane find-or-put kernels (7-level workload: 22.3-23.1 ms
       // for the fused levels at 8 blocks per compute unit, 19.3 at 6)
       const uint32_t gf = (uint32_t)std::min<uint64_t>((nf + kBlock - 1) / kBlock, atomic_grid_blocks(t));
-      hipLaunchKernelGGL(bfs_fused_kernel, dim3(gf), dim3(kBlock), 0, s, m, dt, fr, nf, cnt, mk, ns);
+      hipLaunchKernelGGL(bfs_fused_kernel, dim3(gf), dim3(kBlock), 0, s, m, dt, fr, nf, gcnt, mk, ns);
       HT_HIP(hipGetLastError());
-      HT_HIP(hipEventRecord(ev[7], s));
+      HT_HIP(fop.mark(s));
     } else {
-      hipLaunchKernelGGL(bfs_count_kernel, dim3(g1), dim3(kBlock), 0, s, m, fr, nf, cnt);
+      hipLaunchKernelGGL(bfs_count_kernel, dim3(g1), dim3(kBlock), 0, s, m, fr, nf, gcnt);
       HT_HIP(hipGetLastError());
     }
-    HT_HIP(scan_exclusive(cnt, off, nf, ns + 1, wk, grid, s));
-    HT_HIP(hipEventRecord(ev[1], s));
-    unsigned long long last[3] = {0, 0, 0};
-    HT_HIP(hipMemcpyAsync(&last[0], off + nf - 1, 8, hipMemcpyDeviceToHost, s));
-    HT_HIP(hipMemcpyAsync(&last[1], cnt + nf - 1, 8, hipMemcpyDeviceToHost, s));
-    if (fused && !ck) HT_HIP(hipMemcpyAsync(&last[2], ns, 8, hipMemcpyDeviceToHost, s));
-    HT_HIP(hipStreamSynchronize(s));
-    lms += span_ms(ev[0], ev[1]);
-    const uint64_t total = last[0] + last[1];   // fused bucketed: new states; otherwise successors
-    const uint64_t nb = (fused && !ck) ? last[2] : total;
-    if (batch_sizes) batch_sizes[L] = nb;
-    uint64_t nnew = 0;
+    HT_HIP(scan_exclusive(gcnt, goff, ng, goff + ng, wk, gsc, s));
+    HT_HIP(all.mark(s));
     if (fused && !ck) {
-      nnew = total;
-    } else if (ck) {
-      // span 2: fused probe and placement, evict, scrub, scan of the new counts
-      rc = reserve_scratch(t, nb);   // lists and scratch set for this level, outside the timed spans
-      if (rc) break;
-      const CuckooScratch sc = scratch_view(t, nb);
-      auto* gc = static_cast<uint32_t*>(gcounts.p);
-      auto* noff = static_cast<unsigned long long*>(noffsets.p);
-      const uint64_t ngroups = (nf + kWave - 1) / kWave;
-      // the probe grid of the single-table Cuckoo find-or-put (fused levels of
-      // the 7-level workload: 36.3-38.6 ms at 8 blocks per compute unit, 32.9
-      // at 6)
-      const uint32_t g2 = (uint32_t)std::min<uint64_t>((ngroups + 3) / 4, atomic_grid_blocks(t));
-      HT_HIP(hipEventRecord(ev[2], s));
-      HT_HIP(hipEventRecord(ev[6], s));
-      hipLaunchKernelGGL(bfs_cuckoo_probe_kernel, dim3(g2), dim3(kBlock), 0, s, m, dt, fr, nf, off, sc, gc, cnt, mk);
-      HT_HIP(hipGetLastError());
-      hipLaunchKernelGGL(bfs_cuckoo_evict_kernel, dim3(g2), dim3(kBlock), 0, s, dt, nf, off, sc, gc, cnt, mk);
-      HT_HIP(hipGetLastError());
-      hipLaunchKernelGGL(bfs_cuckoo_scrub_kernel, dim3(g2), dim3(kBlock), 0, s, nf, off, sc, gc);
-      HT_HIP(hipGetLastError());
-      HT_HIP(hipEventRecord(ev[7], s));
-      HT_HIP(scan_exclusive(cnt, noff, nf, ns + 1, wk, grid, s));
-      HT_HIP(hipEventRecord(ev[3], s));
-      unsigned long long lastn[2] = {0, 0};
-      HT_HIP(hipMemcpyAsync(&lastn[0], noff + nf - 1, 8, hipMemcpyDeviceToHost, s));
-      HT_HIP(hipMemcpyAsync(&lastn[1], cnt + nf - 1, 8, hipMemcpyDeviceToHost, s));
+      unsigned long long got[2] = {0, 0};
+      HT_HIP(hipMemcpyAsync(&got[0], goff + ng, 8, hipMemcpyDeviceToHost, s));
+      HT_HIP(hipMemcpyAsync(&got[1], ns, 8, hipMemcpyDeviceToHost, s));
       HT_HIP(hipStreamSynchronize(s));
-      lms += span_ms(ev[2], ev[3]);
-      nnew = lastn[0] + lastn[1];
-    }
-    if (fused) {
-      // last span: the new states written at their scanned offsets
-      rc = next.ensure(std::max<uint64_t>(nnew, 1) * 8);
-      if (rc) break;
-      const unsigned long long* woff = ck ? static_cast<const unsigned long long*>(noffsets.p) : off;
-      HT_HIP(hipEventRecord(ev[4], s));
-      hipLaunchKernelGGL(bfs_fused_write_kernel, dim3(g1), dim3(kBlock), 0, s, m, fr, nf, mk, cnt, woff,
-                         static_cast<uint64_t*>(next.p));
-      HT_HIP(hipGetLastError());
-      HT_HIP(hipEventRecord(ev[5], s));
-      HT_HIP(hipStreamSynchronize(s));
-      lms += span_ms(ev[4], ev[5]);
-      if (fop_ms) fop_ms[L] = span_ms(ev[6], ev[7]);
+      nnew = got[0];
+      nb = got[1];
     } else {
-      rc = batch.ensure(std::max<uint64_t>(nb, 1) * 8);
-      if (!rc) rc = flags.ensure(std::max<uint64_t>(nb, 1));
-      if (!rc) rc = next.ensure(std::max<uint64_t>(nb, 1) * 8);
-      if (!rc) rc = reserve_scratch(t, nb);   // Cuckoo scratch for this batch, outside the timed spans
+      // where each slice's successors begin: slice q is groups q * per ...
+      const uint64_t per = ck ? (uint64_t)atomic_grid_blocks(t) * (kBlock / kWave) * kCuckooTurns : kSplitGroups;
+      const uint64_t nslices = (ng + per - 1) / per;
+      bounds.resize(nslices + 1);
+      if (nslices > 1)
+        HT_HIP(hipMemcpy2DAsync(bounds.data(), 8, goff, per * 8, 8, nslices, hipMemcpyDeviceToHost, s));
+      HT_HIP(hipMemcpyAsync(&bounds[nslices], goff + ng, 8, hipMemcpyDeviceToHost, s));
+      HT_HIP(hipStreamSynchronize(s));
+      if (nslices == 1) bounds[0] = 0;
+      nb = bounds[nslices];
+      uint64_t most = 1;
+      for (uint64_t q = 0; q < nslices; ++q) most = std::max<uint64_t>(most, bounds[q + 1] - bounds[q]);
+      rc = reserve_scratch(t, most);   // the find-or-put's scratch for a slice, outside the timed spans
+      if (!rc && ck) rc = lists.ensure(std::min(per, ng) * 4);
+      if (!rc && !ck) rc = batch.ensure(most * 8);
+      if (!rc && !ck) rc = flags.ensure(most);
+      if (!rc && !ck) rc = nsel.ensure(nslices * 8);
       if (rc) break;
+      ns = static_cast<unsigned long long*>(nsel.p);
       auto* bt = static_cast<uint64_t*>(batch.p);
       auto* fl = static_cast<uint8_t*>(flags.p);
-      // span 2: write the batch, find-or-put it, select the new keys
-      HT_HIP(hipEventRecord(ev[2], s));
-      hipLaunchKernelGGL(bfs_write_kernel, dim3(g1), dim3(kBlock), 0, s, m, fr, nf, cnt, off, bt);
-      HT_HIP(hipGetLastError());
-      HT_HIP(hipEventRecord(ev[6], s));
-      rc = do_find_or_put(t, bt, nb, fl, s);
+      auto* lc = static_cast<uint32_t*>(lists.p);
+      auto* gn = static_cast<unsigned long long*>(gnews.p);
+      if (ck) HT_HIP(all.mark(s));
+      for (uint64_t q = 0; q < nslices && rc == HT_OK; ++q) {
+        const uint64_t n = bounds[q + 1] - bounds[q];
+        const uint64_t a = q * per, z = std::min(ng, a + per);
+        if (ck) {
+          // probe and place, evict, scrub.  The probe grid of the single-table
+          // Cuckoo find-or-put (fused levels of the 7-level workload: 36.3-38.6
+          // ms at 8 blocks per compute unit, 32.9 at 6)
+          const CuckooScratch sc = scratch_view(t, std::max<uint64_t>(n, 1));
+          const uint32_t g2 = (uint32_t)std::min<uint64_t>((z - a + 3) / 4, atomic_grid_blocks(t));
+          HT_HIP(fop.mark(s));
+          hipLaunchKernelGGL(bfs_cuckoo_probe_kernel, dim3(g2), dim3(kBlock), 0, s, m, dt, fr, nf, a, z, goff, sc, lc,
+                             gn, mk);
+          HT_HIP(hipGetLastError());
+          hipLaunchKernelGGL(bfs_cuckoo_evict_kernel, dim3(g2), dim3(kBlock), 0, s, dt, a, z, goff, sc, lc, gn, mk);
+          HT_HIP(hipGetLastError());
+          hipLaunchKernelGGL(bfs_cuckoo_scrub_kernel, dim3(g2), dim3(kBlock), 0, s, a, z, goff, sc, lc);
+          HT_HIP(hipGetLastError());
+          HT_HIP(fop.mark(s));
+          continue;
+        }
+        // split: write the slice's batch, find-or-put it, select the new keys
+        if (!n) {                        // no state of the slice has a successor
+          HT_HIP(zero_words(reinterpret_cast<uint32_t*>(ns + q), 2, s));
+          continue;
+        }
+        const uint32_t gw = (uint32_t)std::min<uint64_t>((z - a + kBlock / kWave - 1) / (kBlock / kWave), grid);
+        HT_HIP(all.mark(s));
+        hipLaunchKernelGGL(bfs_write_kernel, dim3(gw), dim3(kBlock), 0, s, m, fr, nf, a, z, goff, bt);
+        HT_HIP(hipGetLastError());
+        HT_HIP(fop.mark(s));
+        rc = do_find_or_put(t, bt, n, fl, s);
+        if (rc) break;
+        HT_HIP(fop.mark(s));
+        const uint32_t gs = (uint32_t)std::min<uint64_t>((n + 4095) / 4096, grid);
+        HT_HIP(select_count(fl, n, ns + q, wk, gs, s));
+        HT_HIP(all.mark(s));
+        if (!last) {
+          // the next frontier's room grows with the new states found
+          unsigned long long got = 0;
+          HT_HIP(hipMemcpyAsync(&got, ns + q, 8, hipMemcpyDeviceToHost, s));
+          HT_HIP(hipStreamSynchronize(s));
+          if ((nnew + got) * 8 > next.bytes) {
+            // what the slices so far give for the whole level, and a tenth more
+            const uint64_t guess = (uint64_t)((double)(nnew + got) / (double)(q + 1) * (double)nslices * 1.1);
+            rc = next.ensure(std::max<uint64_t>(guess, std::max<uint64_t>(nnew + got, 1)) * 8, nnew * 8, s);
+            if (rc) break;
+          }
+          HT_HIP(all.mark(s));
+          HT_HIP(select_write(bt, fl, n, static_cast<uint64_t*>(next.p) + nnew, wk, gs, s));
+          HT_HIP(all.mark(s));
+          nnew += got;
+        }
+      }
       if (rc) break;
-      HT_HIP(hipEventRecord(ev[7], s));
-      HT_HIP(select_flagged(bt, fl, nb, static_cast<uint64_t*>(next.p), ns, wk, grid, s));
-      HT_HIP(hipEventRecord(ev[3], s));
-      unsigned long long nsv = 0;
-      HT_HIP(hipMemcpyAsync(&nsv, ns, 8, hipMemcpyDeviceToHost, s));
-      HT_HIP(hipStreamSynchronize(s));
-      lms += span_ms(ev[2], ev[3]);
-      nnew = nsv;
-      if (fop_ms) fop_ms[L] = span_ms(ev[6], ev[7]);
+      if (ck) {
+        HT_HIP(scan_exclusive(gn, goff, ng, goff + ng, wk, gsc, s));
+        HT_HIP(all.mark(s));
+        unsigned long long got = 0;
+        HT_HIP(hipMemcpyAsync(&got, goff + ng, 8, hipMemcpyDeviceToHost, s));
+        HT_HIP(hipStreamSynchronize(s));
+        nnew = got;
+      } else if (last) {
+        bounds.resize(nslices);
+        HT_HIP(hipMemcpyAsync(bounds.data(), ns, nslices * 8, hipMemcpyDeviceToHost, s));
+        HT_HIP(hipStreamSynchronize(s));
+        for (auto x : bounds) nnew += x;
+      }
     }
+    if (fused && !last) {
+      // last span: the new states written at their scanned places
+      rc = next.ensure(std::max<uint64_t>(nnew, 1) * 8);
+      if (rc) break;
+      HT_HIP(all.mark(s));
+      hipLaunchKernelGGL(bfs_fused_write_kernel, dim3(g1), dim3(kBlock), 0, s, m, fr, nf, ng, mk, goff,
+                         static_cast<uint64_t*>(next.p));
+      HT_HIP(hipGetLastError());
+      HT_HIP(all.mark(s));
+    }
+    HT_HIP(hipStreamSynchronize(s));
+    const double lms = all.total(), fms = fop.total();
+    if (fop_ms) fop_ms[L] = fms;
     if (level_ms) level_ms[L] = lms;
+    if (batch_sizes) batch_sizes[L] = nb;
     if (new_counts) new_counts[L] = nnew;
     std::swap(frontier.p, next.p);
     std::swap(frontier.bytes, next.bytes);
     nf = nnew;
   }
-  (void)hipStreamSynchronize(s);
+  const hipError_t end = hipStreamSynchronize(s);
+  hold.keep = rc == HT_OK && end == hipSuccess;
   return rc;
 }
 

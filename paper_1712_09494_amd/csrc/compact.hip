@@ -61,14 +61,40 @@ __global__ __launch_bounds__(kBlock) void scan_totals_kernel(const unsigned long
   if (threadIdx.x == 0) totals[blockIdx.x] = s;
 }
 
+// Chunk of the selection's block: a multiple of 16 items, so that the counting
+// pass reads its flags 16 at a time.
+__device__ __forceinline__ void select_chunk_of(uint64_t n, uint64_t& lo, uint64_t& hi) {
+  const uint64_t chunk = ((n + gridDim.x - 1) / gridDim.x + 15) & ~15ull;
+  lo = (uint64_t)blockIdx.x * chunk;
+  hi = lo + chunk;
+  if (lo > n) lo = n;
+  if (hi > n) hi = n;
+}
+
+// Number of non-zero bytes of a word.
+__device__ __forceinline__ uint32_t nonzero_bytes(uint32_t w) {
+  const uint32_t hi = ((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w;   // bit 7 of each non-zero byte
+  return (uint32_t)__popc(hi & 0x80808080u);
+}
+
 // Pass 1 of the selection: per-block number of flagged items (flag != 0).
+// Flags are read 16 at a time when the array is 16-byte aligned; one byte per
+// lane ran at 1.1 TB/s.
 __global__ __launch_bounds__(kBlock) void select_totals_kernel(const uint8_t* __restrict__ flags, uint64_t n,
                                                                unsigned long long* __restrict__ totals) {
   __shared__ unsigned long long lds[kWavesPerBlock];
   uint64_t lo, hi;
-  chunk_of(n, lo, hi);
+  select_chunk_of(n, lo, hi);
   unsigned long long s = 0;
-  for (uint64_t i = lo + threadIdx.x; i < hi; i += kBlock) s += flags[i] != 0 ? 1u : 0u;
+  uint64_t vec = lo;                       // [lo, vec) read as vectors
+  if ((reinterpret_cast<uintptr_t>(flags) & 15) == 0) {
+    vec = lo + ((hi - lo) & ~15ull);
+    for (uint64_t i = lo + 16ull * threadIdx.x; i < vec; i += 16ull * kBlock) {
+      const uint4 v = *reinterpret_cast<const uint4*>(flags + i);
+      s += nonzero_bytes(v.x) + nonzero_bytes(v.y) + nonzero_bytes(v.z) + nonzero_bytes(v.w);
+    }
+  }
+  for (uint64_t i = vec + threadIdx.x; i < hi; i += kBlock) s += flags[i] != 0 ? 1u : 0u;
   s = block_sum(s, lds);
   if (threadIdx.x == 0) totals[blockIdx.x] = s;
 }
@@ -141,7 +167,7 @@ __global__ __launch_bounds__(kBlock) void select_write_kernel(const uint64_t* __
                                                               uint64_t* __restrict__ out) {
   __shared__ uint32_t lds[kWavesPerBlock];
   uint64_t lo, hi;
-  chunk_of(n, lo, hi);
+  select_chunk_of(n, lo, hi);
   unsigned long long run = offs[blockIdx.x];
   const int w = threadIdx.x / kWave;
   for (uint64_t t0 = lo; t0 < hi; t0 += kBlock) {
@@ -175,13 +201,19 @@ hipError_t scan_exclusive(const unsigned long long* in, unsigned long long* out,
   return hipGetLastError();
 }
 
-// out = the in[i] with flags[i] != 0, in index order; their number goes to
-// *count (device).  `work` holds grid + 1 words.
-hipError_t select_flagged(const uint64_t* in, const uint8_t* flags, uint64_t n, uint64_t* out,
-                          unsigned long long* count, unsigned long long* work, uint32_t grid, hipStream_t s) {
-  // n == 0 still runs the passes, so that *count is written (0)
+// Selection of the in[i] with flags[i] != 0, in index order, in two calls
+// with the same n, grid and work (grid + 1 words): the first counts them
+// (number to *count, device) and leaves each block's place in work, the
+// second writes them to out.
+hipError_t select_count(const uint8_t* flags, uint64_t n, unsigned long long* count, unsigned long long* work,
+                        uint32_t grid, hipStream_t s) {
   hipLaunchKernelGGL(select_totals_kernel, dim3(grid), dim3(kBlock), 0, s, flags, n, work);
   hipLaunchKernelGGL(scan_block_totals_kernel, dim3(1), dim3(kBlock), 0, s, work, grid, count);
+  return hipGetLastError();
+}
+
+hipError_t select_write(const uint64_t* in, const uint8_t* flags, uint64_t n, uint64_t* out,
+                        const unsigned long long* work, uint32_t grid, hipStream_t s) {
   hipLaunchKernelGGL(select_write_kernel, dim3(grid), dim3(kBlock), 0, s, in, flags, n, work, out);
   return hipGetLastError();
 }

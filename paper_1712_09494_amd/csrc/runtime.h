@@ -22,6 +22,8 @@ struct SplitMix {
 
 }  // namespace ht_rt
 
+struct ht_explore_ws;        // buffers of an exploration (bfs.hip)
+
 struct ht_table {
   ht_config cfg;             // effective configuration (defaults filled in)
   ht_config user_cfg;        // as passed to ht_create
@@ -50,6 +52,8 @@ struct ht_table {
   // scripted hashes
   ht::ScriptRow* script = nullptr;
   uint32_t nscript = 0;
+  // exploration buffers kept from the last one
+  ht_explore_ws* explore = nullptr;
 };
 
 #define HT_HIP(call)                                           \
@@ -68,6 +72,7 @@ uint32_t atomic_grid_blocks(const ht_table* t);
 bool is_scripted(const ht_table* t);
 int check_table(const ht_table* t);
 int reserve_scratch(ht_table* t, uint64_t n);
+void free_explore(ht_table* t);
 ht::DevTable launch_view(const ht_table* t);
 ht::CuckooScratch scratch_view(const ht_table* t, uint64_t n);   // per_wave left for the caller
 // `fixed`: scratch provided by the caller (Cuckoo tables of single-word keys;

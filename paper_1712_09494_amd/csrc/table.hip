@@ -694,6 +694,7 @@ int ht_destroy(ht_table* t) {
   if (!t) return fail(HT_EINVAL, "table is NULL");
   (void)hipDeviceSynchronize();
   free_scratch(t);
+  free_explore(t);
   free_storage(t);
   if (t->script) (void)hipFree(t->script);
   delete t;

@@ -183,3 +183,38 @@ def test_bfs_fused_rejects_other_tables():
     with b.Table("bucketed", capacity=1024) as t:
         with pytest.raises(b.HtError):
             b.ht_bfs_explore_ex(t.handle, model, 2, 7)
+
+
+class ChainModel:
+    """Process 0 walks 0 -> 1 -> 2 and stops; the other processes stand still,
+    except that process 1 may step 0 -> 1 when `wide`."""
+
+    def __init__(self, wide):
+        self.local = [[[] for _ in range(16)] for _ in range(16)]
+        self.local[0][0], self.local[0][1] = [1], [2]
+        if wide:
+            self.local[1][0] = [1]
+        self.syncs = [(0, 1, [[] for _ in range(16)], [[] for _ in range(16)]) for _ in range(4)]
+
+
+@pytest.mark.parametrize("kind", ["bucketed", "cuckoo"])
+@pytest.mark.parametrize("fused", [False, True])
+def test_bfs_ends_and_repeats(kind, fused):
+    """States without successors end the exploration, the last level asked
+    for is counted like any other, and a table explored again after a clear
+    (with the buffers it kept) gives the same counts."""
+    with b.Table(kind, capacity=1 << 16, nhash=3) as t:
+        for levels, sizes, news in ((1, [1], [1]), (2, [1, 1], [1, 1]), (3, [1, 1, 0], [1, 1, 0])):
+            t.clear()
+            r = t.bfs_explore(ChainModel(False), levels, fused=fused)
+            assert r["batch_sizes"] == sizes and r["new_counts"] == news, levels
+            assert t.size() == 1 + sum(news)
+        t.clear()
+        r = t.bfs_explore(ChainModel(True), 6, fused=fused)      # 3 x 2 states
+        assert r["batch_sizes"] == [2, 3, 2, 0, 0, 0] and r["new_counts"] == [2, 2, 1, 0, 0, 0]
+        o, sizes, news = oracle_bfs(inputs.BfsModel(1), 0, 4)
+        for _ in range(2):
+            t.clear()
+            r = t.bfs_explore(inputs.BfsModel(1), 4, fused=fused)
+            assert r["batch_sizes"] == sizes and r["new_counts"] == news
+            assert np.array_equal(np.sort(b.u64(t.dump())), o.dump())
