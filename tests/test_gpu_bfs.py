@@ -203,7 +203,7 @@ def test_bfs_ends_and_repeats(kind, fused):
     """States without successors end the exploration, the last level asked
     for is counted like any other, and a table explored again after a clear
     (with the buffers it kept) gives the same counts."""
-    with b.Table(kind, capacity=1 << 16, nhash=3) as t:
+    with b.Table(kind, capacity=1 << 19, nhash=3) as t:
         for levels, sizes, news in ((1, [1], [1]), (2, [1, 1], [1, 1]), (3, [1, 1, 0], [1, 1, 0])):
             t.clear()
             r = t.bfs_explore(ChainModel(False), levels, fused=fused)
