@@ -204,12 +204,13 @@ int ht_destroy(ht_table* t);
  * vectors of W words each, row-major (n * W words, 16-byte aligned; HT_EINVAL
  * otherwise).  d_out_is_new: n bytes (device), may be NULL when the flags are
  * not wanted.  Grows the table's scratch (allocating, synchronising) when n
- * exceeds what was reserved.  Cuckoo and state-vector calls on one table
- * must be ordered by the caller (one stream, or events between streams):
- * they share the table's scratch, and a Cuckoo call of single-word keys
- * leaves the deduplication slots its winners took for the next such call's
- * first kernel to empty (state kept on the device, so captured and replayed
- * calls stay exact). */
+ * exceeds what was reserved.  Calls on one table must be ordered by the
+ * caller (one stream, or events between streams; see the conventions above):
+ * they share the table's scratch; a large first batch of a bucketed table, or
+ * one into a small one, holds parts of the table in LDS while it works; and a
+ * Cuckoo call of single-word keys leaves the deduplication slots its winners
+ * took for the next such call's first kernel to empty (state kept on the
+ * device, so captured and replayed calls stay exact). */
 int ht_find_or_put(ht_table* t, const uint64_t* d_keys, uint64_t n,
                    uint8_t* d_out_is_new, hipStream_t stream);
 
@@ -372,7 +373,9 @@ int ht_set_scripted_hash(ht_table* t, const uint64_t* keys,
 int ht_chain_histogram(ht_table* t, uint64_t* out, hipStream_t stream);
 
 /* Infrastructure.  Reserve scratch for batches up to max_batch keys
- * (allocates, synchronises the device). */
+ * (allocates, synchronises the device).  A bucketed table of single-word keys
+ * reserves the workspace of a large first batch (11 bytes a key) when there
+ * is room. */
 int ht_reserve(ht_table* t, uint64_t max_batch);
 
 /* Infrastructure.  Human-readable text of a status code (a static string;

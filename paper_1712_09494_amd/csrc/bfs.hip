@@ -705,7 +705,7 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
         hipLaunchKernelGGL(bfs_write_kernel, dim3(gw), dim3(kBlock), 0, s, m, fr, nf, a, z, goff, bt);
         HT_HIP(hipGetLastError());
         HT_HIP(fop.mark(s));
-        rc = do_find_or_put(t, bt, n, fl, s);
+        rc = do_find_or_put(t, bt, n, fl, s, nullptr, true);
         if (rc) break;
         HT_HIP(fop.mark(s));
         const uint32_t gs = (uint32_t)std::min<uint64_t>((n + 4095) / 4096, grid);
@@ -754,6 +754,7 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
       HT_HIP(all.mark(s));
     }
     HT_HIP(hipStreamSynchronize(s));
+    if (fused) t->puts += nb;
     const double lms = all.total(), fms = fop.total();
     if (fop_ms) fop_ms[L] = fms;
     if (level_ms) level_ms[L] = lms;

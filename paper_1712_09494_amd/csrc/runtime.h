@@ -49,6 +49,10 @@ struct ht_table {
   uint32_t* dirty_cnt = nullptr;
   uint64_t* dirty_desc = nullptr;
   uint64_t dirty_stride = 0;
+  // workspace of the tiled find-or-put
+  void* tile_ws = nullptr;
+  size_t tile_bytes = 0;
+  uint64_t puts = 0;           // keys handed to find-or-put since the table was empty
   // scripted hashes
   ht::ScriptRow* script = nullptr;
   uint32_t nscript = 0;
@@ -76,9 +80,10 @@ void free_explore(ht_table* t);
 ht::DevTable launch_view(const ht_table* t);
 ht::CuckooScratch scratch_view(const ht_table* t, uint64_t n);   // per_wave left for the caller
 // `fixed`: scratch provided by the caller (Cuckoo tables of single-word keys;
-// per_wave is set here), instead of the table's own.
+// per_wave is set here), instead of the table's own.  `repeats`: most of the
+// keys are known to be stored already or repeated in the batch.
 int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t s,
-                   const ht::CuckooScratch* fixed = nullptr);
+                   const ht::CuckooScratch* fixed = nullptr, bool repeats = false);
 uint64_t pow2_at_least(uint64_t x);
 extern thread_local bool g_quiet;   // set: launches create no timing events
 int do_query(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t s);

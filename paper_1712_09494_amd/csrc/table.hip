@@ -11,6 +11,7 @@
 
 #include "multi.h"
 #include "runtime.h"
+#include "tile.h"
 
 namespace ht {
 // kernels (bucketed.hip, cuckoo.hip, util.hip, multi.hip)
@@ -238,12 +239,16 @@ int alloc_storage(ht_table* t) {
 int clear_async(ht_table* t, hipStream_t s) {
   KernelTimer kt("clear", s);
   // slots | stash | overflow list | counters, each padded to 256 bytes (alloc_storage)
+  t->puts = 0;
   const uint64_t nfill = (uint64_t)(reinterpret_cast<uint64_t*>(t->dev.ctr) - t->dev.slots);
   HT_HIP(clear_words(t->dev.slots, nfill, align_up(sizeof(Counters), 256) / 8, s));
   return HT_OK;
 }
 
 int free_scratch(ht_table* t) {
+  if (t->tile_ws) (void)hipFree(t->tile_ws);
+  t->tile_ws = nullptr;
+  t->tile_bytes = 0;
   if (t->dset) (void)hipFree(t->dset);
   t->dset = nullptr;
   t->wkey = nullptr;
@@ -310,6 +315,62 @@ int reserve_scratch(ht_table* t, uint64_t n) {
   }
   HT_HIP(hipDeviceSynchronize());
   return HT_OK;
+}
+
+// Ordinary bucketed tables of single-word keys (none of the measurement and
+// test modes that ask for a particular kernel).
+static bool tile_table(const ht_table* t) {
+  return t->cfg.kind == HT_BUCKETED && t->cfg.key_words <= 1 && !t->cfg.lds_bytes &&
+         !(t->cfg.flags & (HT_FLAG_SCRIPTED_HASH | HT_FLAG_BUCKETED_ONE_LANE | HT_FLAG_BUCKETED_ATOMIC_LOADS));
+}
+
+// Whether a find-or-put of n keys goes through the tiled passes (tile_dev.h).
+// The table has 9 to 64 bytes of slots per key: fewer hold the batch only if
+// it repeats its keys, and streaming more costs as much as the batch's own
+// lines (2^20 keys, direct and tiled: 99 and 98 us at 9 bytes, 78 and 59 at
+// 10, 66 and 41 at 16, 59 and 38 at 32, 57 and 48 at 64; 16-slot buckets at 16
+// bytes 66 and 47).  At least 2^18 keys (2^18: 45 and 32 us at 16 bytes, 29
+// and 24 at 64; 2^17: 33 and 31, 21 and 20), with a tenth more room below
+// 2^20 (2^18 at 9 bytes: 77 and 106 us, the keys of full buckets), at most
+// 2^25 (369 MB of workspace) and kTileMax tiles.  The gain is in
+// the compare-and-swaps of new keys: a batch of keys already stored takes 27
+// us direct and 39 tiled (2^20 keys at 16 bytes), so the batch has to be
+// larger than all that was put before it since the table was empty.
+static bool tile_rule(const ht_table* t, uint64_t n) {
+  if (!tile_table(t) || n < (1ull << 18) || n > (1ull << 25) || t->puts >= n) return false;
+  const uint64_t bytes = t->nslots * 8;
+  return bytes >= (n < (1ull << 20) ? 11 * n : 9 * n) && bytes <= 64 * n &&
+         t->nslots <= (uint64_t)kTileMax * kTileSlots;
+}
+
+// Whether one block does the call with the whole table in LDS: a batch that
+// fills a small table from empty meets itself in the same buckets (1024 keys
+// into 2048 slots: 16-slot buckets 13.7 us direct and 4.6, 8-slot ones 9.2 and
+// 4.5, 64-slot ones 37 and 9.5; 256 keys 4.7 and 4.3; 4096 keys 14.9 and
+// 12.3).  Keys already stored cost a microsecond more here (4.5 and 5.8 us).
+static bool tile_whole_rule(const ht_table* t, uint64_t n) {
+  return tile_table(t) && t->nslots <= kTileSlots && n >= 512 && n <= 2048 && t->puts < n;
+}
+
+// Workspace of the tiled passes; false (the direct kernels serve the call)
+// when it cannot be allocated or the stream is being captured.
+static bool tile_workspace(ht_table* t, size_t bytes, hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (bytes <= t->tile_bytes) return true;
+  if (t->tile_ws) (void)hipFree(t->tile_ws);     // waits for the work that uses it
+  t->tile_ws = nullptr;
+  t->tile_bytes = 0;
+  if (hipMalloc(&t->tile_ws, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    t->tile_ws = nullptr;
+    return false;
+  }
+  t->tile_bytes = bytes;
+  return true;
 }
 
 int validate_config(const ht_config* c) {
@@ -490,8 +551,24 @@ static int vec_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_
 // per wave give the same fill time (5.92 ms; three: 6.02, four: 6.07).
 constexpr uint32_t kEvictPack = 2;
 
+static int tiled_find_or_put(ht_table* t, const DevTable& d, const uint64_t* keys, uint64_t n, uint8_t* out,
+                             const TileShape& sh, hipStream_t s) {
+  const TileJob j = tile_job(d, keys, n, out, sh, t->tile_ws);
+  {
+    KernelTimer kt("tile_partition", s);
+    HT_HIP(tile_partition(j, sh, s));
+  }
+  {
+    KernelTimer kt("tile_insert", s);
+    HT_HIP(tile_insert(j, sh, s));
+  }
+  KernelTimer kt("tile_finish", s);
+  HT_HIP(tile_finish(j, sh, s));
+  return HT_OK;
+}
+
 int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t s,
-                   const CuckooScratch* fixed) {
+                   const CuckooScratch* fixed, bool repeats) {
   if (t->cfg.key_words > 1) {
     if (fixed) return fail(HT_EINVAL, "state-vector tables take no caller scratch");
     return vec_find_or_put(t, keys, n, out, s);
@@ -505,6 +582,18 @@ int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, 
     KernelTimer kt("bucketed_lane_fop", s);
     HT_HIP(bucketed_lane_find_or_put(d, keys, n, out, (uint32_t)blocks, scripted, s));
     return HT_OK;
+  }
+  const bool whole = tile_whole_rule(t, n);
+  const bool tiled = !repeats && !g_quiet && tile_rule(t, n);
+  t->puts += n;
+  if (whole) {
+    KernelTimer kt("tile_whole", s);
+    HT_HIP(tile_whole(d, keys, n, out, s));
+    return HT_OK;
+  }
+  if (tiled) {
+    const TileShape sh = tile_shape(t->nslots, n);
+    if (tile_workspace(t, sh.bytes, s)) return tiled_find_or_put(t, d, keys, n, out, sh, s);
   }
   if (t->cfg.kind == HT_BUCKETED) {
     const uint64_t g = bucketed_keys_per_wave(t->cfg.bucket_slots, R, kFopSlotsPerLane);
@@ -667,7 +756,7 @@ int ht_create(const ht_config* cfg, ht_table** out) {
     return rc;
   }
   rc = clear_async(t, nullptr);
-  if (!rc && cfg->max_batch) rc = reserve_scratch(t, cfg->max_batch);
+  if (!rc && cfg->max_batch) rc = ht_reserve(t, cfg->max_batch);
   if (!rc) {
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) rc = hip_fail(e, "hipDeviceSynchronize");
@@ -1115,6 +1204,9 @@ int ht_chain_histogram(ht_table* t, uint64_t* out, hipStream_t s) {
 int ht_reserve(ht_table* t, uint64_t max_batch) {
   int rc = check_table(t);
   if (rc) return rc;
+  // the tiled passes' workspace, if such a batch would use it (a call without
+  // it allocates it, or runs the direct kernels)
+  if (tile_rule(t, max_batch)) (void)tile_workspace(t, tile_shape(t->nslots, max_batch).bytes, nullptr);
   return reserve_scratch(t, max_batch);
 }
 

@@ -1,0 +1,48 @@
+// Tiled find-or-put: shared declarations.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "ht_device.h"
+
+namespace ht {
+
+constexpr uint32_t kTileSlots = 8192;       // most slots of a tile: 64 KiB of LDS, two blocks per compute unit
+constexpr uint32_t kTileMax = 4096;         // most tiles of a table (the partition's LDS counters)
+
+// One bucketed table's tiled find-or-put.
+struct TileJob {
+  DevTable t;
+  const uint64_t* keys;
+  uint8_t* out;             // may be NULL
+  uint64_t n;
+  uint64_t* skey;           // keys, each chunk sorted by tile
+  uint16_t* sidx;           // their places within the chunk
+  uint8_t* sflag;           // their flags
+  uint16_t* off;            // chunks * (tiles + 1): start of each tile's run in the chunk
+  uint32_t chunks;
+  uint32_t tiles;
+  uint32_t shift;           // log2 of the slots of a tile
+  uint32_t run_lanes;       // lanes that serve one run (a power of two)
+};
+
+// Shape of a tiled find-or-put of n keys into a table of nslots slots, and
+// the workspace it needs.
+struct TileShape {
+  uint32_t tiles, chunks, chunk, shift, run_lanes;
+  size_t bytes;
+};
+
+TileShape tile_shape(uint64_t nslots, uint64_t n);
+// The job of a call, its workspace `ws` holding shape.bytes.
+TileJob tile_job(const DevTable& t, const uint64_t* keys, uint64_t n, uint8_t* out, const TileShape& s, void* ws);
+
+// The three passes.
+hipError_t tile_partition(const TileJob& j, const TileShape& s, hipStream_t st);
+hipError_t tile_insert(const TileJob& j, const TileShape& s, hipStream_t st);
+hipError_t tile_finish(const TileJob& j, const TileShape& s, hipStream_t st);
+// One block, the whole table in LDS (at most kTileSlots slots).
+hipError_t tile_whole(const DevTable& t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t st);
+
+}  // namespace ht

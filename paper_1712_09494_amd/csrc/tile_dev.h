@@ -1,0 +1,385 @@
+// Tiled find-or-put: a batch that is large against its table is sorted by
+// table region first, and each region is then worked on in LDS.
+//
+// A lane that find-or-puts its key straight into the table pays a random
+// line read (54 G/s on this chip, 80 G/s within 16 MB) and, for a new key, a
+// memory-side compare-and-swap (21-27 G/s), however often the batch comes
+// back to the same line.  When the batch has a key for every line or two of
+// the table it is cheaper to stream the table once:
+//   1. partition: a block takes a chunk of C consecutive keys and sorts them
+//      by the tile of h_1's bucket (a tile is a run of whole buckets that fits
+//      in LDS); the sorted chunk, each key's place in the chunk and the start
+//      of each tile's run are stored;
+//   2. tile: a block loads one tile into LDS, inserts the keys of every
+//      chunk's run for it with LDS compare-and-swaps, stores a flag per key
+//      beside the sorted keys and writes the tile back;
+//   3. finish: a block puts one chunk's flags back into batch order; the keys
+//      whose bucket was full go on from h_2 in the table itself, with the
+//      ordinary compare-and-swap probe.
+// Placement is that of the direct kernels (the lowest empty slot of the first
+// bucket of the probe sequence that is not full): all copies of a key are in
+// one tile and meet at one slot, and a bucket seen full stays full, so exactly
+// one copy reports new and the lookups' early exits hold.  No other call may
+// work on the table at the same time (the tile is written back with plain
+// stores).
+// The same passes for Cuckoo tables (h_1 in LDS, the rest and the eviction
+// chains as before) were no faster: 2^20 keys into 2^21 slots 84 against 87
+// us, slower at every smaller size and above 2^23 keys, since most of the
+// keys' lines are those of h_2 and the chains.
+#pragma once
+#include "bucketed_dev.h"
+#include "tile.h"
+
+namespace ht {
+
+constexpr uint32_t kTileBlock = 1024;       // threads of the tile kernels
+constexpr uint32_t kTileMore = 0xff;        // flag of a key that goes on at h_2
+
+// First slot of key k's h_1 bucket.
+__device__ __forceinline__ uint64_t tile_home(const DevTable& t, uint64_t k) {
+  return hidx<false>(t, k, 0) * t.bucket_slots;
+}
+
+// Inclusive prefix sum of `v` over the wave.
+__device__ __forceinline__ uint32_t tile_wave_inclusive(uint32_t v) {
+  const int lane = lane_id();
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint32_t o = shfl32(v, lane >= off ? lane - off : lane);
+    if (lane >= off) v += o;
+  }
+  return v;
+}
+
+// Add the block's lanes' counts to a spread counter: one atomic per block (an
+// atomic per wave puts five hundred of them on each of the sixteen lines in a
+// 2^20-key call: 4 us of the tile pass).  *sum (LDS) is zero before; it holds
+// the block's total afterwards, behind a barrier.
+__device__ __forceinline__ void block_count(unsigned long long* spread, uint32_t v, uint32_t* sum, uint32_t salt) {
+  const unsigned long long s = wave_sum(v);
+  if (lane_id() == 0 && s)
+    __hip_atomic_fetch_add(sum, (uint32_t)s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __syncthreads();
+  if (threadIdx.x == 0 && *sum) add_agent(&spread[(salt % kSpread) * kLineWords], (unsigned long long)*sum);
+}
+
+// ---- partition ---------------------------------------------------------------
+
+template <uint32_t C>
+struct TilePartLds {
+  uint64_t key[C];
+  uint16_t idx[C];
+  uint32_t hist[kTileMax];
+  uint32_t wsum[kTileBlock / kWave];
+};
+
+// Sort chunk `c` of the job's batch by tile.
+template <uint32_t C>
+__device__ __forceinline__ void tile_partition_chunk(const TileJob& j, uint32_t c, TilePartLds<C>& l) {
+  constexpr uint32_t PER = C / kTileBlock;
+  const uint32_t tid = threadIdx.x;
+  const uint64_t base = (uint64_t)c * C;
+  const uint32_t m = j.n - base < C ? (uint32_t)(j.n - base) : C;
+  uint64_t k[PER];
+#pragma unroll
+  for (uint32_t r = 0; r < PER; ++r) {
+    const uint32_t i = r * kTileBlock + tid;
+    k[r] = i < m ? j.keys[base + i] : 0;
+  }
+  for (uint32_t i = tid; i < j.tiles; i += kTileBlock) l.hist[i] = 0;
+  __syncthreads();
+  uint32_t tl[PER], rank[PER];
+#pragma unroll
+  for (uint32_t r = 0; r < PER; ++r) {
+    tl[r] = (uint32_t)(tile_home(j.t, k[r]) >> j.shift);
+    rank[r] = 0;
+    if (r * kTileBlock + tid < m)
+      rank[r] = __hip_atomic_fetch_add(&l.hist[tl[r]], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __syncthreads();
+  // exclusive scan of the counts: consecutive counters per thread, then over
+  // the wave and the block
+  const uint32_t per = (j.tiles + kTileBlock - 1) / kTileBlock;
+  const uint32_t a = tid * per < j.tiles ? tid * per : j.tiles;
+  const uint32_t z = a + per < j.tiles ? a + per : j.tiles;
+  uint32_t mine = 0;
+  for (uint32_t i = a; i < z; ++i) mine += l.hist[i];
+  const uint32_t incl = tile_wave_inclusive(mine);
+  if (lane_id() == kWave - 1) l.wsum[tid / kWave] = incl;
+  __syncthreads();
+  uint32_t run = incl - mine;
+  for (uint32_t w = 0; w < tid / kWave; ++w) run += l.wsum[w];
+  uint16_t* off = j.off + (uint64_t)c * (j.tiles + 1);
+  for (uint32_t i = a; i < z; ++i) {
+    const uint32_t v = l.hist[i];
+    l.hist[i] = run;
+    off[i] = (uint16_t)run;
+    run += v;
+  }
+  if (tid == 0) off[j.tiles] = (uint16_t)m;
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < PER; ++r) {
+    const uint32_t i = r * kTileBlock + tid;
+    if (i < m) {
+      const uint32_t p = l.hist[tl[r]] + rank[r];
+      l.key[p] = k[r];
+      l.idx[p] = (uint16_t)i;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < PER; ++r) {
+    const uint32_t i = r * kTileBlock + tid;
+    if (i < m) {
+      j.skey[base + i] = l.key[i];
+      j.sidx[base + i] = l.idx[i];
+    }
+  }
+}
+
+// ---- tile ---------------------------------------------------------------------
+
+__device__ __forceinline__ uint64_t lds_cas(uint64_t* p, uint64_t want, uint64_t v) {
+  __hip_atomic_compare_exchange_strong(p, &want, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+  return want;
+}
+
+// Find-or-put of key k in the B slots at `bk` in LDS: 1 placed, 0 present,
+// kTileMore when they are full of other keys.  The tile pass is bound by the
+// instructions and turns of this loop where a batch fills its table (keys of
+// one bucket meet and retry: 9 of the 19 us for 2^20 keys into 2^21 slots of
+// 8-slot buckets).  Tried in its place: all 8 slots read before any
+// compare-and-swap, 15 us; one-byte tags, eight to a word that is
+// compare-and-swapped, 10 us (13 against 16 us at B = 16); four-bit tags, 15 us; slot pairs
+// rotated by bucket against bank conflicts, no change.
+__device__ __forceinline__ uint32_t lds_bucket_put(uint64_t* bk, uint32_t B, uint64_t k) {
+  for (uint32_t q = 0; q < B; q += 2) {
+    const ulonglong2 x = *reinterpret_cast<const ulonglong2*>(bk + q);
+    uint64_t v = x.x;
+    if (v == kEmpty) v = lds_cas(bk + q, kEmpty, k);
+    if (v == kEmpty) return 1;
+    if (v == k) return 0;
+    v = x.y;
+    if (v == kEmpty) v = lds_cas(bk + q + 1, kEmpty, k);
+    if (v == kEmpty) return 1;
+    if (v == k) return 0;
+  }
+  return kTileMore;
+}
+
+struct TileLds {
+  uint64_t slot[kTileSlots];
+  uint32_t nnew;            // new keys of the block
+};
+
+// A tile's slots between the table and LDS (buckets are multiples of 8 slots).
+__device__ __forceinline__ void tile_load(uint64_t* lds, const uint64_t* slots, uint32_t ns) {
+  for (uint32_t i = threadIdx.x; i < ns / 2; i += kTileBlock)
+    reinterpret_cast<ulonglong2*>(lds)[i] = reinterpret_cast<const ulonglong2*>(slots)[i];
+}
+
+__device__ __forceinline__ void tile_store(const uint64_t* lds, uint64_t* slots, uint32_t ns) {
+  for (uint32_t i = threadIdx.x; i < ns / 2; i += kTileBlock)
+    reinterpret_cast<ulonglong2*>(slots)[i] = reinterpret_cast<const ulonglong2*>(lds)[i];
+}
+
+// Insert every key of tile `tl` in LDS.  A group of run_lanes lanes serves a
+// chunk's run; U runs per group are in flight together, and the first runs'
+// bounds and keys are loaded with the tile.
+template <uint32_t C>
+__device__ __forceinline__ void tile_insert_keys(const TileJob& j, uint32_t tl, TileLds& l) {
+  constexpr uint32_t U = 4;
+  const uint32_t tid = threadIdx.x;
+  const uint64_t first = (uint64_t)tl << j.shift;
+  const uint64_t nslots = j.t.nrange * j.t.bucket_slots;
+  const uint64_t left = nslots - first;
+  const uint32_t ns = left < (1ull << j.shift) ? (uint32_t)left : 1u << j.shift;
+  const uint32_t G = j.run_lanes;
+  const uint32_t gl = tid & (G - 1);
+  const uint32_t groups = kTileBlock / G;
+  uint32_t e[U], z[U];
+  uint64_t k[U];
+  const auto bounds = [&](uint32_t c0) {
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t c = c0 + u * groups;
+      e[u] = z[u] = 0;
+      if (c < j.chunks) {
+        const uint16_t* off = j.off + (uint64_t)c * (j.tiles + 1) + tl;
+        e[u] = off[0] + gl;
+        z[u] = off[1];
+      }
+    }
+  };
+  const auto keys = [&](uint32_t c0) {
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u)
+      k[u] = e[u] < z[u] ? j.skey[(uint64_t)(c0 + u * groups) * C + e[u]] : 0;
+  };
+  uint32_t c0 = tid / G;
+  bounds(c0);
+  if (tid == 0) l.nnew = 0;
+  tile_load(l.slot, j.t.slots + first, ns);
+  keys(c0);
+  __syncthreads();
+  uint32_t nnew = 0;
+  for (;;) {
+    bool more = false;
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      if (e[u] < z[u]) {
+        const uint32_t r = k[u] == kEmpty
+                               ? sentinel_put(j.t)
+                               : lds_bucket_put(l.slot + (tile_home(j.t, k[u]) - first), j.t.bucket_slots, k[u]);
+        nnew += r == 1;
+        j.sflag[(uint64_t)(c0 + u * groups) * C + e[u]] = (uint8_t)r;
+        e[u] += G;
+        more |= e[u] < z[u];
+      }
+    }
+    if (!more) {
+      c0 += U * groups;
+      if (c0 >= j.chunks) break;
+      bounds(c0);
+    }
+    keys(c0);
+  }
+  block_count(j.t.ctr->size, nnew, &l.nnew, tl);
+  if (l.nnew) tile_store(l.slot, j.t.slots + first, ns);
+}
+
+// Tile of a block of the tile pass: consecutive tiles share lines of the run
+// starts and of the sorted keys, so each XCD (blocks are dealt to the eight in
+// turn) takes a contiguous share of them.
+__device__ __forceinline__ uint32_t tile_of_block(uint32_t b, uint32_t tiles) {
+  return (b & 7) * ((tiles + 7) / 8) + (b >> 3);
+}
+
+// ---- finish -------------------------------------------------------------------
+
+// The rest of key k's probe sequence, from position 1 on, in the table.
+__device__ __forceinline__ uint32_t tile_bucketed_rest(const DevTable& t, uint64_t k) {
+  const uint32_t B = t.bucket_slots;
+  const uint32_t nseq = t.nhash + t.walk;
+  uint64_t b = hidx<false>(t, k, 0);
+  for (uint32_t j = 1; j < nseq; ++j) {
+    b = probe_bucket<false>(t, k, j, b);
+    uint64_t* bk = t.slots + b * B;
+    for (uint32_t c0 = 0; c0 < B; c0 += 8) {
+      uint64_t x[8];
+      load8(bk + c0, x);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        uint64_t v = x[q];
+        if (v == kEmpty) v = cas64(bk + c0 + q, kEmpty, k);
+        if (v == kEmpty) return 1;
+        if (v == k) return 0;
+      }
+    }
+  }
+  return stash_put(t, k);
+}
+
+template <uint32_t C>
+struct TileFinishLds {
+  uint64_t mkey[C];         // keys that go on at h_2
+  uint16_t midx[C];         // and their places in the chunk
+  uint8_t flag[C];
+  uint32_t nmore;
+  uint32_t nnew;
+};
+
+// Finish chunk `c`: flags back into batch order, and the rest of the keys
+// marked kTileMore.
+template <uint32_t C>
+__device__ __forceinline__ void tile_finish_chunk(const TileJob& j, uint32_t c, TileFinishLds<C>& l) {
+  constexpr uint32_t PER = C / kTileBlock;
+  const uint32_t tid = threadIdx.x;
+  const uint64_t base = (uint64_t)c * C;
+  const uint32_t m = j.n - base < C ? (uint32_t)(j.n - base) : C;
+  uint32_t f[PER], x[PER];
+  uint64_t k[PER];
+#pragma unroll
+  for (uint32_t r = 0; r < PER; ++r) {
+    const uint32_t i = r * kTileBlock + tid;
+    f[r] = i < m ? j.sflag[base + i] : 0u;
+    x[r] = i < m ? j.sidx[base + i] : 0u;
+    k[r] = i < m ? j.skey[base + i] : 0u;
+  }
+  if (tid == 0) l.nmore = l.nnew = 0;
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < PER; ++r) {
+    const bool in = r * kTileBlock + tid < m;
+    const bool more = in && f[r] == kTileMore;
+    const uint64_t mm = ballot(more);
+    uint32_t at = 0;
+    if (mm && lane_id() == 0)
+      at = __hip_atomic_fetch_add(&l.nmore, (uint32_t)__popcll(mm), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    at = shfl32(at, 0) + lanes_below(mm);
+    if (more) {
+      l.mkey[at] = k[r];
+      l.midx[at] = (uint16_t)x[r];
+    } else if (in) {
+      l.flag[x[r]] = (uint8_t)f[r];
+    }
+  }
+  __syncthreads();
+  const uint32_t nmore = l.nmore;
+  uint32_t nnew = 0;
+  for (uint32_t e = tid; e < nmore; e += kTileBlock) {
+    const uint32_t r = tile_bucketed_rest(j.t, l.mkey[e]);
+    nnew += r == 1;
+    l.flag[l.midx[e]] = (uint8_t)r;
+  }
+  block_count(j.t.ctr->size, nnew, &l.nnew, c);      // a barrier: every flag is in place
+  if (!j.out) return;
+  uint8_t* out = j.out + base;
+  uint32_t done = 0;
+  if ((reinterpret_cast<uintptr_t>(out) & 3) == 0) {
+    done = m & ~3u;
+    for (uint32_t i = 4 * tid; i < done; i += 4 * kTileBlock)
+      *reinterpret_cast<uint32_t*>(out + i) = *reinterpret_cast<const uint32_t*>(l.flag + i);
+  }
+  for (uint32_t i = done + tid; i < m; i += kTileBlock) out[i] = l.flag[i];
+}
+
+// ---- small tables -------------------------------------------------------------
+// A table that fits in one tile needs no partition: one block holds
+// the whole table in LDS and runs every key's whole probe sequence there.
+
+__device__ __forceinline__ uint32_t lds_find_or_put(const DevTable& t, uint64_t* lds, uint64_t k) {
+  if (k == kEmpty) return sentinel_put(t);
+  const uint32_t nseq = t.nhash + t.walk;
+  uint64_t b = 0;
+  for (uint32_t j = 0; j < nseq; ++j) {
+    b = probe_bucket<false>(t, k, j, b);
+    const uint32_t r = lds_bucket_put(lds + b * t.bucket_slots, t.bucket_slots, k);
+    if (r != kTileMore) return r;
+  }
+  return stash_put(t, k);
+}
+
+__device__ __forceinline__ void tile_whole_table(const DevTable& t, const uint64_t* __restrict__ keys, uint64_t n,
+                                                 uint8_t* __restrict__ out, TileLds& l) {
+  const uint32_t tid = threadIdx.x;
+  const uint32_t ns = (uint32_t)(t.nrange * t.bucket_slots);
+  uint64_t k = tid < n ? keys[tid] : 0;      // goes out with the table's loads
+  if (tid == 0) l.nnew = 0;
+  tile_load(l.slot, t.slots, ns);
+  __syncthreads();
+  uint32_t nnew = 0;
+  for (uint64_t i = tid; i < n; i += kTileBlock) {
+    const uint64_t next = i + kTileBlock < n ? keys[i + kTileBlock] : 0;
+    const uint32_t r = lds_find_or_put(t, l.slot, k);
+    if (out) out[i] = (uint8_t)r;
+    nnew += r == 1;
+    k = next;
+  }
+  block_count(t.ctr->size, nnew, &l.nnew, 0);
+  if (l.nnew) tile_store(l.slot, t.slots, ns);
+}
+
+}  // namespace ht
