@@ -261,55 +261,6 @@ struct SuccIter {
   }
 };
 
-constexpr uint32_t kListed = 2;   // every candidate taken: listed for the evict pass
-
-// Probe and place of one key per lane (called by every lane of the wave; act
-// false for lanes without a key), as the single-table Cuckoo probe kernel
-// does it: h_1, h_2, ... are read in turn, the key found ends the search, an
-// empty candidate is compare-and-swapped at once (keys whose slot indices
-// coincide read all c first and then try the empty ones in order).  Returns
-// 1 placed, 0 found (or another copy placed it), kListed when every candidate
-// is taken.
-__device__ __forceinline__ uint32_t cuckoo_probe_key(const DevTable& t, uint64_t k, bool act, uint32_t sc,
-                                                     uint32_t oc) {
-  uint32_t res = 0;
-  bool pend = act && k != kEmpty;
-  if (act && k == kEmpty) res = sentinel_put(t);
-  if (pend && (sc | oc) && stash_query(t, k, sc, oc)) pend = false;
-  const bool dist = pend && hashes_distinct<false>(t, k);
-  uint32_t em = 0;
-  for (uint32_t j = 0; j < t.nhash && ballot(pend); ++j) {
-    uint64_t idx = 0, v = 0;
-    if (pend) {
-      idx = hidx<false>(t, k, j);
-      v = t.slots[idx];
-    }
-    bool cas = false;
-    if (pend) {
-      if (v == k) pend = false;
-      else if (v == kEmpty) {
-        if (dist) cas = true;
-        else em |= 1u << j;
-      }
-    }
-    if (cas) {
-      const uint64_t old = cas64(&t.slots[idx], kEmpty, k);
-      if (old == kEmpty) res = 1;
-      if (old == kEmpty || old == k) pend = false;
-    }
-  }
-  while (ballot(pend && em)) {
-    if (pend && em) {
-      const uint32_t j = (uint32_t)__builtin_ctz(em);
-      em &= em - 1;
-      const uint64_t old = cas64(&t.slots[hidx<false>(t, k, j)], kEmpty, k);
-      if (old == kEmpty) res = 1;
-      if (old == kEmpty || old == k) pend = false;
-    }
-  }
-  return pend ? kListed : res;
-}
-
 // Fused Cuckoo pass 1: a wave takes groups g0 .. g1-1 of 64 frontier states,
 // one state per lane, and steps through their successors together; each
 // successor is probed and placed as above, new ones marked in the state's mask
@@ -344,7 +295,7 @@ __global__ __launch_bounds__(kBlock) void bfs_cuckoo_probe_kernel(BfsModelDev m,
       uint64_t succ = 0;
       const bool has = live && it.next(m, succ);
       if (!ballot(has)) break;
-      const uint32_t r = cuckoo_probe_key(t, succ, has, sc, oc);
+      const uint32_t r = cuckoo_probe_key(t, t.slots, succ, has, sc, oc);
       if (has && r == 1) {
         if (k < 64) m0 |= 1ull << k;
         else m1 |= 1ull << (k - 64);
@@ -419,8 +370,8 @@ __global__ __launch_bounds__(kBlock) void bfs_cuckoo_evict_kernel(DevTable t, ui
       uint64_t y = k;
       uint32_t steps = 0;
       const uint64_t h1 = hidx<false>(t, y, 0);
-      const bool placed = (t.flags & kFlagLookahead) ? cuckoo_chain<false, true>(t, y, h1, nevict, steps)
-                                                      : cuckoo_chain<false, false>(t, y, h1, nevict, steps);
+      const bool placed = (t.flags & kFlagLookahead) ? cuckoo_chain<false, true>(t, t.slots, t.nhash, y, h1, nevict, steps)
+                                                      : cuckoo_chain<false, false>(t, t.slots, t.nhash, y, h1, nevict, steps);
       if (!placed) stash_put(t, y);
       ++mine;
     }

@@ -47,6 +47,21 @@ hipError_t cuckoo_probe(const DevTable& t, const uint64_t* keys, uint64_t n, uin
   return hipGetLastError();
 }
 
+// Both phases in one block, the table in LDS.
+hipError_t cuckoo_whole(const DevTable& t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t st) {
+  if (t.nrange > kWholeSlots || n > kWholeKeys) return hipErrorInvalidValue;
+  const dim3 g(1), b(kWholeBlock);
+  if (t.flags & kFlagLookahead)
+    hipLaunchKernelGGL((cuckoo_whole_kernel<0, true>), g, b, 0, st, t, keys, (uint32_t)n, out);
+  else if (t.nhash == 3)
+    hipLaunchKernelGGL((cuckoo_whole_kernel<3, false>), g, b, 0, st, t, keys, (uint32_t)n, out);
+  else if (t.nhash == 4)
+    hipLaunchKernelGGL((cuckoo_whole_kernel<4, false>), g, b, 0, st, t, keys, (uint32_t)n, out);
+  else
+    hipLaunchKernelGGL((cuckoo_whole_kernel<0, false>), g, b, 0, st, t, keys, (uint32_t)n, out);
+  return hipGetLastError();
+}
+
 // The paper's single-pass insertion (ablation; see cuckoo_dev.h).
 hipError_t cuckoo_single_pass(const DevTable& t, const uint64_t* keys, uint64_t n, uint8_t* out, uint32_t grid,
                               bool scripted, hipStream_t st) {

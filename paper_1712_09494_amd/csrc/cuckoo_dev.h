@@ -323,6 +323,7 @@ __global__ __launch_bounds__(kBlock) void cuckoo_probe_kernel(DevTable t, const 
 // Eviction chain of Sec. 4.1 for key x starting at slot index `slot` (which
 // is h_j0(x)).  Returns true when the chain ended on an empty slot; on false
 // `x` holds the key left without a slot.  `steps` counts the exchanges.
+// `slots`: the table's, or their copy in LDS; `c` is t.nhash.
 //
 // With the lookahead flag (kFlagLookahead), a key y evicted from h_a(y)
 // first reads its later candidates h_{a+1}(y), ..., h_c(y) (one load each,
@@ -333,11 +334,10 @@ __global__ __launch_bounds__(kBlock) void cuckoo_probe_kernel(DevTable t, const 
 // are taken (y sat at h_a, which the evicting key now holds) and
 // h_{a+1}..h_{j-1} were seen taken, and slots never empty again.
 template <bool SCRIPTED, bool LOOK>
-__device__ __forceinline__ bool cuckoo_chain(const DevTable& t, uint64_t& x, uint64_t slot,
-                                             unsigned long long& nevict, uint32_t& steps) {
-  const uint32_t c = t.nhash;
+__device__ __forceinline__ bool cuckoo_chain(const DevTable& t, uint64_t* slots, uint32_t c, uint64_t& x,
+                                             uint64_t slot, unsigned long long& nevict, uint32_t& steps) {
   for (uint32_t step = 0;; ++step) {
-    const uint64_t old = exch64(&t.slots[slot], x);
+    const uint64_t old = exch64(&slots[slot], x);
     ++steps;
     if (old == kEmpty) return true;
     x = old;
@@ -352,9 +352,9 @@ __device__ __forceinline__ bool cuckoo_chain(const DevTable& t, uint64_t& x, uin
       }
       if (a + 1 < (int)c) {
         uint64_t v[kMaxHash];
-        for (uint32_t j = (uint32_t)(a + 1); j < c; ++j) v[j] = h[j] != slot ? t.slots[h[j]] : 0;
+        for (uint32_t j = (uint32_t)(a + 1); j < c; ++j) v[j] = h[j] != slot ? slots[h[j]] : 0;
         for (uint32_t j = (uint32_t)(a + 1); j < c; ++j) {
-          if (h[j] != slot && v[j] == kEmpty && cas64(&t.slots[h[j]], kEmpty, x) == kEmpty) return true;
+          if (h[j] != slot && v[j] == kEmpty && cas64(&slots[h[j]], kEmpty, x) == kEmpty) return true;
         }
       }
     }
@@ -449,7 +449,7 @@ __device__ __forceinline__ void cuckoo_evict_regions(const DevTable& t, uint64_t
     if (!winner) continue;
     uint64_t y = k;
     uint32_t steps = 0;
-    const bool placed = cuckoo_chain<SCRIPTED, LOOK>(t, y, hidx<SCRIPTED>(t, y, 0), nevict, steps);
+    const bool placed = cuckoo_chain<SCRIPTED, LOOK>(t, t.slots, t.nhash, y, hidx<SCRIPTED>(t, y, 0), nevict, steps);
     if (!placed) stash_put(t, y);        // y may be another key than the winner's
     chain_record(t, steps, placed, r);
     ++nnew;
@@ -559,6 +559,188 @@ __device__ __forceinline__ void cuckoo_scrub_region(uint64_t n, const CuckooScra
     const uint64_t p = s.wmeta[begin + e];
     if (p != ~0ull) s.dset[p] = kEmpty;
   }
+}
+
+constexpr uint32_t kListed = 2;   // every candidate taken: listed for the evict pass
+
+// Probe and place of one key per lane (called by every lane of the wave; act
+// false for lanes without a key; `slots` as above), as the single-table Cuckoo probe kernel
+// does it: h_1, h_2, ... are read in turn, the key found ends the search, an
+// empty candidate is compare-and-swapped at once (keys whose slot indices
+// coincide read all c first and then try the empty ones in order).  Returns
+// 1 placed, 0 found (or another copy placed it), kListed when every candidate
+// is taken.
+__device__ __forceinline__ uint32_t cuckoo_probe_key(const DevTable& t, uint64_t* slots, uint64_t k, bool act,
+                                                     uint32_t sc, uint32_t oc) {
+  uint32_t res = 0;
+  bool pend = act && k != kEmpty;
+  if (act && k == kEmpty) res = sentinel_put(t);
+  if (pend && (sc | oc) && stash_query(t, k, sc, oc)) pend = false;
+  const bool dist = pend && hashes_distinct<false>(t, k);
+  uint32_t em = 0;
+  for (uint32_t j = 0; j < t.nhash && ballot(pend); ++j) {
+    uint64_t idx = 0, v = 0;
+    if (pend) {
+      idx = hidx<false>(t, k, j);
+      v = slots[idx];
+    }
+    bool cas = false;
+    if (pend) {
+      if (v == k) pend = false;
+      else if (v == kEmpty) {
+        if (dist) cas = true;
+        else em |= 1u << j;
+      }
+    }
+    if (cas) {
+      const uint64_t old = cas64(&slots[idx], kEmpty, k);
+      if (old == kEmpty) res = 1;
+      if (old == kEmpty || old == k) pend = false;
+    }
+  }
+  while (ballot(pend && em)) {
+    if (pend && em) {
+      const uint32_t j = (uint32_t)__builtin_ctz(em);
+      em &= em - 1;
+      const uint64_t old = cas64(&slots[hidx<false>(t, k, j)], kEmpty, k);
+      if (old == kEmpty) res = 1;
+      if (old == kEmpty || old == k) pend = false;
+    }
+  }
+  return pend ? kListed : res;
+}
+
+// ---- small tables -------------------------------------------------------------
+// A batch into a small table: one block holds the table in LDS and runs both
+// phases there, a barrier between them in place of the kernel boundary.  The
+// two kernels' time for such a batch is the latency of their dependent memory
+// operations, a memory-side exchange for every step of the longest chain: 4096
+// keys into 8192 slots 20.5 us, here 13.2.  The keys left over are listed for
+// the second phase, so that their chains run side by side (24.5 us with each
+// thread running those of its own keys in turn).
+constexpr uint32_t kWholeSlots = 8192;      // most slots: 64 KiB of LDS
+constexpr uint32_t kWholeKeys = 8192;       // most keys: the set has twice as many places
+constexpr uint32_t kWholeBlock = 1024;
+
+struct CuckooWholeLds {
+  uint64_t slot[kWholeSlots];
+  uint32_t set[2 * kWholeKeys];             // batch indices of the leftover keys (~0: empty)
+  uint16_t left[kWholeKeys];                // batch indices of the keys left over by the first phase
+  uint32_t nleft, nnew, nevict;
+};
+
+// Probe and place key k in the LDS slots, as cuckoo_probe_key does, for C hash
+// functions known at compile time: one key's hashes are computed once.  The
+// pass is bound by their instructions: 4096 keys already stored took 13.7 us
+// with cuckoo_probe_key, which computes them again for every use, and take
+// 9.1.
+template <uint32_t C>
+__device__ __forceinline__ uint32_t cuckoo_whole_probe(const DevTable& t, uint64_t* slots, uint64_t k, uint32_t sc,
+                                                       uint32_t oc) {
+  if (k == kEmpty) return sentinel_put(t);
+  if ((sc | oc) && stash_query(t, k, sc, oc)) return 0;
+  uint64_t h[C];
+#pragma unroll
+  for (uint32_t j = 0; j < C; ++j) h[j] = hidx<false>(t, k, j);
+  bool dist = true;
+#pragma unroll
+  for (uint32_t a = 0; a < C; ++a)
+#pragma unroll
+    for (uint32_t b = a + 1; b < C; ++b) dist &= h[a] != h[b];
+  uint32_t em = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < C; ++j) {
+    uint64_t v = __hip_atomic_load(slots + h[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (v == kEmpty && dist) {
+      v = cas64(slots + h[j], kEmpty, k);
+      if (v == kEmpty) return 1;
+    }
+    if (v == k) return 0;
+    if (v == kEmpty) em |= 1u << j;
+  }
+#pragma unroll
+  for (uint32_t j = 0; j < C; ++j) {         // coinciding indices: all were read first
+    if (em >> j & 1u) {
+      const uint64_t v = cas64(slots + h[j], kEmpty, k);
+      if (v == kEmpty) return 1;
+      if (v == k) return 0;
+    }
+  }
+  return kListed;
+}
+
+// C: the table's hash functions, or 0 for any number.
+template <uint32_t C, bool LOOK>
+__global__ __launch_bounds__(kWholeBlock) void cuckoo_whole_kernel(DevTable t, const uint64_t* __restrict__ keys,
+                                                                   uint32_t n, uint8_t* __restrict__ out) {
+  __shared__ CuckooWholeLds l;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t pairs = (uint32_t)(t.nrange / 2);          // a multiple of 16 slots
+  const uint32_t sc = t.ctr->stash_count;
+  const uint32_t oc = t.ctr->overflow_count;
+  uint64_t k = tid < n ? keys[tid] : 0;                     // goes out with the table's loads
+  for (uint32_t i = tid; i < pairs; i += kWholeBlock)
+    reinterpret_cast<ulonglong2*>(l.slot)[i] = reinterpret_cast<const ulonglong2*>(t.slots)[i];
+  for (uint32_t i = tid; i < 2 * kWholeKeys / 4; i += kWholeBlock)
+    reinterpret_cast<uint4*>(l.set)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+  if (tid == 0) l.nleft = l.nnew = l.nevict = 0;
+  __syncthreads();
+  // probe and place; the keys left over are listed
+  uint32_t nnew = 0;
+  for (uint32_t i0 = 0; i0 < n; i0 += kWholeBlock) {
+    const uint32_t i = i0 + tid;
+    const bool act = i < n;
+    const uint64_t next = i + kWholeBlock < n ? keys[i + kWholeBlock] : 0;
+    uint32_t res = 0;
+    if constexpr (C == 0) res = cuckoo_probe_key(t, l.slot, k, act, sc, oc);
+    else if (act) res = cuckoo_whole_probe<C>(t, l.slot, k, sc, oc);
+    const bool left = act && res == kListed;
+    const uint64_t mm = ballot(left);
+    uint32_t at = 0;
+    if (mm && lane_id() == 0)
+      at = __hip_atomic_fetch_add(&l.nleft, (uint32_t)__popcll(mm), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    at = shfl32(at, 0) + lanes_below(mm);
+    if (left) {
+      l.left[at] = (uint16_t)i;
+    } else if (act) {
+      if (out) out[i] = (uint8_t)res;
+      nnew += res;
+    }
+    k = next;
+  }
+  __syncthreads();
+  // one winner per listed key, and its eviction chain
+  unsigned long long nevict = 0;
+  for (uint32_t e = tid; e < l.nleft; e += kWholeBlock) {
+    const uint32_t i = l.left[e];
+    const uint64_t x = keys[i];
+    uint32_t p = (uint32_t)mix64(x ^ t.stash_seed) & (2 * kWholeKeys - 1);
+    bool winner = false;
+    for (;;) {
+      uint32_t old = ~0u;
+      if (__hip_atomic_compare_exchange_strong(&l.set[p], &old, i, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP)) {
+        winner = true;
+        break;
+      }
+      if (keys[old] == x) break;             // another copy won
+      p = (p + 1) & (2 * kWholeKeys - 1);
+    }
+    if (out) out[i] = winner ? 1 : 0;
+    if (!winner) continue;
+    uint64_t y = x;
+    uint32_t steps = 0;
+    const bool placed =
+        cuckoo_chain<false, LOOK>(t, l.slot, C ? C : t.nhash, y, hidx<false>(t, x, 0), nevict, steps);
+    if (!placed) stash_put(t, y);
+    chain_record(t, steps, placed, tid / kWave);
+    ++nnew;
+  }
+  block_count(t.ctr->size, nnew, &l.nnew, 0);
+  block_count(t.ctr->evictions, (uint32_t)nevict, &l.nevict, 0);
+  if (!l.nnew) return;
+  for (uint32_t i = tid; i < pairs; i += kWholeBlock)
+    reinterpret_cast<ulonglong2*>(t.slots)[i] = reinterpret_cast<const ulonglong2*>(l.slot)[i];
 }
 
 }  // namespace ht

@@ -31,6 +31,7 @@ hipError_t cuckoo_probe(const DevTable&, const uint64_t*, uint64_t, uint8_t*, co
                         uint32_t, bool, bool, hipStream_t);
 hipError_t cuckoo_evict(const DevTable&, uint64_t, uint8_t*, const CuckooScratch&, uint32_t, uint32_t, bool,
                         hipStream_t);
+hipError_t cuckoo_whole(const DevTable&, const uint64_t*, uint64_t, uint8_t*, hipStream_t);
 hipError_t cuckoo_single_pass(const DevTable&, const uint64_t*, uint64_t, uint8_t*, uint32_t, bool, hipStream_t);
 hipError_t cuckoo_scrub(uint64_t, const CuckooScratch&, uint32_t, hipStream_t);
 hipError_t vec_evict(const DevTable&, const uint64_t*, uint64_t, uint8_t*, const CuckooScratch&, uint32_t,
@@ -352,6 +353,21 @@ static bool tile_whole_rule(const ht_table* t, uint64_t n) {
   return tile_table(t) && t->nslots <= kTileSlots && n >= 512 && n <= 2048 && t->puts < n;
 }
 
+// Whether one block does a Cuckoo call with the table in LDS (8192 slots,
+// c = 3, load factor 0.5, two kernels and one block, new keys and keys already
+// stored: 16 keys 7.9 and 3.9 us, 10.2 and 5.4; 1024 keys 9.4 and 5.0, 9.7 and
+// 6.1; 4096 keys 20.5 and 13.2, 10.0 and 9.1; 8192 keys, half of them repeats,
+// 18.8 and 18.7, 10.1 and 13.8; at load factor 0.7 31.6 and 25.0).  Beyond 4096
+// keys only for a batch larger than all that was put before it.  The kernel
+// for c other than 3 and 4 and the lookahead insertion recompute hashes: 1024
+// keys take what c = 3 takes for 2048.
+static bool cuckoo_whole_rule(const ht_table* t, uint64_t n) {
+  if (t->cfg.kind != HT_CUCKOO || t->cfg.key_words > 1 || t->cfg.lds_bytes || t->nslots > kTileSlots) return false;
+  if (t->cfg.flags & (HT_FLAG_SCRIPTED_HASH | HT_FLAG_CUCKOO_PAPER_ORDER | HT_FLAG_CUCKOO_SINGLE_PASS)) return false;
+  if ((t->cfg.nhash != 3 && t->cfg.nhash != 4) || (t->cfg.flags & HT_FLAG_CUCKOO_LOOKAHEAD)) return n <= 1024;
+  return n <= 4096 || (n <= 8192 && t->puts < n);
+}
+
 // Workspace of the tiled passes; false (the direct kernels serve the call)
 // when it cannot be allocated or the stream is being captured.
 static bool tile_workspace(ht_table* t, size_t bytes, hipStream_t s) {
@@ -583,7 +599,7 @@ int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, 
     HT_HIP(bucketed_lane_find_or_put(d, keys, n, out, (uint32_t)blocks, scripted, s));
     return HT_OK;
   }
-  const bool whole = tile_whole_rule(t, n);
+  const bool whole = tile_whole_rule(t, n), cwhole = cuckoo_whole_rule(t, n);
   const bool tiled = !repeats && !g_quiet && tile_rule(t, n);
   t->puts += n;
   if (whole) {
@@ -608,6 +624,11 @@ int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, 
     const uint64_t blocks = std::min<uint64_t>((n + kBlock - 1) / kBlock, max_blocks(t));
     KernelTimer kt("cuckoo_single_pass", s);
     HT_HIP(cuckoo_single_pass(d, keys, n, out, (uint32_t)blocks, scripted, s));
+    return HT_OK;
+  }
+  if (cwhole) {
+    KernelTimer kt("cuckoo_whole", s);
+    HT_HIP(cuckoo_whole(d, keys, n, out, s));
     return HT_OK;
   }
   CuckooScratch sc{};

@@ -51,18 +51,6 @@ __device__ __forceinline__ uint32_t tile_wave_inclusive(uint32_t v) {
   return v;
 }
 
-// Add the block's lanes' counts to a spread counter: one atomic per block (an
-// atomic per wave puts five hundred of them on each of the sixteen lines in a
-// 2^20-key call: 4 us of the tile pass).  *sum (LDS) is zero before; it holds
-// the block's total afterwards, behind a barrier.
-__device__ __forceinline__ void block_count(unsigned long long* spread, uint32_t v, uint32_t* sum, uint32_t salt) {
-  const unsigned long long s = wave_sum(v);
-  if (lane_id() == 0 && s)
-    __hip_atomic_fetch_add(sum, (uint32_t)s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  __syncthreads();
-  if (threadIdx.x == 0 && *sum) add_agent(&spread[(salt % kSpread) * kLineWords], (unsigned long long)*sum);
-}
-
 // ---- partition ---------------------------------------------------------------
 
 template <uint32_t C>
