@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "ht_device.h"
+#include "tile.h"
 
 namespace ht {
 
@@ -18,6 +19,7 @@ struct MultiSpec {
   const uint64_t* keys;
   uint8_t* out;
   uint64_t n;
+  bool tiled;               // may be filled by the tiled passes
 };
 
 // One Cuckoo table of a many-table launch.  `s` is the table's scratch view
@@ -64,12 +66,23 @@ struct MultiPlanDev {
   void* base = nullptr;
   uint32_t nitems = 0, ncitems = 0;
   uint32_t grid = 0, cgrid = 0;
+  // a second way to fill the bucketed tables: the tiled passes (tile_dev.h)
+  // for those that can take them, items only of the others for the
+  // persistent launch
+  TileJob* jobs = nullptr;
+  uint64_t* chunks = nullptr;
+  uint64_t* tiles = nullptr;
+  uint64_t* rest = nullptr;
+  void* tile_base = nullptr;
+  uint32_t njobs = 0, nchunks = 0, ntiles = 0, nrest = 0, rest_grid = 0;
 };
 
 hipError_t multi_plan_build(const std::vector<MultiSpec>& specs, const std::vector<MultiCuckooSpec>& cspecs,
                             uint32_t max_blocks, MultiPlanDev& plan);
 void multi_plan_free(MultiPlanDev& plan);
 hipError_t multi_plan_launch(const MultiPlanDev& plan, hipStream_t s);
+// The bucketed tables by the tiled passes (plans with njobs > 0).
+hipError_t multi_plan_launch_tiled(const MultiPlanDev& plan, hipStream_t s);
 hipError_t multi_cuckoo_launch(const MultiPlanDev& plan, int phase, hipStream_t s);
 
 hipError_t multi_dyn_alloc(MultiDyn& d, uint32_t cap_tabs, uint32_t cap_items);

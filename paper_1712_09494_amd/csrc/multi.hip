@@ -246,8 +246,9 @@ static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 // Fill the descriptors and (table, region) items of `nt` bucketed tables
 // (find-or-put).  Returns the item count, or ~0 when the items would exceed
 // cap_items.
+// With `rest`, items of the tables not marked tiled only.
 static uint64_t fill_bucketed(const MultiSpec* sp, uint32_t nt, uint64_t max_waves, MultiTable* tabs,
-                              uint64_t* items, uint64_t cap_items) {
+                              uint64_t* items, uint64_t cap_items, bool rest = false) {
   uint64_t total = 0;
   for (uint32_t i = 0; i < nt; ++i) total += sp[i].n;
   const uint64_t chunk = multi_chunk(total, max_waves);
@@ -261,6 +262,7 @@ static uint64_t fill_bucketed(const MultiSpec* sp, uint32_t nt, uint64_t max_wav
     m.n = sp[i].n;
     m.chunk = chunk;
     m.nregions = (uint32_t)((sp[i].n + chunk - 1) / chunk);
+    if (rest && sp[i].tiled) continue;
     if (nitems + m.nregions > cap_items) return ~0ull;
     for (uint64_t r = 0; r < m.nregions; ++r) items[nitems++] = make_item(i, r);
   }
@@ -350,6 +352,95 @@ static void launch_query(const MultiQuery* d_tabs, uint32_t nq, uint64_t nitems,
                      nitems);
 }
 
+static uint64_t total_of(const std::vector<MultiSpec>& specs) {
+  uint64_t n = 0;
+  for (const auto& sp : specs) n += sp.n;
+  return n;
+}
+
+// The tiled way of a plan: jobs, items and the passes' workspace in a second
+// device allocation (11 bytes a key; a plan without room for it keeps the
+// persistent launch alone).  Whole small tables come first in the tile pass,
+// since they take longest; the tiles are dealt so that each XCD (blocks go to
+// the eight in turn) takes a contiguous share of them, whose run starts and
+// sorted keys share lines.
+static void build_tiled(const std::vector<MultiSpec>& specs, uint64_t max_waves, MultiPlanDev& plan) {
+  uint32_t count = 0;
+  for (const auto& sp : specs) count += sp.tiled ? 1u : 0u;
+  if (!count) return;
+  const uint32_t min_tiles = std::max<uint32_t>(1, 512 / count);
+  std::vector<TileJob> jobs;
+  std::vector<TileShape> shapes;
+  std::vector<uint64_t> chunks, whole, tiles;
+  size_t ws = 0;
+  for (const auto& sp : specs) {
+    if (!sp.tiled) continue;
+    const uint64_t nslots = sp.t.nrange * sp.t.bucket_slots;
+    const uint32_t id = (uint32_t)jobs.size();
+    TileShape sh{};
+    if (nslots <= kTileSlots) {
+      whole.push_back(tile_item(id, 0));
+    } else {
+      sh = tile_shape(nslots, sp.n, min_tiles, 4096);
+      for (uint32_t c = 0; c < sh.chunks; ++c) chunks.push_back(tile_item(id, c));
+      for (uint32_t c = 0; c < sh.tiles; ++c) tiles.push_back(tile_item(id, c));
+      ws += sh.bytes;
+    }
+    jobs.push_back(tile_job(sp.t, sp.keys, sp.n, sp.out, sh, nullptr));
+    shapes.push_back(sh);
+  }
+  // block b of the tile pass runs on XCD b % 8
+  std::vector<uint64_t> order = whole;
+  const size_t each = (tiles.size() + 7) / 8;
+  for (size_t r = 0; r < each; ++r)
+    for (size_t x = 0; x < 8; ++x)
+      if (x * each + r < tiles.size()) order.push_back(tiles[x * each + r]);
+  const uint64_t cap = total_of(specs) / 64 + specs.size();
+  std::vector<MultiTable> tabs(specs.size());
+  std::vector<uint64_t> rest(cap);
+  const uint64_t nrest = fill_bucketed(specs.data(), (uint32_t)specs.size(), max_waves, tabs.data(), rest.data(), cap,
+                                       true);
+  if (nrest == ~0ull) return;
+  rest.resize(nrest);
+  const size_t b_jobs = align256(sizeof(TileJob) * jobs.size()), b_chunks = align256(chunks.size() * 8),
+               b_tiles = align256(order.size() * 8), b_rest = align256(rest.size() * 8);
+  void* base = nullptr;
+  if (hipMalloc(&base, b_jobs + b_chunks + b_tiles + b_rest + ws) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  char* c = static_cast<char*>(base);
+  char* w = c + b_jobs + b_chunks + b_tiles + b_rest;
+  size_t id = 0;
+  for (const auto& sp : specs) {
+    if (!sp.tiled) continue;
+    jobs[id] = tile_job(sp.t, sp.keys, sp.n, sp.out, shapes[id], w);
+    w += shapes[id].bytes;
+    ++id;
+  }
+  hipError_t e = hipMemcpy(c, jobs.data(), sizeof(TileJob) * jobs.size(), hipMemcpyHostToDevice);
+  if (e == hipSuccess && !chunks.empty())
+    e = hipMemcpy(c + b_jobs, chunks.data(), chunks.size() * 8, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(c + b_jobs + b_chunks, order.data(), order.size() * 8, hipMemcpyHostToDevice);
+  if (e == hipSuccess && !rest.empty())
+    e = hipMemcpy(c + b_jobs + b_chunks + b_tiles, rest.data(), rest.size() * 8, hipMemcpyHostToDevice);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(base);
+    return;
+  }
+  plan.tile_base = base;
+  plan.jobs = reinterpret_cast<TileJob*>(c);
+  plan.chunks = reinterpret_cast<uint64_t*>(c + b_jobs);
+  plan.tiles = reinterpret_cast<uint64_t*>(c + b_jobs + b_chunks);
+  plan.rest = reinterpret_cast<uint64_t*>(c + b_jobs + b_chunks + b_tiles);
+  plan.njobs = (uint32_t)jobs.size();
+  plan.nchunks = (uint32_t)chunks.size();
+  plan.ntiles = (uint32_t)order.size();
+  plan.nrest = (uint32_t)rest.size();
+  plan.rest_grid = multi_grid(plan.nrest, (uint32_t)(max_waves / (kBlock / kWave)));
+}
+
 // Build descriptors and the item lists on the host and copy them to one
 // device allocation (synchronous).  Returns hipSuccess or the HIP error
 // (hipErrorInvalidValue when a Cuckoo table's scratch has too few per-wave
@@ -394,11 +485,13 @@ hipError_t multi_plan_build(const std::vector<MultiSpec>& specs, const std::vect
   if (e == hipSuccess && nc) e = hipMemcpy(plan.ctabs, ctabs.data(), sizeof(MultiCuckoo) * nc, hipMemcpyHostToDevice);
   if (e == hipSuccess && !citems.empty())
     e = hipMemcpy(plan.citems, citems.data(), citems.size() * 8, hipMemcpyHostToDevice);
+  if (e == hipSuccess) build_tiled(specs, max_waves, plan);
   return e;
 }
 
 void multi_plan_free(MultiPlanDev& plan) {
   if (plan.base) (void)hipFree(plan.base);
+  if (plan.tile_base) (void)hipFree(plan.tile_base);
   plan = MultiPlanDev{};
 }
 
@@ -406,6 +499,14 @@ hipError_t multi_plan_launch(const MultiPlanDev& plan, hipStream_t s) {
   if (plan.nitems == 0) return hipSuccess;
   hipLaunchKernelGGL(multi_fill_kernel, dim3(plan.grid), dim3(kBlock), 0, s, plan.tabs, plan.items, plan.nitems);
   return hipGetLastError();
+}
+
+hipError_t multi_plan_launch_tiled(const MultiPlanDev& plan, hipStream_t s) {
+  if (plan.nrest)
+    hipLaunchKernelGGL(multi_fill_kernel, dim3(plan.rest_grid), dim3(kBlock), 0, s, plan.tabs, plan.rest, plan.nrest);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return tile_multi(plan.jobs, plan.chunks, plan.nchunks, plan.tiles, plan.ntiles, s);
 }
 
 // The Cuckoo phases: `phase` 0 = probe and place, 1 = evict, 2 = scrub.

@@ -167,6 +167,8 @@ struct ht_multi_plan {
   std::vector<ht_table*> tables;
   MultiPlanDev dev;           // bucketed persistent launch + Cuckoo phase launches
   std::vector<VecJob> vec;
+  std::vector<uint64_t> keys;           // per table: keys of a launch
+  std::vector<uint8_t> tiled;           // per table: filled by the tiled passes when they run
   uint32_t grid = 0;
 };
 
@@ -341,6 +343,15 @@ static bool tile_rule(const ht_table* t, uint64_t n) {
   if (!tile_table(t) || n < (1ull << 18) || n > (1ull << 25) || t->puts >= n) return false;
   const uint64_t bytes = t->nslots * 8;
   return bytes >= (n < (1ull << 20) ? 11 * n : 9 * n) && bytes <= 64 * n &&
+         t->nslots <= (uint64_t)kTileMax * kTileSlots;
+}
+
+// Whether a table of a many-table plan is filled by the tiled passes: their
+// launches are shared, so the batch's size does not matter, only that the
+// table has room for it and is not large against it.
+static bool plan_tile_rule(const ht_table* t, uint64_t n) {
+  const uint64_t bytes = t->nslots * 8;
+  return tile_table(t) && n >= 64 && n <= (1ull << 25) && bytes >= 9 * n && bytes <= 64 * n &&
          t->nslots <= (uint64_t)kTileMax * kTileSlots;
 }
 
@@ -838,8 +849,10 @@ int ht_query(ht_table* t, const uint64_t* d_keys, uint64_t n, uint8_t* d_out_fou
   return do_query(t, d_keys, n, d_out_found, s);
 }
 
-int ht_multi_plan_create(ht_table* const* t, const uint64_t* const* d_keys, const uint64_t* n,
-                         uint8_t* const* d_out_is_new, uint32_t ntables, ht_multi_plan** out) {
+// `once`: for a single launch, which does not pay for the tiled passes'
+// workspace.
+static int plan_create(ht_table* const* t, const uint64_t* const* d_keys, const uint64_t* n,
+                       uint8_t* const* d_out_is_new, uint32_t ntables, bool once, ht_multi_plan** out) {
   if (!out) return fail(HT_EINVAL, "out is NULL");
   *out = nullptr;
   if (ntables && (!t || !d_keys || !n || !d_out_is_new)) return fail(HT_EINVAL, "NULL argument array");
@@ -848,6 +861,7 @@ int ht_multi_plan_create(ht_table* const* t, const uint64_t* const* d_keys, cons
   std::vector<MultiCuckooSpec> cuckoo;
   std::vector<ht_multi_plan::VecJob> vec;
   std::vector<ht_table*> seen;
+  std::vector<uint8_t> tiled(ntables, 0);
   for (uint32_t i = 0; i < ntables; ++i) {
     int rc = check_table(t[i]);
     if (rc) return rc;
@@ -887,10 +901,14 @@ int ht_multi_plan_create(ht_table* const* t, const uint64_t* const* d_keys, cons
     sp.keys = d_keys[i];
     sp.out = d_out_is_new[i];
     sp.n = n[i];
+    sp.tiled = !once && plan_tile_rule(t[i], n[i]);
+    tiled[i] = sp.tiled;
     specs.push_back(sp);
   }
   ht_multi_plan* p = new ht_multi_plan();
   p->tables = seen;
+  p->keys.assign(n, n + ntables);
+  p->tiled = tiled;
   p->vec = vec;
   int dev = 0;
   (void)hipGetDevice(&dev);
@@ -905,9 +923,24 @@ int ht_multi_plan_create(ht_table* const* t, const uint64_t* const* d_keys, cons
   return HT_OK;
 }
 
+int ht_multi_plan_create(ht_table* const* t, const uint64_t* const* d_keys, const uint64_t* n,
+                         uint8_t* const* d_out_is_new, uint32_t ntables, ht_multi_plan** out) {
+  return plan_create(t, d_keys, n, d_out_is_new, ntables, false, out);
+}
+
 int ht_multi_plan_launch(ht_multi_plan* p, hipStream_t s) {
   if (!p) return fail(HT_EINVAL, "plan is NULL");
-  if (p->dev.nitems) {
+  // the tiled passes while the tables they would fill hold less than the launch brings
+  bool tiles = p->dev.njobs != 0;
+  for (size_t i = 0; i < p->tables.size(); ++i) {
+    ht_table* t = p->tables[i];
+    if (p->tiled[i] && t->puts >= p->keys[i]) tiles = false;
+    if (t->cfg.key_words <= 1) t->puts += p->keys[i];
+  }
+  if (tiles) {
+    KernelTimer kt("multi_tiles", s);
+    HT_HIP(multi_plan_launch_tiled(p->dev, s));
+  } else if (p->dev.nitems) {
     KernelTimer kt("multi_fill", s);
     HT_HIP(multi_plan_launch(p->dev, s));
   }
@@ -944,7 +977,7 @@ int ht_find_or_put_multi(ht_table* const* t, const uint64_t* const* d_keys, cons
                          uint8_t* const* d_out_is_new, uint32_t ntables, hipStream_t s) {
   if (ntables == 0) return HT_OK;
   ht_multi_plan* p = nullptr;
-  int rc = ht_multi_plan_create(t, d_keys, n, d_out_is_new, ntables, &p);
+  int rc = plan_create(t, d_keys, n, d_out_is_new, ntables, true, &p);
   if (rc) return rc;
   rc = ht_multi_plan_launch(p, s);
   if (!rc) rc = ht_multi_plan_status(p, s);

@@ -27,6 +27,10 @@ struct TileJob {
   uint32_t run_lanes;       // lanes that serve one run (a power of two)
 };
 
+// An item of a many-table launch: a chunk or a tile of a job (tiles == 0: the
+// whole table by one block).
+__host__ __device__ inline uint64_t tile_item(uint32_t job, uint32_t part) { return ((uint64_t)job << 32) | part; }
+
 // Shape of a tiled find-or-put of n keys into a table of nslots slots, and
 // the workspace it needs.
 struct TileShape {
@@ -34,7 +38,9 @@ struct TileShape {
   size_t bytes;
 };
 
-TileShape tile_shape(uint64_t nslots, uint64_t n);
+// `min_tiles`: tiles are made smaller (to 2048 slots) while there are fewer;
+// `chunk`: 4096 or 8192 keys, 0 to choose by n.
+TileShape tile_shape(uint64_t nslots, uint64_t n, uint32_t min_tiles = 512, uint32_t chunk = 0);
 // The job of a call, its workspace `ws` holding shape.bytes.
 TileJob tile_job(const DevTable& t, const uint64_t* keys, uint64_t n, uint8_t* out, const TileShape& s, void* ws);
 
@@ -44,5 +50,11 @@ hipError_t tile_insert(const TileJob& j, const TileShape& s, hipStream_t st);
 hipError_t tile_finish(const TileJob& j, const TileShape& s, hipStream_t st);
 // One block, the whole table in LDS (at most kTileSlots slots).
 hipError_t tile_whole(const DevTable& t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t st);
+
+// The same for many tables (every job with chunks of 4096 keys): `chunks` are
+// the (job, chunk) items of the partition and finish passes, `tiles` the (job,
+// tile) items of the tile pass, in device memory.
+hipError_t tile_multi(const TileJob* jobs, const uint64_t* chunks, uint32_t nchunks, const uint64_t* tiles,
+                      uint32_t ntiles, hipStream_t st);
 
 }  // namespace ht

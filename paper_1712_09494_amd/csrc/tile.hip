@@ -30,6 +30,43 @@ __global__ __launch_bounds__(kTileBlock) void tile_whole_kernel(DevTable t, cons
   tile_whole_table(t, keys, n, out, l);
 }
 
+__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
+  return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32)) << 32) |
+         __builtin_amdgcn_readfirstlane((uint32_t)x);
+}
+
+__global__ __launch_bounds__(kTileBlock) void tile_multi_partition_kernel(const TileJob* __restrict__ jobs,
+                                                                          const uint64_t* __restrict__ items) {
+  __shared__ TilePartLds<4096> l;
+  const uint64_t it = uniform64(items[blockIdx.x]);
+  tile_partition_chunk<4096>(jobs[it >> 32], (uint32_t)it, l);
+}
+
+__global__ __launch_bounds__(kTileBlock) void tile_multi_insert_kernel(const TileJob* __restrict__ jobs,
+                                                                       const uint64_t* __restrict__ items) {
+  __shared__ TileLds l;
+  const uint64_t it = uniform64(items[blockIdx.x]);
+  const TileJob& j = jobs[it >> 32];
+  if (j.tiles) tile_insert_keys<4096>(j, (uint32_t)it, l);
+  else tile_whole_table(j.t, j.keys, j.n, j.out, l);
+}
+
+__global__ __launch_bounds__(kTileBlock) void tile_multi_finish_kernel(const TileJob* __restrict__ jobs,
+                                                                       const uint64_t* __restrict__ items) {
+  __shared__ TileFinishLds<4096> l;
+  const uint64_t it = uniform64(items[blockIdx.x]);
+  tile_finish_chunk<4096>(jobs[it >> 32], (uint32_t)it, l);
+}
+
+hipError_t tile_multi(const TileJob* jobs, const uint64_t* chunks, uint32_t nchunks, const uint64_t* tiles,
+                      uint32_t ntiles, hipStream_t st) {
+  const dim3 b(kTileBlock);
+  if (nchunks) hipLaunchKernelGGL(tile_multi_partition_kernel, dim3(nchunks), b, 0, st, jobs, chunks);
+  if (ntiles) hipLaunchKernelGGL(tile_multi_insert_kernel, dim3(ntiles), b, 0, st, jobs, tiles);
+  if (nchunks) hipLaunchKernelGGL(tile_multi_finish_kernel, dim3(nchunks), b, 0, st, jobs, chunks);
+  return hipGetLastError();
+}
+
 static size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 
 // Tiles: 8192 slots, down to 2048 while that leaves fewer than 512 of them (a
@@ -37,12 +74,12 @@ static size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 // on, where runs get short (2^22 keys into 2^23 slots, the three passes: 120
 // us with 4096, 104 with 8192; 2^20 keys: 37 and 40, half the blocks).  Lanes
 // per run: about a run's length.
-TileShape tile_shape(uint64_t nslots, uint64_t n) {
+TileShape tile_shape(uint64_t nslots, uint64_t n, uint32_t min_tiles, uint32_t chunk) {
   TileShape s{};
   s.shift = 13;
-  while (s.shift > 11 && (nslots >> s.shift) < 512) --s.shift;
+  while (s.shift > 11 && (nslots >> s.shift) < min_tiles) --s.shift;
   s.tiles = (uint32_t)((nslots + (1ull << s.shift) - 1) >> s.shift);
-  s.chunk = n >= (1ull << 21) ? 8192 : 4096;
+  s.chunk = chunk ? chunk : n >= (1ull << 21) ? 8192 : 4096;
   s.chunks = (uint32_t)((n + s.chunk - 1) / s.chunk);
   const uint64_t len = s.chunk / (s.tiles ? s.tiles : 1);
   s.run_lanes = 1;

@@ -135,3 +135,81 @@ def test_captured_calls_stay_direct():
             t.clear()
             t.find_or_put(big)                                 # a larger workspace
             assert t.size() == big.numel()
+
+
+# capacity, keys, distinct, kind and options of a many-table plan: small tables (one block each), tables of several
+# tiles, and ones the passes do not take (too empty, too full, flags, other kinds, no keys)
+PLAN = [
+    (700, 600, 500, "bucketed", dict(bucket_slots=8)), (8192, 7000, 7000, "bucketed", dict(bucket_slots=16)),
+    (8200, 64, 64, "bucketed", dict(bucket_slots=8)), (8200, 5000, 4000, "bucketed", dict(bucket_slots=8)),
+    (50001, 30001, 30000, "bucketed", dict(bucket_slots=32)), (300000, 180000, 150000, "bucketed", dict(bucket_slots=8)),
+    (40000, 4097, 4097, "bucketed", dict(bucket_slots=64)), (1 << 20, 900, 900, "bucketed", dict(bucket_slots=8)),
+    (1000, 3000, 400, "bucketed", dict(bucket_slots=16)), (20000, 9000, 8000, "cuckoo", {}),
+    (30000, 15000, 15000, "bucketed", dict(bucket_slots=8, flags=b.HT_FLAG_BUCKETED_ONE_LANE)),
+    (5000, 0, 0, "bucketed", dict(bucket_slots=8)), (6000, 3000, 2500, "bucketed", dict(bucket_slots=8, key_words=2)),
+]
+
+
+def plan_tables():
+    tables, keys = [], []
+    for i, (cap, n, d, kind, kw) in enumerate(PLAN):
+        w = kw.get("key_words", 1)
+        tables.append(b.Table(kind, capacity=cap, nhash=3, **kw))
+        if w > 1:
+            k = inputs.vector_sequence(n, d, w, seed=60 + i)
+        else:
+            k = inputs.random_sequence(n, d, seed=60 + i) if n else np.zeros(0, dtype=np.uint64)
+            if n > 1000:
+                k[11::977] = np.uint64(b.EMPTY)
+        keys.append(np.ascontiguousarray(k))
+    return tables, keys
+
+
+def check_plan(tables, keys, outs, new):
+    for t, k, o, (cap, n, d, kind, kw) in zip(tables, keys, outs, PLAN):
+        f = o.cpu().numpy()[:n]
+        if kw.get("key_words", 1) > 1:
+            assert int(f.sum()) == (d if new else 0) and t.size() == d
+            continue
+        exp = Oracle() if new else Oracle(k)
+        check_flags_r2(k, f, exp.find_or_put(k), f"cap={cap} n={n}")
+        check_dump_r3(b.u64(t.dump()), exp.dump(), t.size(), f"cap={cap} n={n}")
+
+
+def test_plan_with_tiled_tables():
+    tables, keys = plan_tables()
+    outs = [torch.full((max(n, 1),), 9, dtype=torch.uint8, device="cuda") for _, n, _, _, _ in PLAN]
+    plan = b.MultiPlan(tables, [dev(k) for k in keys], outs)
+
+    def launch(expect):
+        b.ht_timing_enable(True)
+        plan.launch()
+        names = set(b.ht_timing_report())
+        b.ht_timing_enable(False)
+        assert (expect in names) and not ({"multi_tiles", "multi_fill"} - {expect}) & names, names
+
+    launch("multi_tiles")                  # empty tables
+    check_plan(tables, keys, outs, True)
+    launch("multi_fill")                   # as much in them as the launch brings
+    check_plan(tables, keys, outs, False)
+    # cleared and launched in a graph, with eager work between the replays
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        for t in tables:
+            t.clear()
+        plan.launch(stream=s)
+    for _ in range(3):
+        for o in outs:
+            o.fill_(9)
+        g.replay()
+        torch.cuda.synchronize()
+        check_plan(tables, keys, outs, True)
+        assert tables[5].query(dev(keys[5])).all()
+        plan.launch()
+        torch.cuda.synchronize()
+        check_plan(tables, keys, outs, False)
+    plan.close()
+    for t in tables:
+        t.close()
