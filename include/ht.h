@@ -107,10 +107,11 @@ enum {
   HT_FLAG_CUCKOO_SINGLE_PASS = 1u << 4,
   /* Bucketed, single-word keys: probe with one lane per key (each lane reads
    * its buckets eight slots at a time and compare-and-swaps the first empty
-   * slot) instead of a group of B/4 lanes sharing each bucket (Sec. 4.2).
+   * slot) in every call.  Without the flag a find-or-put takes the faster of
+   * this and a group of B/4 lanes sharing each bucket (Sec. 4.2); a nonzero
+   * keys_per_group or HT_FLAG_BUCKETED_ATOMIC_LOADS asks for the groups.
    * Same table, probe sequence and results; a wave serves 64 keys per turn
-   * instead of 256/B.  Faster where hits dominate (BFS keys, heavy
-   * duplication).  The many-table launch always probes this way. */
+   * instead of 256/B.  The many-table launch always probes this way. */
   HT_FLAG_BUCKETED_ONE_LANE = 1u << 5,
   /* Measurement: record each Cuckoo eviction chain's number of exchanges in
    * a histogram read by ht_chain_histogram (one extra atomic per chain). */
@@ -139,8 +140,9 @@ typedef struct {
   uint32_t bucket_slots;   /* bucketed: B in {8, 16, 32, 64}; 0 = 16 (one 128-byte
                               line of 64-bit keys).  Ignored by cuckoo */
   uint32_t keys_per_group; /* keys each lane group (bucketed) or lane (cuckoo)
-                              keeps in flight: 1, 2 or 4; 0 = 1.  Bucketed
-                              lane-group queries use at least 2 */
+                              keeps in flight: 1, 2 or 4; 0 = 1, and bucketed
+                              find-or-puts may probe with one lane per key.
+                              Bucketed lane-group queries use at least 2 */
   uint32_t stash_slots;    /* stash size (power of two, <= 65536); 0 = 1024 */
   uint32_t max_chain;      /* cuckoo eviction bound; 0 = 8 * ceil(log2 capacity) */
   uint64_t seed;           /* seed of the hash constants */

@@ -184,10 +184,10 @@ __global__ __launch_bounds__(kBlock) void bfs_write_kernel(BfsModelDev m, const 
 // mask of new successors (bit k = successor k; two words; not written when
 // mask is NULL), per group of 64 states their number, and the number of
 // successors generated added to *generated.
-__global__ __launch_bounds__(kBlock) void bfs_fused_kernel(BfsModelDev m, DevTable t, const uint64_t* __restrict__ f,
-                                                           uint64_t nf, unsigned long long* __restrict__ gcnt,
-                                                           uint64_t* __restrict__ mask,
-                                                           unsigned long long* __restrict__ generated) {
+__global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
+void bfs_fused_kernel(BfsModelDev m, DevTable t, const uint64_t* __restrict__ f, uint64_t nf,
+                      unsigned long long* __restrict__ gcnt, uint64_t* __restrict__ mask,
+                      unsigned long long* __restrict__ generated) {
   const uint64_t first = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   const int lane = lane_id();
@@ -269,13 +269,11 @@ struct SuccIter {
 // group's region of the scratch list, which starts at the group's first
 // successor offset, counted from group g0's (a group never lists more keys
 // than it has successors).
-__global__ __launch_bounds__(kBlock) void bfs_cuckoo_probe_kernel(BfsModelDev m, DevTable t,
-                                                                  const uint64_t* __restrict__ f, uint64_t nf,
-                                                                  uint64_t g0, uint64_t g1,
-                                                                  const unsigned long long* __restrict__ soff,
-                                                                  CuckooScratch s, uint32_t* __restrict__ lcnt,
-                                                                  unsigned long long* __restrict__ gnew,
-                                                                  uint64_t* __restrict__ mask) {
+__global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
+void bfs_cuckoo_probe_kernel(BfsModelDev m, DevTable t, const uint64_t* __restrict__ f, uint64_t nf, uint64_t g0,
+                             uint64_t g1, const unsigned long long* __restrict__ soff, CuckooScratch s,
+                             uint32_t* __restrict__ lcnt, unsigned long long* __restrict__ gnew,
+                             uint64_t* __restrict__ mask) {
   const int lane = lane_id();
   const uint64_t wave =
       __builtin_amdgcn_readfirstlane((uint32_t)(((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave));
@@ -582,9 +580,9 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
     HT_HIP(all.mark(s));
     if (fused && !ck) {
       HT_HIP(fop.mark(s));
-      // the grid of the one-lane find-or-put kernels (7-level workload: 22.3-23.1 ms
-      // for the fused levels at 8 blocks per compute unit, 19.3 at 6)
-      const uint32_t gf = (uint32_t)std::min<uint64_t>((nf + kBlock - 1) / kBlock, atomic_grid_blocks(t));
+      // 5 blocks per compute unit (fused levels of the 7-level workload: 17.3 ms
+      // at 5, 17.9 at 6, 18.3 at 7, 19.4 at 8)
+      const uint32_t gf = (uint32_t)std::min<uint64_t>((nf + kBlock - 1) / kBlock, t->cus * 5);
       hipLaunchKernelGGL(bfs_fused_kernel, dim3(gf), dim3(kBlock), 0, s, m, dt, fr, nf, gcnt, mk, ns);
       HT_HIP(hipGetLastError());
       HT_HIP(fop.mark(s));

@@ -16,6 +16,12 @@ constexpr uint64_t kEmpty = ~0ull;
 constexpr uint32_t HT_KIND_BUCKETED = 1;
 constexpr uint32_t HT_KIND_CUCKOO = 2;
 
+// A kernel that is to run eight waves per SIMD (64 vector registers or fewer)
+// has to keep to 80 scalar registers too: with 83 one wave slot is lost, and a
+// grid of 8 blocks per compute unit runs as seven and one (find-or-put of 2^20
+// keys 54 -> 65 us).
+#define HT_EIGHT_WAVES __attribute__((amdgpu_num_sgpr(80)))
+
 constexpr int kWave = 64;
 constexpr int kBlock = 256;          // 4 waves per workgroup
 constexpr int kSpread = 16;          // hot counters are spread over 16 lines

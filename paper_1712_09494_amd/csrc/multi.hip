@@ -50,8 +50,8 @@ __host__ __device__ inline uint64_t make_item(uint32_t table, uint64_t region) {
   return ((uint64_t)table << 40) | region;
 }
 
-__global__ __launch_bounds__(kBlock) void multi_fill_kernel(const MultiTable* __restrict__ tabs,
-                                                            const uint64_t* __restrict__ items, uint32_t nitems) {
+__global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
+void multi_fill_kernel(const MultiTable* __restrict__ tabs, const uint64_t* __restrict__ items, uint32_t nitems) {
   const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
   const uint64_t nwaves = (uint64_t)gridDim.x * (kBlock / kWave);
   for (uint64_t idx = wave; idx < nitems; idx += nwaves) {
@@ -89,9 +89,9 @@ __device__ __forceinline__ uint64_t uniform_item(const uint64_t* items, uint64_t
          __builtin_amdgcn_readfirstlane((uint32_t)raw);
 }
 
-__global__ __launch_bounds__(kBlock) void multi_cuckoo_probe_kernel(const MultiCuckoo* __restrict__ tabs,
-                                                                    const uint64_t* __restrict__ items,
-                                                                    uint32_t nitems) {
+__global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
+void multi_cuckoo_probe_kernel(const MultiCuckoo* __restrict__ tabs, const uint64_t* __restrict__ items,
+                               uint32_t nitems) {
   const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
   const uint64_t nwaves = (uint64_t)gridDim.x * (kBlock / kWave);
   for (uint64_t idx = wave; idx < nitems; idx += nwaves) {
@@ -160,8 +160,8 @@ struct MultiQuery {
   uint32_t pad_;
 };
 
-__global__ __launch_bounds__(kBlock) void multi_query_kernel(const MultiQuery* __restrict__ tabs, uint32_t ntabs,
-                                                             uint64_t nitems) {
+__global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
+void multi_query_kernel(const MultiQuery* __restrict__ tabs, uint32_t ntabs, uint64_t nitems) {
   const int lane = lane_id();
   const uint64_t wave =
       __builtin_amdgcn_readfirstlane((uint32_t)(((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave));

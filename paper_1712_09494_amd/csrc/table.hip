@@ -178,7 +178,7 @@ uint32_t max_blocks(const ht_table* t) { return t->cus * 8; }
 
 // Grid of the one-lane-per-key kernels that mix random reads with
 // compare-and-swaps (the Cuckoo probe phases, the state-vector kernels, the
-// one-lane bucketed find-or-put and fused BFS levels): 6
+// one-lane bucketed find-or-put): 6
 // blocks (24 waves) per compute unit, which keeps fewer requests queued at
 // the memory than the full 8.  Measured on the 2^20-key batches of a
 // 2^26-key fill at c = 4 (probe kernel, average per launch): 73.9 us at 8
@@ -353,6 +353,25 @@ static bool plan_tile_rule(const ht_table* t, uint64_t n) {
   const uint64_t bytes = t->nslots * 8;
   return tile_table(t) && n >= 64 && n <= (1ull << 25) && bytes >= 9 * n && bytes <= 64 * n &&
          t->nslots <= (uint64_t)kTileMax * kTileSlots;
+}
+
+// Whether a find-or-put probes with one lane per key instead of the lane
+// groups of Sec. 4.2, when neither is asked for.  Since each lane takes its
+// first empty slot from a mask of eight, one lane per key is mostly the faster
+// (2^25 keys, 10% repeats, batches of 2^20 at load factors 0.5, 0.7 and 0.9,
+// groups and lanes: 8 slots 1.72 1.80 1.98 and 1.71 1.77 1.92 ms, 16 slots
+// 1.82 1.95 2.12 and 1.76 1.87 2.01, 64 slots 4.37 4.22 3.92 and 2.52 2.59
+// 2.86; batches of 2^16: 4.58 4.86 5.65 and 4.26 4.59 5.49, 8.17 8.09 8.10
+// and 5.32 5.94 7.58; exploration batches 19.8 and 18.8 ms).  The groups are
+// ahead where a wide bucket's reads meet too few waves to hide them (new keys
+// into 64-slot buckets, groups and lanes: 5000 keys 7.7 and 10.4 us, 20000
+// 10.1 and 11.1, 2^16 15.8 and 12.3; 16 slots: 5000 keys 6.1 and 6.5, 20000
+// 6.9 and 6.8), and in large batches of mostly new keys into 8-slot buckets
+// (batches of 2^22: 1.46 1.56 1.76 and 1.51 1.58 1.71 ms).
+static bool lane_rule(const ht_table* t, uint64_t n, bool repeats) {
+  if (t->user_cfg.keys_per_group || (t->cfg.flags & HT_FLAG_BUCKETED_ATOMIC_LOADS)) return false;
+  if (t->cfg.bucket_slots == 8) return n < (1ull << 21) || repeats;
+  return n >= 512ull * t->cfg.bucket_slots;
 }
 
 // Whether one block does the call with the whole table in LDS: a batch that
@@ -603,13 +622,6 @@ int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, 
   const DevTable d = launch_view(t);
   const bool scripted = is_scripted(t);
   const uint32_t R = t->cfg.keys_per_group;
-  if (t->cfg.kind == HT_BUCKETED && (t->cfg.flags & HT_FLAG_BUCKETED_ONE_LANE)) {
-    // W2 fill: 4.08 ms at 8 blocks per compute unit, 3.72 at 6, 3.90 at 4
-    const uint64_t blocks = std::min<uint64_t>((n + kBlock - 1) / kBlock, atomic_grid_blocks(t));
-    KernelTimer kt("bucketed_lane_fop", s);
-    HT_HIP(bucketed_lane_find_or_put(d, keys, n, out, (uint32_t)blocks, scripted, s));
-    return HT_OK;
-  }
   const bool whole = tile_whole_rule(t, n), cwhole = cuckoo_whole_rule(t, n);
   const bool tiled = !repeats && !g_quiet && tile_rule(t, n);
   t->puts += n;
@@ -621,6 +633,13 @@ int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, 
   if (tiled) {
     const TileShape sh = tile_shape(t->nslots, n);
     if (tile_workspace(t, sh.bytes, s)) return tiled_find_or_put(t, d, keys, n, out, sh, s);
+  }
+  const bool one_lane = (t->cfg.flags & HT_FLAG_BUCKETED_ONE_LANE) != 0;
+  if (t->cfg.kind == HT_BUCKETED && (one_lane || lane_rule(t, n, repeats))) {
+    const uint64_t blocks = std::min<uint64_t>((n + kBlock - 1) / kBlock, atomic_grid_blocks(t));
+    KernelTimer kt(one_lane ? "bucketed_lane_fop" : "bucketed_fop", s);
+    HT_HIP(bucketed_lane_find_or_put(d, keys, n, out, (uint32_t)blocks, scripted, s));
+    return HT_OK;
   }
   if (t->cfg.kind == HT_BUCKETED) {
     const uint64_t g = bucketed_keys_per_wave(t->cfg.bucket_slots, R, kFopSlotsPerLane);
@@ -700,7 +719,10 @@ int do_query(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStr
   // Sec. 4.2 (same answers; one lane per key is faster at every bucket width)
   if (t->cfg.kind == HT_BUCKETED &&
       ((t->cfg.flags & HT_FLAG_BUCKETED_ONE_LANE) || !(t->cfg.flags & HT_FLAG_BUCKETED_GROUP_QUERY))) {
-    const uint64_t blocks = std::min<uint64_t>((n + kBlock - 1) / kBlock, max_blocks(t));
+    // a block per 256 keys: waves that wait for a lane's second bucket make
+    // room for new ones as they end (16.8 M queries, half hits: 426 us on a
+    // persistent grid of 8 blocks per compute unit, 385 so; 2^20 the same)
+    const uint64_t blocks = std::min<uint64_t>((n + kBlock - 1) / kBlock, 1u << 22);
     KernelTimer kt("bucketed_lane_query", s);
     HT_HIP(bucketed_lane_query(d, keys, n, out, (uint32_t)blocks, scripted, s));
     return HT_OK;

@@ -19,13 +19,14 @@ __global__ __launch_bounds__(kTileBlock) void tile_insert_kernel(TileJob j) {
 }
 
 template <uint32_t C>
-__global__ __launch_bounds__(kTileBlock) void tile_finish_kernel(TileJob j) {
+__global__ __launch_bounds__(kTileBlock) HT_EIGHT_WAVES
+void tile_finish_kernel(TileJob j) {
   __shared__ TileFinishLds<C> l;
   tile_finish_chunk<C>(j, blockIdx.x, l);
 }
 
-__global__ __launch_bounds__(kTileBlock) void tile_whole_kernel(DevTable t, const uint64_t* __restrict__ keys,
-                                                                uint64_t n, uint8_t* __restrict__ out) {
+__global__ __launch_bounds__(kTileBlock) HT_EIGHT_WAVES
+void tile_whole_kernel(DevTable t, const uint64_t* __restrict__ keys, uint64_t n, uint8_t* __restrict__ out) {
   __shared__ TileLds l;
   tile_whole_table(t, keys, n, out, l);
 }
@@ -42,8 +43,8 @@ __global__ __launch_bounds__(kTileBlock) void tile_multi_partition_kernel(const 
   tile_partition_chunk<4096>(jobs[it >> 32], (uint32_t)it, l);
 }
 
-__global__ __launch_bounds__(kTileBlock) void tile_multi_insert_kernel(const TileJob* __restrict__ jobs,
-                                                                       const uint64_t* __restrict__ items) {
+__global__ __launch_bounds__(kTileBlock) HT_EIGHT_WAVES
+void tile_multi_insert_kernel(const TileJob* __restrict__ jobs, const uint64_t* __restrict__ items) {
   __shared__ TileLds l;
   const uint64_t it = uniform64(items[blockIdx.x]);
   const TileJob& j = jobs[it >> 32];
@@ -51,8 +52,8 @@ __global__ __launch_bounds__(kTileBlock) void tile_multi_insert_kernel(const Til
   else tile_whole_table(j.t, j.keys, j.n, j.out, l);
 }
 
-__global__ __launch_bounds__(kTileBlock) void tile_multi_finish_kernel(const TileJob* __restrict__ jobs,
-                                                                       const uint64_t* __restrict__ items) {
+__global__ __launch_bounds__(kTileBlock) HT_EIGHT_WAVES
+void tile_multi_finish_kernel(const TileJob* __restrict__ jobs, const uint64_t* __restrict__ items) {
   __shared__ TileFinishLds<4096> l;
   const uint64_t it = uniform64(items[blockIdx.x]);
   tile_finish_chunk<4096>(jobs[it >> 32], (uint32_t)it, l);

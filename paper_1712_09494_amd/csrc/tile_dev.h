@@ -247,29 +247,6 @@ __device__ __forceinline__ uint32_t tile_of_block(uint32_t b, uint32_t tiles) {
 
 // ---- finish -------------------------------------------------------------------
 
-// The rest of key k's probe sequence, from position 1 on, in the table.
-__device__ __forceinline__ uint32_t tile_bucketed_rest(const DevTable& t, uint64_t k) {
-  const uint32_t B = t.bucket_slots;
-  const uint32_t nseq = t.nhash + t.walk;
-  uint64_t b = hidx<false>(t, k, 0);
-  for (uint32_t j = 1; j < nseq; ++j) {
-    b = probe_bucket<false>(t, k, j, b);
-    uint64_t* bk = t.slots + b * B;
-    for (uint32_t c0 = 0; c0 < B; c0 += 8) {
-      uint64_t x[8];
-      load8(bk + c0, x);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        uint64_t v = x[q];
-        if (v == kEmpty) v = cas64(bk + c0 + q, kEmpty, k);
-        if (v == kEmpty) return 1;
-        if (v == k) return 0;
-      }
-    }
-  }
-  return stash_put(t, k);
-}
-
 template <uint32_t C>
 struct TileFinishLds {
   uint64_t mkey[C];         // keys that go on at h_2
@@ -318,7 +295,8 @@ __device__ __forceinline__ void tile_finish_chunk(const TileJob& j, uint32_t c, 
   const uint32_t nmore = l.nmore;
   uint32_t nnew = 0;
   for (uint32_t e = tid; e < nmore; e += kTileBlock) {
-    const uint32_t r = tile_bucketed_rest(j.t, l.mkey[e]);
+    const uint64_t key = l.mkey[e];
+    const uint32_t r = lane_put_from<false>(j.t, key, 0, hidx<false>(j.t, key, 0), j.t.bucket_slots);
     nnew += r == 1;
     l.flag[l.midx[e]] = (uint8_t)r;
   }
