@@ -517,7 +517,9 @@ struct Spans {
 // 28.4 and 31.1 ms, 8192 26.4 and 28.2, 16384 25.4 and 27.7, 32768 24.9 and
 // 28.9 (its buffers no longer stay with the table), whole levels 24.3 and
 // 28.1 before memory has to be cleared, 395 after.  Fused Cuckoo: four groups
-// for each wave of the probe grid (at most 1.7 GB of lists).
+// for each wave of the probe grid (at most 2.3 GB of lists).  Its fused levels
+// of a 6-level exploration: 5.25 ms a call at three turns of 8 blocks per
+// compute unit, 5.04 at four; four turns of 6 blocks 5.20.
 constexpr uint64_t kSplitGroups = 16384;
 constexpr uint64_t kCuckooTurns = 4;
 
@@ -601,7 +603,7 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
       nb = got[1];
     } else {
       // where each slice's successors begin: slice q is groups q * per ...
-      const uint64_t per = ck ? (uint64_t)atomic_grid_blocks(t) * (kBlock / kWave) * kCuckooTurns : kSplitGroups;
+      const uint64_t per = ck ? (uint64_t)grid * (kBlock / kWave) * kCuckooTurns : kSplitGroups;
       const uint64_t nslices = (ng + per - 1) / per;
       bounds.resize(nslices + 1);
       if (nslices > 1)
@@ -628,11 +630,10 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
         const uint64_t n = bounds[q + 1] - bounds[q];
         const uint64_t a = q * per, z = std::min(ng, a + per);
         if (ck) {
-          // probe and place, evict, scrub.  The probe grid of the single-table
-          // Cuckoo find-or-put (fused levels of the 7-level workload: 36.3-38.6
-          // ms at 8 blocks per compute unit, 32.9 at 6)
+          // probe and place, evict, scrub, at 8 blocks per compute unit (fused
+          // levels of the 7-level workload: 29.6 ms at 6, 29.1 at 8)
           const CuckooScratch sc = scratch_view(t, std::max<uint64_t>(n, 1));
-          const uint32_t g2 = (uint32_t)std::min<uint64_t>((z - a + 3) / 4, atomic_grid_blocks(t));
+          const uint32_t g2 = (uint32_t)std::min<uint64_t>((z - a + 3) / 4, grid);
           HT_HIP(fop.mark(s));
           hipLaunchKernelGGL(bfs_cuckoo_probe_kernel, dim3(g2), dim3(kBlock), 0, s, m, dt, fr, nf, a, z, goff, sc, lc,
                              gn, mk);
