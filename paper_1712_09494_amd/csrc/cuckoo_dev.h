@@ -320,6 +320,39 @@ __global__ __launch_bounds__(kBlock) void cuckoo_probe_kernel(DevTable t, const 
   if (s.dirty) cuckoo_scrub_deferred(s, wave, nwaves, regions, cnt0, p0);
 }
 
+// Where a key with slot hash k that was exchanged out of `slot` goes on: the
+// hash function that placed it there is the last j with h_j == slot (a); it
+// continues with h_{a+1}, which maps elsewhere by the choice of a, or, after
+// h_c (or when none maps here), with the first h_j that maps elsewhere.
+// False when every h_j maps here.  One pass over j, keeping no per-j values,
+// so the kernels stay within 64 vector registers.
+template <bool SCRIPTED>
+__device__ __forceinline__ bool cuckoo_next(const DevTable& t, uint32_t c, uint64_t k, uint64_t& slot) {
+  int a = -1;
+  bool after = false, have_first = false;
+  uint64_t hnext = 0, hfirst = 0;
+  for (uint32_t j = 0; j < c; ++j) {
+    const uint64_t hj = hidx<SCRIPTED>(t, k, j);
+    if (hj == slot) {
+      a = (int)j;
+      after = true;
+    } else {
+      if (after) {
+        hnext = hj;
+        after = false;
+      }
+      if (!have_first) {
+        hfirst = hj;
+        have_first = true;
+      }
+    }
+  }
+  if (a >= 0 && a + 1 < (int)c) slot = hnext;
+  else if (have_first) slot = hfirst;
+  else return false;
+  return true;
+}
+
 // Eviction chain of Sec. 4.1 for key x starting at slot index `slot` (which
 // is h_j0(x)).  Returns true when the chain ended on an empty slot; on false
 // `x` holds the key left without a slot.  `steps` counts the exchanges.
@@ -358,37 +391,7 @@ __device__ __forceinline__ bool cuckoo_chain(const DevTable& t, uint64_t* slots,
         }
       }
     }
-    // The hash function that placed x here is the last j with h_j(x) == slot
-    // (a); x continues with h_{a+1}, which maps elsewhere by the choice of a,
-    // or, after h_c (or when none maps here), with the first h_j that maps
-    // elsewhere.  One pass over j, keeping no per-j values, so the kernel
-    // stays within 64 vector registers.
-    int a = -1;
-    bool after = false, have_first = false;
-    uint64_t hnext = 0, hfirst = 0;
-    for (uint32_t j = 0; j < c; ++j) {
-      const uint64_t hj = hidx<SCRIPTED>(t, x, j);
-      if (hj == slot) {
-        a = (int)j;
-        after = true;
-      } else {
-        if (after) {
-          hnext = hj;
-          after = false;
-        }
-        if (!have_first) {
-          hfirst = hj;
-          have_first = true;
-        }
-      }
-    }
-    if (a >= 0 && a + 1 < (int)c) {
-      slot = hnext;
-    } else if (have_first) {
-      slot = hfirst;
-    } else {
-      return false;   // no other slot for x
-    }
+    if (!cuckoo_next<SCRIPTED>(t, c, x, slot)) return false;   // no other slot for x
   }
 }
 

@@ -177,14 +177,12 @@ namespace ht_rt {
 uint32_t max_blocks(const ht_table* t) { return t->cus * 8; }
 
 // Grid of the one-lane-per-key kernels that mix random reads with
-// compare-and-swaps (the Cuckoo probe phases, the state-vector kernels, the
-// one-lane bucketed find-or-put): 6
-// blocks (24 waves) per compute unit, which keeps fewer requests queued at
-// the memory than the full 8.  Measured on the 2^20-key batches of a
+// compare-and-swaps (the single-table Cuckoo probe and its deferred scrub, the
+// bucketed state-vector kernels, the one-lane bucketed find-or-put): 6 blocks
+// (24 waves) per compute unit, which keeps fewer requests queued at the memory
+// than the full 8.  Measured on the 2^20-key batches of a
 // 2^26-key fill at c = 4 (probe kernel, average per launch): 73.9 us at 8
-// blocks per unit, 67.7 at 7, 66.6 at 6, 70.2 at 5, 67.5 at 4; 2^24 state
-// vectors in batches of 2^20: 5-7% faster at 6 than at 8 for both designs
-// and W = 2, 4.  The bucketed lane-group kernel is fastest at 8 (two slots
+// blocks per unit, 67.7 at 7, 66.6 at 6, 70.2 at 5, 67.5 at 4.  The bucketed lane-group kernel is fastest at 8 (two slots
 // per lane: fill 3.88 ms at 8, 4.05 at 7, 4.33 at 6; four slots per lane at
 // B = 64: 8.75 at 8, 10.3 at 6), and so is the many-table bucketed fill (256
 // tables: 5.73 ms at 8, 5.92 at 6).
@@ -550,21 +548,17 @@ CuckooScratch scratch_view(const ht_table* t, uint64_t n) {
   return sc;
 }
 
-// Launch shape of the one-lane-per-key kernels: blocks and keys per wave.
-static void lane_grid(const ht_table* t, uint64_t n, uint32_t keys_per_lane, uint64_t& blocks, uint64_t& per_wave) {
-  const uint64_t waves_needed = (n + (uint64_t)kWave * keys_per_lane - 1) / ((uint64_t)kWave * keys_per_lane);
-  blocks = std::min<uint64_t>((waves_needed + 3) / 4, atomic_grid_blocks(t));
-  const uint64_t nwaves = blocks * 4;
-  per_wave = (n + nwaves - 1) / nwaves;
-}
-
 static int vec_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t s) {
   int rc = reserve_scratch(t, n);
   if (rc != HT_OK) return rc;
   const DevTable d = launch_view(t);
-  uint64_t blocks = 0;
   CuckooScratch sc = scratch_view(t, n);
-  lane_grid(t, n, 1, blocks, sc.per_wave);
+  // Cuckoo at 8 blocks per compute unit, bucketed at 6 (four batches of 2^20
+  // vectors of two words, with queries: Cuckoo 655 us at 6 and 625 at 8, 8-slot
+  // buckets 405 and 417)
+  const uint32_t grid = t->cfg.kind == HT_CUCKOO ? max_blocks(t) : atomic_grid_blocks(t);
+  const uint64_t blocks = std::min<uint64_t>((n + kBlock - 1) / kBlock, grid);
+  sc.per_wave = (n + blocks * (kBlock / kWave) - 1) / (blocks * (kBlock / kWave));
   const uint32_t W = t->cfg.key_words;
   // one walk looks up and claims, then the commit
   {

@@ -98,6 +98,23 @@ __device__ __forceinline__ uint64_t vec_bucket(const DevTable& t, uint64_t hb, u
   return prev + 1 == t.nrange ? 0 : prev + 1;
 }
 
+// Masks over eight slots: handles (committed or placeholders) with hash bits
+// hb, and empty slots.  Taken without a branch, so that the lanes of a wave
+// meet at their compare-and-swaps instead of waiting for one another slot
+// after slot (2^20 vectors of four words a call into 8-slot buckets: 83 -> 74
+// us, queries of 2^20 64 -> 46; 64-slot buckets 148 -> 121 and 122 -> 95).
+__device__ __forceinline__ uint32_t vec_eight(const uint64_t (&x)[8], uint64_t hb, uint32_t& empty) {
+  uint32_t same = 0;
+  empty = 0;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const bool e = x[q] == kEmpty;
+    empty |= (e ? 1u : 0u) << q;
+    same |= (!e && handle_hb(x[q]) == hb ? 1u : 0u) << q;
+  }
+  return same;
+}
+
 template <int W>
 __device__ bool vec_lookup_bucketed(const DevTable& t, uint64_t hb, const uint64_t (&v)[W]) {
   const uint32_t B = t.bucket_slots;
@@ -109,11 +126,10 @@ __device__ bool vec_lookup_bucketed(const DevTable& t, uint64_t hb, const uint64
     for (uint32_t c0 = 0; c0 < B; c0 += 8) {
       uint64_t x[8];
       load8(bk + c0, x);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        if (x[k] == kEmpty) return false;       // prefix: the rest of the sequence is unused
-        if (vec_holds<W>(t, x[k], hb, v)) return true;
-      }
+      uint32_t em;
+      for (uint32_t m = vec_eight(x, hb, em); m; m &= m - 1)
+        if (vec_holds<W>(t, bk[c0 + __builtin_ctz(m)], hb, v)) return true;
+      if (em) return false;                     // prefix: the rest of the sequence is unused
     }
   }
   return false;
@@ -195,32 +211,16 @@ __device__ inline void vec_stash_put(const DevTable& t, uint64_t hd) {
   add_agent(&t.ctr->lost, 1u);
 }
 
-__device__ inline void vec_place_cuckoo(const DevTable& t, uint64_t hd, unsigned long long& nevict) {
-  const uint32_t c = t.nhash;
-  for (uint32_t j = 0; j < c; ++j) {
-    uint64_t* p = &t.slots[hidx<false>(t, handle_hb(hd), j)];
-    if (*p == kEmpty && cas64(p, kEmpty, hd) == kEmpty) return;
-  }
-  // every candidate taken: the exchange chain of Sec. 4.1 from h_1
-  uint64_t x = hd;
+// The exchange chain of Sec. 4.1 from h_1 with handle x, whose vector is absent
+// and has every candidate taken.
+__device__ __forceinline__ void vec_chain(const DevTable& t, uint64_t x, unsigned long long& nevict) {
   uint64_t slot = hidx<false>(t, handle_hb(x), 0);
   for (uint32_t step = 0;; ++step) {
     const uint64_t old = exch64(&t.slots[slot], x);
     if (old == kEmpty) return;
     x = old;
     ++nevict;
-    if (step + 1 >= t.max_chain) break;
-    // next hash after the last one that maps x here, skipping ones that also do
-    uint64_t h[kMaxHash];
-    int a = -1;
-    for (uint32_t j = 0; j < c; ++j) {
-      h[j] = hidx<false>(t, handle_hb(x), j);
-      if (h[j] == slot) a = (int)j;
-    }
-    uint32_t nj = (uint32_t)(a + 1) % c;
-    for (uint32_t tries = 0; h[nj] == slot && tries < c; ++tries) nj = (nj + 1) % c;
-    if (h[nj] == slot) break;
-    slot = h[nj];
+    if (step + 1 >= t.max_chain || !cuckoo_next<false>(t, t.nhash, handle_hb(x), slot)) break;
   }
   vec_stash_put(t, x);
 }
@@ -256,48 +256,65 @@ constexpr uint64_t kLeftover = ~1ull;
 // each winner reports 1, takes an arena entry, writes its words and runs the
 // exchange chain of Sec. 4.1 from h_1 with its handle.  Every list entry's
 // meta word becomes its scratch-set slot (or ~0) for the scrub kernel.
+// The time is that of the chains, one dependent exchange after another, so a
+// wave first gathers its leftovers from among the claims of its list and runs
+// up to 64 of them at once (calls of 2^20 vectors up to load 0.7, two and four
+// words: 51.6 and 55.4 us a call in list order, 44.0 and 43.6 so).
 template <int W>
-__global__ __launch_bounds__(kBlock) void vec_evict_kernel(DevTable t, const uint64_t* __restrict__ keys,
-                                                            uint64_t n, uint8_t* __restrict__ out,
-                                                            CuckooScratch s) {
+__global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
+void vec_evict_kernel(DevTable t, const uint64_t* __restrict__ keys, uint64_t n, uint8_t* __restrict__ out,
+                      CuckooScratch s) {
   const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
   const int lane = lane_id();
   const uint64_t begin = wave * s.per_wave;
   const uint32_t cnt = begin < n ? s.wcnt[wave] : 0u;
   unsigned long long nnew = 0, nevict = 0;
-  for (uint32_t e0 = 0; e0 < cnt; e0 += kWave) {
-    const uint32_t e = e0 + (uint32_t)lane;
+  __shared__ uint32_t gathered[kBlock / kWave][2 * kWave];
+  uint32_t* list = gathered[threadIdx.x / kWave];
+  uint32_t e0 = 0, have = 0;
+  for (;;) {
+    while (have < (uint32_t)kWave && e0 < cnt) {
+      const uint32_t e = e0 + (uint32_t)lane;
+      const bool left = e < cnt && s.wkey[begin + e] == kLeftover;
+      if (e < cnt && !left) s.wmeta[begin + e] = ~0ull;
+      const uint64_t mm = ballot(left);
+      if (left) list[have + lanes_below(mm)] = e;
+      have += (uint32_t)__popcll(mm);
+      e0 += kWave;
+    }
+    if (!have) break;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wave's own list
+    const uint32_t take = have < (uint32_t)kWave ? have : (uint32_t)kWave;
+    have -= take;
     bool winner = false;
     uint64_t hb = 0;
     uint64_t v[W];
 #pragma unroll
     for (int j = 0; j < W; ++j) v[j] = 0;
-    if (e < cnt) {
-      uint64_t p = ~0ull;
-      if (s.wkey[begin + e] == kLeftover) {
-        const uint64_t m = s.wmeta[begin + e];
-        const uint64_t i = m & kBatchMask;
-        hb = m >> 33;
-        load_vec<W>(keys + i * W, v);
-        p = mix64(hb ^ s.dset_seed) & s.dset_mask;
-        for (;;) {
-          const uint64_t old = cas64(&s.dset[p], kEmpty, i);
-          if (old == kEmpty) {
-            winner = true;
-            break;
-          }
-          if (old < n) {                   // the set holds indices of this batch only
-            uint64_t u[W];
-            load_vec<W>(keys + old * W, u);
-            if (vec_eq<W>(u, v)) break;    // an equal vector of the batch won
-          }
-          p = (p + 1) & s.dset_mask;
+    if ((uint32_t)lane < take) {
+      const uint32_t e = list[have + lane];
+      const uint64_t m = s.wmeta[begin + e];
+      const uint64_t i = m & kBatchMask;
+      hb = m >> 33;
+      load_vec<W>(keys + i * W, v);
+      uint64_t p = mix64(hb ^ s.dset_seed) & s.dset_mask;
+      for (;;) {
+        const uint64_t old = cas64(&s.dset[p], kEmpty, i);
+        if (old == kEmpty) {
+          winner = true;
+          break;
         }
-        if (out) out[i] = winner ? 1 : 0;
-        if (!winner) p = ~0ull;
+        if (old < n) {                   // the set holds indices of this batch only
+          uint64_t u[W];
+          load_vec<W>(keys + old * W, u);
+          if (vec_eq<W>(u, v)) break;    // an equal vector of the batch won
+        }
+        p = (p + 1) & s.dset_mask;
       }
-      s.wmeta[begin + e] = p;
+      if (out) out[i] = winner ? 1 : 0;
+      s.wmeta[begin + e] = winner ? p : ~0ull;
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (!ballot(winner)) continue;
     const uint64_t idx = arena_take(t, winner, wave);
     if (winner) {
@@ -308,7 +325,7 @@ __global__ __launch_bounds__(kBlock) void vec_evict_kernel(DevTable t, const uin
 #pragma unroll
         for (int j = 0; j < W; j += 2)
           *reinterpret_cast<ulonglong2*>(t.arena + idx * W + j) = make_ulonglong2(v[j], v[j + 1]);
-        vec_place_cuckoo(t, (hb << kArenaBits) | idx, nevict);
+        vec_chain(t, (hb << kArenaBits) | idx, nevict);
       }
     }
   }
@@ -364,9 +381,9 @@ __device__ __forceinline__ int vec_find_or_claim_seen(const DevTable& t, uint64_
 // leftovers, as kLeftover) are listed per wave region as (location, hash
 // bits << 33 | batch index) for the commit and evict kernels.
 template <int W>
-__global__ __launch_bounds__(kBlock) void vec_find_or_claim_kernel(DevTable t, const uint64_t* __restrict__ keys,
-                                                                    uint64_t n, uint8_t* __restrict__ out,
-                                                                    CuckooScratch s) {
+__global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
+void vec_find_or_claim_kernel(DevTable t, const uint64_t* __restrict__ keys, uint64_t n, uint8_t* __restrict__ out,
+                              CuckooScratch s) {
   const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
   const int lane = lane_id();
   const uint64_t begin = wave * s.per_wave;
@@ -414,10 +431,20 @@ __global__ __launch_bounds__(kBlock) void vec_find_or_claim_kernel(DevTable t, c
       for (uint32_t q = 0; q < steps && !st; ++q) {
         b = vec_bucket(t, hb, q, b);
         for (uint32_t c0 = 0; c0 < B && !st; c0 += 8) {
+          // stored handles with the same hash bits first (they lie before the
+          // first empty slot), then the empty slots from the lowest on: every
+          // lane at its own first empty slot together
+          uint64_t* bk = t.slots + b * B + c0;
           uint64_t x[8];
-          load8(t.slots + b * B + c0, x);
-          for (uint32_t k = 0; k < 8 && !st; ++k) {
-            st = vec_find_or_claim_seen<W>(t, t.slots + b * B + c0 + k, x[k], ph, hb, v, keys, n);
+          load8(bk, x);
+          uint32_t em;
+          for (uint32_t m = vec_eight(x, hb, em); m && !st; m &= m - 1) {
+            const uint32_t k = (uint32_t)__builtin_ctz(m);
+            st = vec_find_or_claim_seen<W>(t, bk + k, bk[k], ph, hb, v, keys, n);
+          }
+          for (; em && !st; em &= em - 1) {
+            const uint32_t k = (uint32_t)__builtin_ctz(em);
+            st = vec_claim_seen<W>(bk + k, kEmpty, ph, hb, v, keys, n);
             if (st == 1) loc = b * B + c0 + k;
           }
         }
@@ -503,8 +530,8 @@ __global__ __launch_bounds__(kBlock) void vec_commit_kernel(DevTable t, const ui
 }
 
 template <int W>
-__global__ __launch_bounds__(kBlock) void vec_query_kernel(DevTable t, const uint64_t* __restrict__ keys,
-                                                            uint64_t n, uint8_t* __restrict__ out) {
+__global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
+void vec_query_kernel(DevTable t, const uint64_t* __restrict__ keys, uint64_t n, uint8_t* __restrict__ out) {
   const uint32_t sc = t.ctr->stash_count;
   const uint32_t oc = t.ctr->overflow_count;
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
