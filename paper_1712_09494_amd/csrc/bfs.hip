@@ -172,6 +172,16 @@ __device__ __forceinline__ void write_tiles(const BfsModelDev& m, const uint64_t
   }
 }
 
+// Where the slices of `per` groups begin in the scan of the groups' counts
+// (ng + 1 entries), and the total: out[0 .. nslices].
+__global__ __launch_bounds__(kBlock) void bfs_bounds_kernel(const unsigned long long* __restrict__ goff, uint64_t ng,
+                                                            uint64_t per, uint64_t nslices,
+                                                            unsigned long long* __restrict__ out) {
+  const uint64_t stride = (uint64_t)gridDim.x * kBlock;
+  for (uint64_t q = (uint64_t)blockIdx.x * kBlock + threadIdx.x; q <= nslices; q += stride)
+    out[q] = goff[q < nslices ? q * per : ng];
+}
+
 // Split pass: every successor of groups g0 .. g1-1.
 __global__ __launch_bounds__(kBlock) void bfs_write_kernel(BfsModelDev m, const uint64_t* __restrict__ f, uint64_t nf,
                                                            uint64_t g0, uint64_t g1,
@@ -443,10 +453,11 @@ struct Buf {
 // are small (kKeepBytes) and given back with it.
 struct ht_explore_ws {
   int device = 0;
-  Buf frontier, next, batch, flags, gcounts, goffsets, gnews, tmp, nsel, masks, lists;
+  Buf frontier, next, batch, flags, gcounts, goffsets, gnews, tmp, nsel, masks, lists, slices;
   size_t bytes() const {
     size_t n = 0;
-    for (const Buf* b : {&frontier, &next, &batch, &flags, &gcounts, &goffsets, &gnews, &tmp, &nsel, &masks, &lists})
+    for (const Buf* b : {&frontier, &next, &batch, &flags, &gcounts, &goffsets, &gnews, &tmp, &nsel, &masks, &lists,
+                         &slices})
       n += b->bytes;
     return n;
   }
@@ -547,7 +558,8 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
   ExploreHold hold(t);
   ht_explore_ws& ws = *t->explore;
   Buf &frontier = ws.frontier, &next = ws.next, &batch = ws.batch, &flags = ws.flags, &gcounts = ws.gcounts,
-      &goffsets = ws.goffsets, &gnews = ws.gnews, &tmp = ws.tmp, &nsel = ws.nsel, &masks = ws.masks, &lists = ws.lists;
+      &goffsets = ws.goffsets, &gnews = ws.gnews, &tmp = ws.tmp, &nsel = ws.nsel, &masks = ws.masks, &lists = ws.lists,
+      &slices = ws.slices;
   const uint32_t grid = max_blocks(t);
   rc = frontier.ensure(8);
   if (!rc) rc = nsel.ensure(8);
@@ -606,11 +618,16 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
       const uint64_t per = ck ? (uint64_t)grid * (kBlock / kWave) * kCuckooTurns : kSplitGroups;
       const uint64_t nslices = (ng + per - 1) / per;
       bounds.resize(nslices + 1);
-      if (nslices > 1)
-        HT_HIP(hipMemcpy2DAsync(bounds.data(), 8, goff, per * 8, 8, nslices, hipMemcpyDeviceToHost, s));
-      HT_HIP(hipMemcpyAsync(&bounds[nslices], goff + ng, 8, hipMemcpyDeviceToHost, s));
+      rc = slices.ensure((nslices + 1) * 8);
+      if (rc) break;
+      auto* sl = static_cast<unsigned long long*>(slices.p);
+      const uint32_t gb = (uint32_t)std::min<uint64_t>(nslices / kBlock + 1, grid);
+      hipLaunchKernelGGL(bfs_bounds_kernel, dim3(gb), dim3(kBlock), 0, s, goff, ng, per, nslices, sl);
+      HT_HIP(hipGetLastError());
+      // (a strided copy to host memory had not arrived after the wait when a
+      // profiler's interception was in place)
+      HT_HIP(hipMemcpyAsync(bounds.data(), sl, (nslices + 1) * 8, hipMemcpyDeviceToHost, s));
       HT_HIP(hipStreamSynchronize(s));
-      if (nslices == 1) bounds[0] = 0;
       nb = bounds[nslices];
       uint64_t most = 1;
       for (uint64_t q = 0; q < nslices; ++q) most = std::max<uint64_t>(most, bounds[q + 1] - bounds[q]);

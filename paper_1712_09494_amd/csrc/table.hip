@@ -180,12 +180,12 @@ uint32_t max_blocks(const ht_table* t) { return t->cus * 8; }
 // compare-and-swaps (the single-table Cuckoo probe and its deferred scrub, the
 // bucketed state-vector kernels, the one-lane bucketed find-or-put): 6 blocks
 // (24 waves) per compute unit, which keeps fewer requests queued at the memory
-// than the full 8.  Measured on the 2^20-key batches of a
-// 2^26-key fill at c = 4 (probe kernel, average per launch): 73.9 us at 8
-// blocks per unit, 67.7 at 7, 66.6 at 6, 70.2 at 5, 67.5 at 4.  The bucketed lane-group kernel is fastest at 8 (two slots
-// per lane: fill 3.88 ms at 8, 4.05 at 7, 4.33 at 6; four slots per lane at
-// B = 64: 8.75 at 8, 10.3 at 6), and so is the many-table bucketed fill (256
-// tables: 5.73 ms at 8, 5.92 at 6).
+// than the full 8.  Measured on the 2^20-key batches of a 2^26-key fill at
+// c = 4 (probe kernel, average per launch): 73.9 us at 8 blocks per unit, 67.7
+// at 7, 66.6 at 6, 70.2 at 5, 67.5 at 4.  The bucketed lane-group kernel is
+// fastest at 8 (two slots per lane: fill 3.88 ms at 8, 4.05 at 7, 4.33 at 6;
+// four slots per lane at B = 64: 8.75 at 8, 10.3 at 6), and so is the
+// many-table bucketed fill (256 tables: 5.73 ms at 8, 5.92 at 6).
 uint32_t atomic_grid_blocks(const ht_table* t) { return t->cus * 6; }
 
 bool is_scripted(const ht_table* t) { return (t->cfg.flags & HT_FLAG_SCRIPTED_HASH) != 0; }
