@@ -66,14 +66,39 @@ struct BfsModelDev {
 
 __device__ __forceinline__ uint32_t local_of(uint64_t st, uint32_t p) { return (uint32_t)(st >> (4 * p)) & 15u; }
 
+// The model's transitions in LDS, a row per process and local state: the four
+// targets and their number in one 8-byte read.
+struct ModelLds {
+  uint2 row[16 * 16];
+  int8_t act[2][4][16];
+  uint8_t proc[2][4];
+};
+
+__device__ __forceinline__ void model_to_lds(const BfsModelDev& m, ModelLds& l) {
+  for (uint32_t q = threadIdx.x; q < 256; q += kBlock) {
+    const uint8_t* g = m.ltgt[q / 16][q % 16];
+    l.row[q] = make_uint2(g[0] | (uint32_t)g[1] << 8 | (uint32_t)g[2] << 16 | (uint32_t)g[3] << 24,
+                          m.lcnt[q / 16][q % 16]);
+  }
+  for (uint32_t q = threadIdx.x; q < 64; q += kBlock) {
+    l.act[0][q / 16][q % 16] = m.pe[q / 16][q % 16];
+    l.act[1][q / 16][q % 16] = m.qe[q / 16][q % 16];
+    if (q < 4) {
+      l.proc[0][q] = m.sp[q];
+      l.proc[1][q] = m.sq[q];
+    }
+  }
+  __syncthreads();
+}
+
 // Number of successors of `st`.
-__device__ __forceinline__ uint32_t successor_count(const BfsModelDev& m, uint64_t st) {
+__device__ __forceinline__ uint32_t successor_count(const BfsModelDev& m, const ModelLds& l, uint64_t st) {
   uint32_t c = 0;
 #pragma unroll
-  for (uint32_t p = 0; p < 16; ++p) c += m.lcnt[p][local_of(st, p)];
+  for (uint32_t p = 0; p < 16; ++p) c += l.row[p * 16 + local_of(st, p)].y;
 #pragma unroll
   for (uint32_t a = 0; a < 4; ++a)
-    c += (m.pe[a][local_of(st, m.sp[a])] >= 0 && m.qe[a][local_of(st, m.sq[a])] >= 0) ? 1u : 0u;
+    c += (l.act[0][a][local_of(st, m.sp[a])] >= 0 && l.act[1][a][local_of(st, m.sq[a])] >= 0) ? 1u : 0u;
   return c;
 }
 
@@ -91,25 +116,27 @@ __device__ __forceinline__ uint32_t wave_inclusive32(uint32_t v) {
 // Successors of each group of 64 frontier states.
 __global__ __launch_bounds__(kBlock) void bfs_count_kernel(BfsModelDev m, const uint64_t* __restrict__ f, uint64_t nf,
                                                            unsigned long long* __restrict__ gcnt) {
+  __shared__ ModelLds model;
+  model_to_lds(m, model);
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   for (uint64_t i0 = (uint64_t)blockIdx.x * kBlock + (threadIdx.x & ~63u); i0 < nf; i0 += stride) {
     const uint64_t i = i0 + lane_id();
-    const uint32_t incl = wave_inclusive32(i < nf ? successor_count(m, f[i]) : 0u);
+    const uint32_t incl = wave_inclusive32(i < nf ? successor_count(m, model, f[i]) : 0u);
     if (lane_id() == kWave - 1) gcnt[i0 / kWave] = incl;
   }
 }
 
 // Successors of `st` in model order; visit(succ) is called for each.
 template <class F>
-__device__ __forceinline__ void for_each_successor(const BfsModelDev& m, uint64_t st, F&& visit) {
+__device__ __forceinline__ void for_each_successor(const BfsModelDev& m, const ModelLds& l, uint64_t st, F&& visit) {
   for (uint32_t p = 0; p < 16; ++p) {
-    const uint32_t s = local_of(st, p);
+    const uint2 r = l.row[p * 16 + local_of(st, p)];
     const uint64_t cleared = st & ~(15ull << (4 * p));
-    for (uint32_t k = 0; k < m.lcnt[p][s]; ++k) visit(cleared | ((uint64_t)m.ltgt[p][s][k] << (4 * p)));
+    for (uint32_t k = 0; k < r.y; ++k) visit(cleared | ((uint64_t)((r.x >> (8 * k)) & 255u) << (4 * p)));
   }
   for (uint32_t a = 0; a < 4; ++a) {
     const uint32_t p = m.sp[a], q = m.sq[a];
-    const int tp = m.pe[a][local_of(st, p)], tq = m.qe[a][local_of(st, q)];
+    const int tp = l.act[0][a][local_of(st, p)], tq = l.act[1][a][local_of(st, q)];
     if (tp >= 0 && tq >= 0) {
       const uint64_t cleared = st & ~(15ull << (4 * p)) & ~(15ull << (4 * q));
       visit(cleared | ((uint64_t)tp << (4 * p)) | ((uint64_t)tq << (4 * q)));
@@ -117,56 +144,76 @@ __device__ __forceinline__ void for_each_successor(const BfsModelDev& m, uint64_
   }
 }
 
+// Successors of `st` in model order as for_each_successor, with the loops
+// over processes and targets unrolled (constant shifts): visit(live, succ) is
+// called 68 times.
+template <class F>
+__device__ __forceinline__ void unrolled_successors(const BfsModelDev& m, const ModelLds& l, uint64_t st, F&& visit) {
+#pragma unroll
+  for (uint32_t p = 0; p < 16; ++p) {
+    const uint2 r = l.row[p * 16 + local_of(st, p)];
+    const uint64_t cleared = st & ~(15ull << (4 * p));
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) visit(k < r.y, cleared | ((uint64_t)((r.x >> (8 * k)) & 255u) << (4 * p)));
+  }
+#pragma unroll
+  for (uint32_t a = 0; a < 4; ++a) {
+    const uint32_t p = m.sp[a], q = m.sq[a];
+    const int tp = l.act[0][a][local_of(st, p)], tq = l.act[1][a][local_of(st, q)];
+    const uint64_t cleared = st & ~(15ull << (4 * p)) & ~(15ull << (4 * q));
+    visit(tp >= 0 && tq >= 0, cleared | ((uint64_t)tp << (4 * p)) | ((uint64_t)tq << (4 * q)));
+  }
+}
+
 // Writing successors (all of them, or those a mask marks) at their scanned
 // places, staged through LDS so that the stores coalesce: a block takes a tile
-// of kBlock consecutive states (four groups), whose outputs form one
-// contiguous range; each thread places its state's successors that fall in
-// the current window of kWriteWin positions, then the block copies the
-// window out in consecutive words.  A thread per state storing its own
+// of four groups of 64 states, whose outputs form one contiguous range; its
+// waves in turn place their group's successors in the window, which the block
+// then copies out in consecutive words.  A thread per state storing its own
 // successors one after another wrote 8-byte words to 64 unrelated places per
 // instruction: 7.7 ms for the 5.7 GB batch of the 7-level workload's last
-// level, 2.6 ms staged.  The tiles cover groups g0 .. g1-1 of the frontier's
-// nf states; goff (one entry more than there are groups) is the scan of the
-// groups' counts, and out[0] receives the first output of group g0.
-constexpr uint32_t kWriteWin = 2048;
+// level.  What it costs is making the successors: with the transitions read
+// from kernel arguments in loops, and windows that cut across the waves, all
+// seven levels took 4.6 ms, with rows in LDS and a window per wave 1.45 (4.4
+// TB/s).  The tiles cover groups g0 .. g1-1 of the frontier's nf states; goff
+// (one entry more than there are groups) is the scan of the groups' counts,
+// and out[0] receives the first output of group g0.
+constexpr uint32_t kMostSuccessors = 16 * 4 + 4;
 
 template <bool MASKED>
 __device__ __forceinline__ void write_tiles(const BfsModelDev& m, const uint64_t* __restrict__ f, uint64_t nf,
                                             uint64_t g0, uint64_t g1, const unsigned long long* __restrict__ goff,
                                             const uint64_t* __restrict__ mask, uint64_t* __restrict__ out) {
   constexpr uint64_t kTileGroups = kBlock / kWave;
-  __shared__ uint64_t win[kWriteWin];
+  __shared__ uint64_t win[kWave * kMostSuccessors];
+  __shared__ ModelLds model;
+  model_to_lds(m, model);
   const uint32_t tid = threadIdx.x;
   const uint64_t zero = goff[g0];
   for (uint64_t t0 = g0 + (uint64_t)blockIdx.x * kTileGroups; t0 < g1; t0 += (uint64_t)gridDim.x * kTileGroups) {
-    const uint64_t base = goff[t0] - zero;
-    const uint64_t end = goff[t0 + kTileGroups < g1 ? t0 + kTileGroups : g1] - zero;
     const uint64_t g = t0 + tid / kWave;
     const uint64_t i = t0 * kWave + tid;
     const bool live = g < g1 && i < nf;
     const uint64_t st = live ? f[i] : 0ull;
     const uint64_t m0 = MASKED && live ? mask[2 * i] : ~0ull;
     const uint64_t m1 = MASKED && live ? mask[2 * i + 1] : ~0ull;
-    const uint32_t c = !live ? 0u : MASKED ? (uint32_t)(__popcll(m0) + __popcll(m1)) : successor_count(m, st);
-    const uint32_t incl = wave_inclusive32(c);
-    const uint64_t myend = (g < g1 ? goff[g] - zero : end) + incl;
-    const uint64_t mine = myend - c;
-    for (uint64_t w = base; w < end; w += kWriteWin) {
-      if (live && mine < w + kWriteWin && myend > w) {
-        uint64_t o = mine;
-        uint32_t k = 0;
-        for_each_successor(m, st, [&](uint64_t succ) {
-          const bool take = !MASKED || (((k < 64 ? (m0 >> k) : (m1 >> (k - 64))) & 1ull) != 0);
-          ++k;
-          if (take) {
-            if (o >= w && o < w + kWriteWin) win[o - w] = succ;
-            ++o;
-          }
+    const uint32_t c = !live ? 0u : MASKED ? (uint32_t)(__popcll(m0) + __popcll(m1)) : successor_count(m, model, st);
+    const uint32_t mine = wave_inclusive32(c) - c;
+    for (uint64_t q = t0; q < g1 && q < t0 + kTileGroups; ++q) {
+      if (q == g && c) {
+        uint32_t o = mine, k = 0;
+        unrolled_successors(m, model, st, [&](bool is, uint64_t succ) {
+          const bool take = is && (!MASKED || (((k < 64 ? (m0 >> k) : (m1 >> (k - 64))) & 1ull) != 0));
+          if (take) win[o] = succ;
+          o += take;
+          k += is;
         });
       }
       __syncthreads();
-      const uint64_t nw = end - w < kWriteWin ? end - w : kWriteWin;
-      for (uint32_t j = tid; j < nw; j += kBlock) out[w + j] = win[j];
+      const uint64_t base = goff[q];
+      const uint32_t nw = (uint32_t)(goff[q + 1] - base);
+      uint64_t* const to = out + (base - zero);
+      for (uint32_t j = tid; j < nw; j += kBlock) to[j] = win[j];
       __syncthreads();
     }
   }
@@ -198,6 +245,8 @@ __global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
 void bfs_fused_kernel(BfsModelDev m, DevTable t, const uint64_t* __restrict__ f, uint64_t nf,
                       unsigned long long* __restrict__ gcnt, uint64_t* __restrict__ mask,
                       unsigned long long* __restrict__ generated) {
+  __shared__ ModelLds model;
+  model_to_lds(m, model);
   const uint64_t first = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   const int lane = lane_id();
@@ -207,7 +256,7 @@ void bfs_fused_kernel(BfsModelDev m, DevTable t, const uint64_t* __restrict__ f,
     uint64_t m0 = 0, m1 = 0;
     uint32_t k = 0, nnew = 0;
     if (i < nf) {
-      for_each_successor(m, f[i], [&](uint64_t succ) {
+      for_each_successor(m, model, f[i], [&](uint64_t succ) {
         const uint32_t r = lane_find_or_put<false>(t, succ);
         if (r) {                   // 1 = stored, 2 = kept on the overflow list: new either way
           if (k < 64) m0 |= 1ull << k;
@@ -246,11 +295,11 @@ __global__ __launch_bounds__(kBlock) void bfs_fused_write_kernel(BfsModelDev m, 
 struct SuccIter {
   uint64_t st;
   uint32_t p = 0, kk = 0, a = 0;
-  __device__ __forceinline__ bool next(const BfsModelDev& m, uint64_t& succ) {
+  __device__ __forceinline__ bool next(const ModelLds& l, uint64_t& succ) {
     while (p < 16) {
-      const uint32_t s = local_of(st, p);
-      if (kk < m.lcnt[p][s]) {
-        succ = (st & ~(15ull << (4 * p))) | ((uint64_t)m.ltgt[p][s][kk] << (4 * p));
+      const uint2 r = l.row[p * 16 + local_of(st, p)];
+      if (kk < r.y) {
+        succ = (st & ~(15ull << (4 * p))) | ((uint64_t)((r.x >> (8 * kk)) & 255u) << (4 * p));
         ++kk;
         return true;
       }
@@ -258,8 +307,8 @@ struct SuccIter {
       kk = 0;
     }
     while (a < 4) {
-      const uint32_t pp = m.sp[a], q = m.sq[a];
-      const int tp = m.pe[a][local_of(st, pp)], tq = m.qe[a][local_of(st, q)];
+      const uint32_t pp = l.proc[0][a], q = l.proc[1][a];
+      const int tp = l.act[0][a][local_of(st, pp)], tq = l.act[1][a][local_of(st, q)];
       ++a;
       if (tp >= 0 && tq >= 0) {
         succ = (st & ~(15ull << (4 * pp)) & ~(15ull << (4 * q))) | ((uint64_t)tp << (4 * pp)) |
@@ -284,6 +333,8 @@ void bfs_cuckoo_probe_kernel(BfsModelDev m, DevTable t, const uint64_t* __restri
                              uint64_t g1, const unsigned long long* __restrict__ soff, CuckooScratch s,
                              uint32_t* __restrict__ lcnt, unsigned long long* __restrict__ gnew,
                              uint64_t* __restrict__ mask) {
+  __shared__ ModelLds model;
+  model_to_lds(m, model);
   const int lane = lane_id();
   const uint64_t wave =
       __builtin_amdgcn_readfirstlane((uint32_t)(((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave));
@@ -301,7 +352,7 @@ void bfs_cuckoo_probe_kernel(BfsModelDev m, DevTable t, const uint64_t* __restri
     uint32_t k = 0, nnew = 0, nlist = 0;
     for (;;) {
       uint64_t succ = 0;
-      const bool has = live && it.next(m, succ);
+      const bool has = live && it.next(model, succ);
       if (!ballot(has)) break;
       const uint32_t r = cuckoo_probe_key(t, t.slots, succ, has, sc, oc);
       if (has && r == 1) {
@@ -594,9 +645,11 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
     HT_HIP(all.mark(s));
     if (fused && !ck) {
       HT_HIP(fop.mark(s));
-      // 5 blocks per compute unit (fused levels of the 7-level workload: 17.3 ms
-      // at 5, 17.9 at 6, 18.3 at 7, 19.4 at 8)
-      const uint32_t gf = (uint32_t)std::min<uint64_t>((nf + kBlock - 1) / kBlock, t->cus * 5);
+      // 3 blocks per compute unit: successors repeat among the states in flight,
+      // and the fewer these are, the more copies meet in the caches (fused levels
+      // of the 7-level workload: 17.8 ms at 2, 16.5 at 3, 17.2 at 4, 17.8 at 5,
+      // 18.7 at 8; 6 levels 2.30 at 3, 2.35 at 5 and 8)
+      const uint32_t gf = (uint32_t)std::min<uint64_t>((nf + kBlock - 1) / kBlock, t->cus * 3);
       hipLaunchKernelGGL(bfs_fused_kernel, dim3(gf), dim3(kBlock), 0, s, m, dt, fr, nf, gcnt, mk, ns);
       HT_HIP(hipGetLastError());
       HT_HIP(fop.mark(s));
@@ -648,7 +701,7 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
         const uint64_t a = q * per, z = std::min(ng, a + per);
         if (ck) {
           // probe and place, evict, scrub, at 8 blocks per compute unit (fused
-          // levels of the 7-level workload: 29.6 ms at 6, 29.1 at 8)
+          // levels of the 7-level workload: 29.6 ms at 4, 28.8 at 6, 28.6 at 8)
           const CuckooScratch sc = scratch_view(t, std::max<uint64_t>(n, 1));
           const uint32_t g2 = (uint32_t)std::min<uint64_t>((z - a + 3) / 4, grid);
           HT_HIP(fop.mark(s));

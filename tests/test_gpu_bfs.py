@@ -218,3 +218,32 @@ def test_bfs_ends_and_repeats(kind, fused):
             r = t.bfs_explore(inputs.BfsModel(1), 4, fused=fused)
             assert r["batch_sizes"] == sizes and r["new_counts"] == news
             assert np.array_equal(np.sort(b.u64(t.dump())), o.dump())
+
+
+class FullModel(inputs.BfsModel):
+    """Every state has the most successors a model can give: four local
+    transitions of each process and all four synchronising actions (68)."""
+
+    def __init__(self):
+        super().__init__(7)
+        self.local = [[[(s + 1 + k * (1 + p % 3)) % 16 for k in range(4)] for s in range(16)] for p in range(16)]
+        self.syncs = [(p, 15 - p, [[(s + 5) % 16] for s in range(16)], [[(3 * s + p) % 16] for s in range(16)])
+                      for p in range(4)]
+
+    def successors(self, frontier):
+        return np.array([x for st in frontier for x in self.successors_py(int(st))], dtype=np.uint64)
+
+
+@pytest.mark.parametrize("kind", ["bucketed", "cuckoo"])
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("initial", [0, b.EMPTY])
+def test_bfs_most_successors(kind, fused, initial):
+    """Groups of 64 states with 64 * 68 successors each, from both ends of the
+    key range (the all-ones state included)."""
+    model = FullModel()
+    o, sizes, news = oracle_bfs(model, initial, 3)
+    assert sizes[0] == 68 and sizes[1] == 68 * news[0]
+    with b.Table(kind, capacity=int(o.size * 1.5), nhash=3) as t:
+        r = t.bfs_explore(model, 3, initial=initial, fused=fused)
+        assert r["batch_sizes"] == sizes and r["new_counts"] == news
+        assert np.array_equal(np.sort(b.u64(t.dump())), o.dump())
