@@ -249,9 +249,9 @@ def main():
     paper = {}
     if not args.no_paper:
         for name, kind, kw in (("cuckoo_paper_order", "cuckoo", dict(flags=b.HT_FLAG_CUCKOO_PAPER_ORDER)),
-                               ("bucketed_b16", "bucketed", dict(bucket_slots=16)),
+                               ("bucketed_b16", "bucketed", dict(bucket_slots=16, keys_per_group=1)),
                                ("bucketed_b16_paper_full", "bucketed",
-                                dict(bucket_slots=16, flags=b.HT_FLAG_BUCKETED_PAPER_FULL))):
+                                dict(bucket_slots=16, keys_per_group=1, flags=b.HT_FLAG_BUCKETED_PAPER_FULL))):
             t = b.Table(kind, capacity=cap, nhash=args.cuckoo_nhash if kind == "cuckoo" else 3,
                         max_batch=args.batch, **kw)
             per_batch_times(t)                                # warm-up fill
@@ -676,7 +676,9 @@ def measured_counter(kernel: str, field: str, workload: str = "random_scaling_2p
     """A per-dispatch figure of `kernel` from the committed counter summary
     (None when missing or stale)."""
     c = _counters(workload)
-    k = None if c is None else c.get("kernels", {}).get(kernel + "_kernel")
+    ks = {} if c is None else c.get("kernels", {})
+    # the bucketed find-or-put is one of two kernels: by one lane per key or by lane groups
+    k = ks.get(kernel + "_kernel") or (ks.get("bucketed_lane_fop_kernel") if kernel == "bucketed_fop" else None)
     return None if k is None or k.get(field) is None else float(k[field])
 
 
@@ -824,9 +826,8 @@ def run_w1(b, inputs, torch, dev, stream):
     line16 = line_probe_rate(b, torch, dev, stream, slots)
     res = {"keys": int(ins.size), "slots": slots, "cache_resident": True, "line_probe_16MiB_Gps": line16,
            "designs": {}}
-    # bucketed: lane-group find-or-put (queries one lane per key, the
-    # default), the same with the lane-group query of Sec. 4.2, and one lane
-    # per key for both
+    # bucketed: the default, the same with the lane-group query of Sec. 4.2,
+    # and one lane per key asked for in every call
     for name, kind, kw in (("bucketed", "bucketed", dict(bucket_slots=8)),
                            ("bucketed_group_query", "bucketed",
                             dict(bucket_slots=8, flags=b.HT_FLAG_BUCKETED_GROUP_QUERY)),
@@ -1221,7 +1222,7 @@ def run_bfs(b, inputs, torch, levels=7, lf=0.7):
             ("cuckoo_fused", "cuckoo", {}, b.HT_BFS_FUSED),
             # the paper's own designs: the 128-byte bucket with lane groups, and
             # Cuckoo placing every new key by exchange into h_1 (Sec. 4.1)
-            ("bucketed_b16", "bucketed", dict(bucket_slots=16), b.HT_BFS_SPLIT),
+            ("bucketed_b16", "bucketed", dict(bucket_slots=16, keys_per_group=1), b.HT_BFS_SPLIT),
             ("cuckoo_paper_order", "cuckoo", dict(flags=b.HT_FLAG_CUCKOO_PAPER_ORDER), b.HT_BFS_SPLIT)):
         # c = 3 bucketed, c = 4 Cuckoo as in the W2 step (Cuckoo BFS levels: 31.6 against 33.1 ms fused,
         # 43.7 against 45.8 ms split at c = 3)

@@ -1,4 +1,7 @@
-// Bucketed (GPUexplore-style) table: find-or-put and query kernels.
+// Bucketed (GPUexplore-style) table: find-or-put and query kernels, by lane
+// groups as the paper has it and, further down, by one lane per key, which is
+// what a table runs unless its batch or its flags are better served by groups
+// (lane_rule in table.hip).
 //
 // Paper Sec. 4.2 / Fig. 4: a key is hashed with h_1 to a bucket; the whole
 // bucket is read cooperatively, one slot share per lane; the lanes vote
@@ -323,7 +326,7 @@ __global__ __launch_bounds__(kBlock) void bucketed_query_kernel(DevTable t, cons
   }
 }
 
-// ---- one lane per key (HT_FLAG_BUCKETED_ONE_LANE) ---------------------------
+// ---- one lane per key --------------------------------------------------------
 // The same table and probe sequence, but each lane probes whole buckets for
 // its own key: eight slots per step (four independent 16-byte loads), then
 // the first empty slot is compare-and-swapped.  Copies of a key read the same

@@ -157,8 +157,8 @@ def main():
     ap.add_argument("--mix-group", type=int, default=6)
     ap.add_argument("--mix-for", default="bucketed_fop,cuckoo_probe")
     ap.add_argument("--commands-file", help="text file with the commands of the runs, one per line")
-    ap.add_argument("--kernels", default="bucketed_fop_kernel,cuckoo_probe_kernel,cuckoo_evict_kernel,"
-                                         "cuckoo_scrub_kernel,probe_mix,probe_copy_kernel")
+    ap.add_argument("--kernels", default="bucketed_fop_kernel,bucketed_lane_fop_kernel,cuckoo_probe_kernel,"
+                                         "cuckoo_evict_kernel,cuckoo_scrub_kernel,probe_mix,probe_copy_kernel")
     ap.add_argument("--outdir", default=os.path.join(ROOT, "profiles"))
     args = ap.parse_args()
     cmds = open(args.commands_file).read().strip().splitlines() if args.commands_file else []
