@@ -225,26 +225,35 @@ __device__ __forceinline__ void vec_chain(const DevTable& t, uint64_t x, unsigne
   vec_stash_put(t, x);
 }
 
-// Arena entries for the lanes with `want` set: one counter atomic per wave
-// and range.  A wave starts at its own range and moves on while a range is
-// full, so every entry of every range is handed out.  ~0 when all are taken.
-__device__ inline uint64_t arena_take(const DevTable& t, bool want, uint64_t wave) {
-  uint64_t idx = ~0ull;
+// Arena entries for the U wants of each lane: one counter atomic per call and
+// range.  A wave starts at its own range and moves on while a range is full,
+// so every entry of every range is handed out.  ~0 when all are taken.
+template <int U>
+__device__ __forceinline__ void arena_take(const DevTable& t, bool (&want)[U], uint64_t wave, uint64_t (&idx)[U]) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) idx[u] = ~0ull;
   for (uint32_t a = 0; a < (uint32_t)kSpread; ++a) {
-    const uint64_t wm = ballot(want);
-    if (!wm) break;
+    uint64_t rank[U], total = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint64_t wm = ballot(want[u]);
+      rank[u] = total + lanes_below(wm);
+      total += (uint64_t)__popcll(wm);
+    }
+    if (!total) break;
     const uint32_t rg = (uint32_t)((wave + a) % kSpread);
     unsigned long long first = 0;
-    if (lane_id() == 0) first = add_agent(&t.ctr->arena_next[rg * kLineWords], (unsigned long long)__popcll(wm));
+    if (lane_id() == 0) first = add_agent(&t.ctr->arena_next[rg * kLineWords], (unsigned long long)total);
     first = shfl64(first, 0);
     const uint64_t avail = first < t.arena_cap ? t.arena_cap - first : 0;
-    const uint64_t rank = lanes_below(wm);
-    if (want && rank < avail) {
-      idx = (uint64_t)rg * t.arena_cap + first + rank;
-      want = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (want[u] && rank[u] < avail) {
+        idx[u] = (uint64_t)rg * t.arena_cap + first + rank[u];
+        want[u] = false;
+      }
     }
   }
-  return idx;
 }
 
 // List entry of a vector whose Cuckoo candidates were all taken at claim
@@ -316,7 +325,10 @@ void vec_evict_kernel(DevTable t, const uint64_t* __restrict__ keys, uint64_t n,
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (!ballot(winner)) continue;
-    const uint64_t idx = arena_take(t, winner, wave);
+    bool want[1] = {winner};
+    uint64_t took[1];
+    arena_take<1>(t, want, wave, took);
+    const uint64_t idx = took[0];
     if (winner) {
       ++nnew;
       if (idx == ~0ull) {
@@ -500,32 +512,44 @@ __device__ __forceinline__ uint64_t* vec_location(const DevTable& t, uint64_t lo
 }
 
 // Kernel 2: the claimed slots get arena entries, the vectors' words and
-// their final handles.
+// their final handles.  A wave takes up to three turns of its list together,
+// list entries and batch rows loaded before the one arena atomic: turn by
+// turn each waited for three dependent round trips (2^20 vectors a call, two
+// and four words: 26.3 and 33.2 us a call turn by turn, 23.9 and 27.5 so).
 template <int W>
 __global__ __launch_bounds__(kBlock) void vec_commit_kernel(DevTable t, const uint64_t* __restrict__ keys, uint64_t n,
                                                              CuckooScratch s) {
+  constexpr int U = 3;
   const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
   const uint64_t begin = wave * s.per_wave;
   const uint32_t cnt = begin < n ? s.wcnt[wave] : 0u;
-  for (uint32_t e0 = 0; e0 < cnt; e0 += kWave) {
-    const uint32_t e = e0 + (uint32_t)lane_id();
-    const uint64_t loc = e < cnt ? s.wkey[begin + e] : ~0ull;
-    const bool have = loc != ~0ull && loc != kLeftover;
-    if (!ballot(have)) continue;
-    const uint64_t idx = arena_take(t, have, wave);
-    if (!have) continue;
-    if (idx == ~0ull) {
-      add_agent(&t.ctr->lost, 1u);               // cannot happen: every claimed location has an entry
-      continue;
-    }
-    const uint64_t m = s.wmeta[begin + e];
-    const uint64_t i = m & kBatchMask;
-    uint64_t v[W];
-    load_vec<W>(keys + i * W, v);
+  for (uint32_t e0 = 0; e0 < cnt; e0 += U * kWave) {
+    uint64_t loc[U], m[U], v[U][W], idx[U];
+    bool have[U], want[U];
 #pragma unroll
-    for (int j = 0; j < W; j += 2)
-      *reinterpret_cast<ulonglong2*>(t.arena + idx * W + j) = make_ulonglong2(v[j], v[j + 1]);
-    store_coherent(vec_location(t, loc), ((m >> 33) << kArenaBits) | idx);
+    for (int u = 0; u < U; ++u) {
+      const uint32_t e = e0 + u * kWave + (uint32_t)lane_id();
+      loc[u] = e < cnt ? s.wkey[begin + e] : kLeftover;
+      m[u] = e < cnt ? s.wmeta[begin + e] : 0ull;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      have[u] = want[u] = loc[u] != kLeftover;
+      if (have[u]) load_vec<W>(keys + (m[u] & kBatchMask) * W, v[u]);
+    }
+    arena_take<U>(t, want, wave, idx);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!have[u]) continue;
+      if (idx[u] == ~0ull) {
+        add_agent(&t.ctr->lost, 1u);             // cannot happen: every claimed location has an entry
+        continue;
+      }
+#pragma unroll
+      for (int j = 0; j < W; j += 2)
+        *reinterpret_cast<ulonglong2*>(t.arena + idx[u] * W + j) = make_ulonglong2(v[u][j], v[u][j + 1]);
+      store_coherent(vec_location(t, loc[u]), ((m[u] >> 33) << kArenaBits) | idx[u]);
+    }
   }
 }
 
