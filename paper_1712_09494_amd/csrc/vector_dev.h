@@ -366,11 +366,22 @@ __device__ __forceinline__ int vec_claim_seen(uint64_t* p, uint64_t hd, uint64_t
   return 0;
 }
 
-// One slot of a bucketed walk that both looks up and claims: a member stored
-// by an earlier call (a committed handle) that holds the vector gives 3;
-// otherwise as vec_claim_seen.  No handle is committed while this runs (the
-// commit kernel comes after), so a failed compare-and-swap only ever returns
-// a placeholder.
+// One slot of a walk that only looks up: 3 = a member stored by an earlier call
+// (a committed handle) holds the vector, 2 = an equal vector of the batch does,
+// 0 = go on.
+template <int W>
+__device__ __forceinline__ int vec_find_seen(const DevTable& t, uint64_t hd, uint64_t hb, const uint64_t (&v)[W],
+                                             const uint64_t* __restrict__ keys, uint64_t n) {
+  const bool place = (hd & kPlaceBit) != 0;
+  if (hd == kEmpty || handle_hb(hd) != hb || (place && (hd & kBatchMask) >= n)) return 0;
+  uint64_t u[W];
+  load_vec<W>(place ? keys + (hd & kBatchMask) * W : t.arena + handle_idx(hd) * W, u);
+  return !vec_eq<W>(u, v) ? 0 : place ? 2 : 3;
+}
+
+// One slot of a walk that both looks up and claims: the answers of the two
+// above.  No handle is committed while this runs (the commit kernel comes
+// after), so a failed compare-and-swap only ever returns a placeholder.
 template <int W>
 __device__ __forceinline__ int vec_find_or_claim_seen(const DevTable& t, uint64_t* p, uint64_t hd, uint64_t ph,
                                                       uint64_t hb, const uint64_t (&v)[W],
@@ -452,7 +463,7 @@ void vec_find_or_claim_kernel(DevTable t, const uint64_t* __restrict__ keys, uin
           uint32_t em;
           for (uint32_t m = vec_eight(x, hb, em); m && !st; m &= m - 1) {
             const uint32_t k = (uint32_t)__builtin_ctz(m);
-            st = vec_find_or_claim_seen<W>(t, bk + k, bk[k], ph, hb, v, keys, n);
+            st = vec_find_seen<W>(t, bk[k], hb, v, keys, n);   // read again: the mask alone is kept
           }
           for (; em && !st; em &= em - 1) {
             const uint32_t k = (uint32_t)__builtin_ctz(em);
@@ -534,7 +545,7 @@ __global__ __launch_bounds__(kBlock) void vec_commit_kernel(DevTable t, const ui
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      have[u] = want[u] = loc[u] != kLeftover;
+      have[u] = want[u] = loc[u] < kLeftover;    // a location: neither that nor ~0
       if (have[u]) load_vec<W>(keys + (m[u] & kBatchMask) * W, v[u]);
     }
     arena_take<U>(t, want, wave, idx);
