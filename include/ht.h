@@ -153,9 +153,10 @@ typedef struct {
   uint32_t bucket_walk;    /* bucketed: consecutive buckets probed after h_c's
                               bucket before the stash; 0 = 64 */
   uint32_t lds_bytes;      /* ablation of the shared-memory setting of Sec. 6:
-                              bytes of LDS allocated (and left unused) per
-                              256-thread block of the single-table find-or-put
-                              and query kernels, which lowers how many waves a
+                              bytes of LDS allocated per 256-thread block of
+                              the single-table find-or-put and query kernels
+                              (left unused, but for the few KiB that some of
+                              them work in), which lowers how many waves a
                               compute unit holds; 0 = none.  At most the
                               device's LDS per block (HT_EINVAL otherwise) */
   uint32_t key_words;      /* words per key: 1 (64-bit keys), 2 or 4 (state

@@ -107,6 +107,11 @@ struct DevTable {
   uint32_t pad_;
 };
 
+// Dynamic LDS of a launch by a kernel with `own` bytes of its own: the rest of
+// the table's setting, so that a block's whole LDS is the setting (which may be
+// all that a block can have).
+inline uint32_t lds_left(const DevTable& t, size_t own) { return t.lds > own ? t.lds - (uint32_t)own : 0u; }
+
 // Scratch of the Cuckoo find-or-put (owned by the table).
 struct CuckooScratch {
   uint64_t* dset;        // deduplication set, dset_mask + 1 words, all empty when an evict kernel starts

@@ -260,6 +260,10 @@ __device__ __forceinline__ void arena_take(const DevTable& t, bool (&want)[U], u
 // time: it goes to the evict kernel.
 constexpr uint64_t kLeftover = ~1ull;
 
+struct EvictLds {
+  uint32_t list[kBlock / kWave][2 * kWave];   // a wave's gathered leftovers
+};
+
 // Kernel 3 (Cuckoo): the leftover vectors are deduplicated in the scratch
 // set by batch index (equal vectors compared word by word in the batch);
 // each winner reports 1, takes an arena entry, writes its words and runs the
@@ -278,8 +282,8 @@ void vec_evict_kernel(DevTable t, const uint64_t* __restrict__ keys, uint64_t n,
   const uint64_t begin = wave * s.per_wave;
   const uint32_t cnt = begin < n ? s.wcnt[wave] : 0u;
   unsigned long long nnew = 0, nevict = 0;
-  __shared__ uint32_t gathered[kBlock / kWave][2 * kWave];
-  uint32_t* list = gathered[threadIdx.x / kWave];
+  __shared__ EvictLds gathered;
+  uint32_t* list = gathered.list[threadIdx.x / kWave];
   uint32_t e0 = 0, have = 0;
   for (;;) {
     while (have < (uint32_t)kWave && e0 < cnt) {
