@@ -585,6 +585,7 @@ def kernel_rooflines(per_kernel, args, d, cap, new_per_batch, cuckoo_c=3):
         avg_ms = per_kernel[name]["avg_ms"]
         achieved = m["bytes"] / (avg_ms * 1e-3) / 1e9
         traffic = measured_traffic(name) if full_size else None
+        forms = sorted(k.split(".")[1] for k in per_kernel if k.startswith(name + "."))
         out[name] = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "bytes_per_launch": int(m["bytes"]), "avg_launch_ms": avg_ms,
@@ -592,6 +593,8 @@ def kernel_rooflines(per_kernel, args, d, cap, new_per_batch, cuckoo_c=3):
                      "model": {"lines_per_key": round(m["lines_per_key"], 4),
                                "cas_per_key": round(m["cas_per_key"], 4),
                                "model_vs_counter": round(m["bytes"] / traffic, 3) if traffic else None}}
+        if forms:
+            out[name]["forms"] = forms
     return out
 
 

@@ -581,7 +581,8 @@ def ht_timing_enable(on: bool = True) -> None:
 
 
 def ht_timing_report() -> dict:
-    """{kernel: (launches, total_ms)} of the launches timed so far."""
+    """{kernel: (launches, total_ms)} of the launches timed so far; a name with
+    a dot is the part of the name before it that one of its kernels served."""
     import json
     buf = C.create_string_buffer(1 << 16)
     _check(load().ht_timing_report(buf, len(buf)), "ht_timing_report")

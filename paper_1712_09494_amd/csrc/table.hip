@@ -109,6 +109,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // recorded on the launch stream; ht_timing_report resolves them.
 struct PendingTiming {
   const char* name;
+  const char* form;           // NULL, or which of a name's kernels it was
   hipEvent_t a, b;
 };
 std::mutex g_tmu;
@@ -123,11 +124,12 @@ struct KernelTimer {
   PendingTiming p{};
   bool on = false;
   hipStream_t s;
-  KernelTimer(const char* name, hipStream_t st) : s(st) {
+  KernelTimer(const char* name, hipStream_t st, const char* form = nullptr) : s(st) {
     if (g_quiet) return;
     std::lock_guard<std::mutex> lk(g_tmu);
     if (!g_timing) return;
     p.name = name;
+    p.form = form;
     if (hipEventCreate(&p.a) != hipSuccess || hipEventCreate(&p.b) != hipSuccess) return;
     on = hipEventRecord(p.a, s) == hipSuccess;
   }
@@ -144,9 +146,13 @@ void resolve_timings() {
   for (auto& p : g_pending) {
     float ms = 0.f;
     if (hipEventSynchronize(p.b) == hipSuccess && hipEventElapsedTime(&ms, p.a, p.b) == hipSuccess) {
-      auto& e = g_acc[p.name];
-      e.first += 1;
-      e.second += ms;
+      const auto add = [&](const std::string& key) {
+        auto& e = g_acc[key];
+        e.first += 1;
+        e.second += ms;
+      };
+      add(p.name);
+      if (p.form) add(std::string(p.name) + "." + p.form);
     }
     (void)hipEventDestroy(p.a);
     (void)hipEventDestroy(p.b);
@@ -631,7 +637,7 @@ int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, 
   const bool one_lane = (t->cfg.flags & HT_FLAG_BUCKETED_ONE_LANE) != 0;
   if (t->cfg.kind == HT_BUCKETED && (one_lane || lane_rule(t, n, repeats))) {
     const uint64_t blocks = std::min<uint64_t>((n + kBlock - 1) / kBlock, atomic_grid_blocks(t));
-    KernelTimer kt(one_lane ? "bucketed_lane_fop" : "bucketed_fop", s);
+    KernelTimer kt(one_lane ? "bucketed_lane_fop" : "bucketed_fop", s, one_lane ? nullptr : "lanes");
     HT_HIP(bucketed_lane_find_or_put(d, keys, n, out, (uint32_t)blocks, scripted, s));
     return HT_OK;
   }
@@ -639,7 +645,7 @@ int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, 
     const uint64_t g = bucketed_keys_per_wave(t->cfg.bucket_slots, R, kFopSlotsPerLane);
     const uint64_t waves = (n + g - 1) / g;
     const uint64_t blocks = std::min<uint64_t>((waves + 3) / 4, max_blocks(t));
-    KernelTimer kt("bucketed_fop", s);
+    KernelTimer kt("bucketed_fop", s, "groups");
     HT_HIP(bucketed_find_or_put(d, keys, n, out, (uint32_t)blocks, R,
                                 (t->cfg.flags & HT_FLAG_BUCKETED_ATOMIC_LOADS) != 0, scripted, s));
     return HT_OK;

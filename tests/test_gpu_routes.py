@@ -1,0 +1,47 @@
+"""GPU: which kernels serve a find-or-put, from the timing report: the names
+tell the forms of one kernel apart, and the rules that choose between forms
+are looked at on both sides of their edges.  Flags against the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import Oracle  # noqa: E402
+from paper_1712_09494_amd import binding as b  # noqa: E402
+from paper_1712_09494_amd import inputs  # noqa: E402
+from parity import check_flags_r2  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int64)).cuda()
+
+
+def routes(call):
+    """The names that a call adds to the timing report, with their launches."""
+    b.ht_timing_enable(True)
+    call()
+    r = {k: v[0] for k, v in b.ht_timing_report().items()}
+    b.ht_timing_enable(False)
+    return r
+
+
+def served(t, o, keys):
+    out = {}
+    r = routes(lambda: out.update(f=t.find_or_put(dev(keys))))
+    check_flags_r2(keys, out["f"].cpu().numpy(), o.find_or_put(keys), f"n={keys.size}")
+    return r
+
+
+def test_names_tell_lanes_from_groups():
+    keys = inputs.uniform_keys(3000, seed=1)
+    for kw, names in ((dict(keys_per_group=1), {"bucketed_fop", "bucketed_fop.groups"}),
+                      (dict(flags=b.HT_FLAG_BUCKETED_ATOMIC_LOADS), {"bucketed_fop", "bucketed_fop.groups"}),
+                      (dict(flags=b.HT_FLAG_BUCKETED_ONE_LANE), {"bucketed_lane_fop"})):
+        with b.Table("bucketed", capacity=40000, nhash=3, bucket_slots=16, **kw) as t:
+            assert served(t, Oracle(), keys) == dict.fromkeys(names, 1)
+    n = 1 << 20                                # lanes, whichever rule chooses them
+    with b.Table("bucketed", capacity=40 * n, nhash=3, bucket_slots=16) as t:
+        r = served(t, Oracle(), inputs.uniform_keys(n, seed=2))
+        assert r == {"bucketed_fop": 1, "bucketed_fop.lanes": 1}
