@@ -324,10 +324,10 @@ int reserve_scratch(ht_table* t, uint64_t n) {
   return HT_OK;
 }
 
-// Ordinary bucketed tables of single-word keys (none of the measurement and
-// test modes that ask for a particular kernel).
+// Ordinary bucketed tables of single-word keys (none of the settings and modes
+// that ask for a particular kernel).
 static bool tile_table(const ht_table* t) {
-  return t->cfg.kind == HT_BUCKETED && t->cfg.key_words <= 1 && !t->cfg.lds_bytes &&
+  return t->cfg.kind == HT_BUCKETED && t->cfg.key_words <= 1 && !t->cfg.lds_bytes && !t->user_cfg.keys_per_group &&
          !(t->cfg.flags & (HT_FLAG_SCRIPTED_HASH | HT_FLAG_BUCKETED_ONE_LANE | HT_FLAG_BUCKETED_ATOMIC_LOADS));
 }
 

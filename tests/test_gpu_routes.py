@@ -45,3 +45,21 @@ def test_names_tell_lanes_from_groups():
     with b.Table("bucketed", capacity=40 * n, nhash=3, bucket_slots=16) as t:
         r = served(t, Oracle(), inputs.uniform_keys(n, seed=2))
         assert r == {"bucketed_fop": 1, "bucketed_fop.lanes": 1}
+
+
+@pytest.mark.parametrize("width", [8, 64])
+@pytest.mark.parametrize("per_group", [0, 1, 2, 4])
+def test_keys_per_group_asks_for_the_groups(width, per_group):
+    """First batches that an ordinary table takes in LDS, by a single call and
+    by a plan."""
+    for n, cap, whole in ((1000, 4096, "tile_whole"), (1 << 18, 1 << 19, "tile_insert")):
+        keys = inputs.uniform_keys(n, seed=n)
+        with b.Table("bucketed", capacity=cap, nhash=3, bucket_slots=width, keys_per_group=per_group) as t:
+            r = served(t, Oracle(), keys)
+            assert r == {"bucketed_fop": 1, "bucketed_fop.groups": 1} if per_group else whole in r
+            t.clear()
+            out = torch.empty(n, dtype=torch.uint8, device="cuda")
+            plan = b.MultiPlan([t], [dev(keys)], [out])
+            assert routes(plan.launch) == {"multi_fill" if per_group else "multi_tiles": 1}
+            assert out.all() and t.size() == n
+            plan.close()
