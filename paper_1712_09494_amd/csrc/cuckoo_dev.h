@@ -134,11 +134,14 @@ constexpr uint64_t kIdxMask = (1ull << 40) - 1;
 // slot indices coincide read all c slots first and then try the empty ones
 // in order.  Keys with every candidate taken go to the wave's region as
 // (key, index).  In paper order nothing is placed: the first empty slot (or
-// the end of the probe) lists the key.
-template <int R, bool SCRIPTED, bool PAPER_ORDER>
+// the end of the probe) lists the key.  With `meet` (the wave's kMeetPlaces
+// words; R = 1) one lane compare-and-swaps for the copies of its key.
+template <int R, bool SCRIPTED, bool PAPER_ORDER, bool MEET = false>
 __device__ __forceinline__ unsigned long long cuckoo_probe_region(const DevTable& t, const uint64_t* __restrict__ keys,
                                                                   uint64_t n, uint8_t* __restrict__ out,
-                                                                  const CuckooScratch& s, uint64_t wave) {
+                                                                  const CuckooScratch& s, uint64_t wave,
+                                                                  uint32_t* meet = nullptr) {
+  static_assert(!MEET || R == 1, "copies meet one key per lane at a time");
   const int lane = lane_id();
   const uint64_t begin = wave * s.per_wave;
   uint64_t end = begin + s.per_wave;
@@ -210,8 +213,21 @@ __device__ __forceinline__ unsigned long long cuckoo_probe_region(const DevTable
       }
       if (PAPER_ORDER) continue;
       uint64_t old[R];
+      if constexpr (MEET) {
+        if (cas[0]) {
+          const Meeting with = wave_meet(meet, (uint32_t)idx[0]);
+          const bool any = ballot(with.maybe) != 0;
+          const bool copy = any && shfl64(k[0], with.lead) == k[0] && with.maybe;
+          if (!copy) old[0] = cas64(&t.slots[idx[0]], kEmpty, k[0]);
+          if (any) {
+            const uint64_t led = shfl64(old[0], with.lead);
+            if (copy) old[0] = led == kEmpty ? k[0] : led;
+          }
+        }
+      } else {
 #pragma unroll
-      for (int r = 0; r < R; ++r) old[r] = cas[r] ? cas64(&t.slots[idx[r]], kEmpty, k[r]) : 0;
+        for (int r = 0; r < R; ++r) old[r] = cas[r] ? cas64(&t.slots[idx[r]], kEmpty, k[r]) : 0;
+      }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (cas[r] && (old[r] == kEmpty || old[r] == k[r])) {

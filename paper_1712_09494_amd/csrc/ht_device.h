@@ -307,6 +307,33 @@ __device__ __forceinline__ void wave_count(unsigned long long* spread, unsigned 
   if (lane_id() == 0 && s) add_agent(&spread[(salt % kSpread) * kLineWords], s);
 }
 
+// Copies of one key in a wave.  Each active lane leaves its number and 26 bits
+// of its key's hash at one of the wave's kMeetPlaces words in LDS and reads the
+// word back: the lane named there (`lead`) stands for every lane with its key,
+// which then takes its result instead of compare-and-swapping the same slot.
+// `maybe`: another lane is named, with the same hash bits (the caller compares
+// the keys).  Different keys at one place leave all but one of them to act for
+// themselves.
+constexpr uint32_t kMeetPlaces = 128;
+
+struct MeetLds {                              // of a block of kBlock threads
+  uint32_t wave[kBlock / kWave][kMeetPlaces];
+};
+
+struct Meeting {
+  uint32_t lead;
+  bool maybe;
+};
+
+__device__ __forceinline__ Meeting wave_meet(uint32_t* places, uint32_t hash) {
+  uint32_t* p = places + (hash & (kMeetPlaces - 1));
+  const uint32_t mine = hash << 6 | (uint32_t)lane_id();
+  __hip_atomic_store(p, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const uint32_t got = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return Meeting{got & 63u, got != mine && got >> 6 == mine >> 6};
+}
+
 // Add the block's lanes' counts to a spread counter: one atomic per block (an
 // atomic per wave puts five hundred of them on each of the sixteen lines in a
 // 2^20-key call: 4 us of the tile pass).  *sum (LDS) is zero before; it holds

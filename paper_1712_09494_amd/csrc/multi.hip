@@ -56,6 +56,7 @@ __global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
 void multi_fill_kernel(const MultiTable* __restrict__ tabs, const uint64_t* __restrict__ items, uint32_t nitems) {
   const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
   const uint64_t nwaves = (uint64_t)gridDim.x * (kBlock / kWave);
+  __shared__ MeetLds meet;
   for (uint64_t idx = wave; idx < nitems; idx += nwaves) {
     // uniform across the wave: keep the item (and so the table descriptor's
     // address) in scalar registers
@@ -67,7 +68,7 @@ void multi_fill_kernel(const MultiTable* __restrict__ tabs, const uint64_t* __re
     const uint64_t end = begin + m.chunk < m.n ? begin + m.chunk : m.n;
     unsigned long long nnew = 0;
     for (uint64_t i = begin + lane_id(); i < end; i += kWave) {
-      const uint32_t r = lane_find_or_put<false>(m.t, m.keys[i]);
+      const uint32_t r = lane_find_or_put<false>(m.t, m.keys[i], meet.wave[threadIdx.x / kWave]);
       if (m.out) m.out[i] = (uint8_t)r;
       nnew += r == 1;
     }
@@ -96,13 +97,15 @@ void multi_cuckoo_probe_kernel(const MultiCuckoo* __restrict__ tabs, const uint6
                                uint32_t nitems) {
   const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
   const uint64_t nwaves = (uint64_t)gridDim.x * (kBlock / kWave);
+  __shared__ MeetLds places;
+  uint32_t* const meet = places.wave[threadIdx.x / kWave];
   for (uint64_t idx = wave; idx < nitems; idx += nwaves) {
     const uint64_t it = uniform_item(items, idx);
     const MultiCuckoo& m = tabs[(uint32_t)(it >> 40)];
     const uint64_t region = it & kRegionMask;
     const unsigned long long nnew =
         m.paper ? cuckoo_probe_region<1, false, true>(m.t, m.keys, m.n, m.out, m.s, region)
-                : cuckoo_probe_region<1, false, false>(m.t, m.keys, m.n, m.out, m.s, region);
+                : cuckoo_probe_region<1, false, false, true>(m.t, m.keys, m.n, m.out, m.s, region, meet);
     wave_count(m.t.ctr->size, nnew, (uint32_t)(wave + idx));
   }
 }

@@ -252,6 +252,7 @@ struct TileFinishLds {
   uint64_t mkey[C];         // keys that go on at h_2
   uint16_t midx[C];         // and their places in the chunk
   uint8_t flag[C];
+  uint32_t meet[kTileBlock / kWave][kMeetPlaces];
   uint32_t nmore;
   uint32_t nnew;
 };
@@ -296,7 +297,8 @@ __device__ __forceinline__ void tile_finish_chunk(const TileJob& j, uint32_t c, 
   uint32_t nnew = 0;
   for (uint32_t e = tid; e < nmore; e += kTileBlock) {
     const uint64_t key = l.mkey[e];
-    const uint32_t r = lane_put_from<false>(j.t, key, 0, hidx<false>(j.t, key, 0), j.t.bucket_slots);
+    const uint32_t r = lane_put_from<false>(j.t, key, 0, hidx<false>(j.t, key, 0), j.t.bucket_slots,
+                                            l.meet[tid / kWave]);
     nnew += r == 1;
     l.flag[l.midx[e]] = (uint8_t)r;
   }

@@ -349,6 +349,19 @@ void vec_evict_kernel(DevTable t, const uint64_t* __restrict__ keys, uint64_t n,
   wave_count(t.ctr->evictions, nevict, (uint32_t)wave);
 }
 
+// The lane that claims for this lane's vector: itself, or a lane of the wave
+// with an equal vector (see wave_meet).
+template <int W>
+__device__ __forceinline__ uint32_t vec_meet(uint32_t* places, uint64_t hb, const uint64_t (&v)[W]) {
+  const Meeting with = wave_meet(places, (uint32_t)hb);
+  bool equal = with.maybe;
+  if (ballot(equal)) {
+#pragma unroll
+    for (int j = 0; j < W; ++j) equal &= shfl64(v[j], with.lead) == v[j];
+  }
+  return equal ? with.lead : (uint32_t)lane_id();
+}
+
 // One slot of a claim walk, given the value read there: 1 = the placeholder
 // is now here, 2 = an equal vector of the batch holds this slot, 0 = go on.
 template <int W>
@@ -408,7 +421,7 @@ __device__ __forceinline__ int vec_find_or_claim_seen(const DevTable& t, uint64_
 // leftovers, as kLeftover) are listed per wave region as (location, hash
 // bits << 33 | batch index) for the commit and evict kernels.
 template <int W>
-__global__ __launch_bounds__(kBlock) HT_EIGHT_WAVES
+__global__ __launch_bounds__(kBlock, 8) HT_EIGHT_WAVES
 void vec_find_or_claim_kernel(DevTable t, const uint64_t* __restrict__ keys, uint64_t n, uint8_t* __restrict__ out,
                               CuckooScratch s) {
   const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
@@ -421,6 +434,8 @@ void vec_find_or_claim_kernel(DevTable t, const uint64_t* __restrict__ keys, uin
   const uint64_t nslots = t.nrange * B;
   const uint32_t sc = t.ctr->stash_count;
   const uint32_t oc = t.ctr->overflow_count;
+  __shared__ MeetLds places;
+  uint32_t* const meet = places.wave[threadIdx.x / kWave];
   uint32_t nlist = 0;
   unsigned long long nnew = 0;
   for (uint64_t base = begin; base < end; base += kWave) {
@@ -441,8 +456,17 @@ void vec_find_or_claim_kernel(DevTable t, const uint64_t* __restrict__ keys, uin
       }
       for (uint32_t j = 0; j < t.nhash && !st; ++j) {
         const uint64_t sl = hidx<false>(t, hb, j);
-        st = vec_find_or_claim_seen<W>(t, t.slots + sl, t.slots[sl], ph, hb, v, keys, n);
+        const uint64_t hd = t.slots[sl];
+        if (hd != kEmpty) {
+          st = vec_find_seen<W>(t, hd, hb, v, keys, n);
+          continue;
+        }
+        const uint32_t lead = vec_meet<W>(meet, hb, v);
+        const bool copy = lead != (uint32_t)lane;
+        if (!copy) st = vec_claim_seen<W>(t.slots + sl, kEmpty, ph, hb, v, keys, n);
         if (st == 1) loc = sl;
+        const uint32_t led = shfl32((uint32_t)st, lead);
+        if (copy && led) st = 2;
       }
       claimed = st == 1;
       leftover = st == 0;                        // every candidate taken: the evict kernel decides
@@ -460,7 +484,8 @@ void vec_find_or_claim_kernel(DevTable t, const uint64_t* __restrict__ keys, uin
         for (uint32_t c0 = 0; c0 < B && !st; c0 += 8) {
           // stored handles with the same hash bits first (they lie before the
           // first empty slot), then the empty slots from the lowest on: every
-          // lane at its own first empty slot together
+          // lane at its own first empty slot together, one lane for the equal
+          // vectors of the wave
           uint64_t* bk = t.slots + b * B + c0;
           uint64_t x[8];
           load8(bk, x);
@@ -469,10 +494,16 @@ void vec_find_or_claim_kernel(DevTable t, const uint64_t* __restrict__ keys, uin
             const uint32_t k = (uint32_t)__builtin_ctz(m);
             st = vec_find_seen<W>(t, bk[k], hb, v, keys, n);   // read again: the mask alone is kept
           }
-          for (; em && !st; em &= em - 1) {
-            const uint32_t k = (uint32_t)__builtin_ctz(em);
-            st = vec_claim_seen<W>(bk + k, kEmpty, ph, hb, v, keys, n);
-            if (st == 1) loc = b * B + c0 + k;
+          if (em && !st) {
+            const uint32_t lead = vec_meet<W>(meet, hb, v);
+            const bool copy = lead != (uint32_t)lane;
+            for (; em && !st && !copy; em &= em - 1) {
+              const uint32_t k = (uint32_t)__builtin_ctz(em);
+              st = vec_claim_seen<W>(bk + k, kEmpty, ph, hb, v, keys, n);
+              if (st == 1) loc = b * B + c0 + k;
+            }
+            const uint32_t led = shfl32((uint32_t)st, lead);
+            if (copy && led) st = 2;
           }
         }
       }
