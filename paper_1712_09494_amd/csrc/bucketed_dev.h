@@ -355,9 +355,9 @@ __device__ __forceinline__ bool eight_slots(const uint64_t (&x)[8], uint64_t k, 
 // they hold eight other keys.  `meet`: kMeetPlaces words of the wave, `hash`
 // the key's place there.  One lane acts for the copies of its key in the wave:
 // compare-and-swaps of one slot are served one after another, 11 ns each
-// (2^18 copies of one key into an empty table: 2939 us with one per lane, 52
-// so; all keys different: 41.1 and 43.2).
-// The lanes meet while their slots are on the way.
+// (2^18 copies of one key into an empty table: 2939 us with one per lane, 56
+// so; all keys different: 41 either way; a fill of 2^26 keys in batches of 2^20
+// 3476 and 3497).  The lanes meet while their slots are on the way.
 __device__ __forceinline__ uint32_t eight_put(uint64_t* p, uint64_t k, uint32_t* meet, uint32_t hash) {
   uint64_t x[8];
   load8(p, x);

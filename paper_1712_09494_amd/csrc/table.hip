@@ -360,22 +360,25 @@ static bool plan_tile_rule(const ht_table* t, uint64_t n) {
 }
 
 // Whether a find-or-put probes with one lane per key instead of the lane
-// groups of Sec. 4.2, when neither is asked for.  Since each lane takes its
-// first empty slot from a mask of eight, one lane per key is mostly the faster
-// (2^25 keys, 10% repeats, batches of 2^20 at load factors 0.5, 0.7 and 0.9,
-// groups and lanes: 8 slots 1.72 1.80 1.98 and 1.71 1.77 1.92 ms, 16 slots
-// 1.82 1.95 2.12 and 1.76 1.87 2.01, 64 slots 4.37 4.22 3.92 and 2.52 2.59
-// 2.86; batches of 2^16: 4.58 4.86 5.65 and 4.26 4.59 5.49, 8.17 8.09 8.10
-// and 5.32 5.94 7.58; exploration batches 19.8 and 18.8 ms).  The groups are
-// ahead where a wide bucket's reads meet too few waves to hide them (new keys
-// into 64-slot buckets, groups and lanes: 5000 keys 7.7 and 10.4 us, 20000
-// 10.1 and 11.1, 2^16 15.8 and 12.3; 16 slots: 5000 keys 6.1 and 6.5, 20000
-// 6.9 and 6.8), and in large batches of mostly new keys into 8-slot buckets
-// (batches of 2^22: 1.46 1.56 1.76 and 1.51 1.58 1.71 ms).
+// groups of Sec. 4.2, when neither is asked for: when its keys fill the grid of
+// one lane per key and the table has 16 slots or more for each.  Then a lane's
+// eight-slot steps wait behind enough other waves, and the keys in flight
+// rarely meet in a bucket (new keys, and keys stored before, by groups and by
+// lanes, at load factors 0.3, 0.6 and 0.8; 2^20 keys, 2^26 slots: 8-slot
+// buckets 57 62 87 and 57 59 81 us, 30 32 40 and 27 30 34; 16 slots 58 71 99
+// and 57 67 91; 64 slots 141 140 163 and 87 124 164, 104 104 103 and 32 47
+// 66).  Fewer keys run groups, which read a bucket at once (2^16 keys, 2^22
+// slots, load factors 0.3 and 0.8: 8 slots 11.7 18.7 and 11.2 20.8, 16 slots
+// 11.8 16.1 and 12.3 21.4, 64 slots 17.9 19.4 and 16.2 33.2; 64-slot buckets
+// nearly full 58 and 258), and so do keys that crowd the table: each bucket's
+// new keys take its next slot one after another, and lanes bring more of them
+// at once (2^18 keys into 2^19 empty slots: 8 slots 41 and 41, 16 slots 38 and
+// 63, 64 slots 76 and 175).  An exploration's batches, mostly repeats, need
+// no such room (18.8 against 19.8 ms for seven levels).
 static bool lane_rule(const ht_table* t, uint64_t n, bool repeats) {
   if (t->user_cfg.keys_per_group || (t->cfg.flags & HT_FLAG_BUCKETED_ATOMIC_LOADS)) return false;
-  if (t->cfg.bucket_slots == 8) return n < (1ull << 21) || repeats;
-  return n >= 512ull * t->cfg.bucket_slots;
+  if (repeats) return t->cfg.bucket_slots == 8 || n >= 512ull * t->cfg.bucket_slots;
+  return n >= (uint64_t)atomic_grid_blocks(t) * kBlock && t->nslots / 16 >= n;
 }
 
 // Whether one block does the call with the whole table in LDS: a batch that

@@ -63,3 +63,15 @@ def test_keys_per_group_asks_for_the_groups(width, per_group):
             assert routes(plan.launch) == {"multi_fill" if per_group else "multi_tiles": 1}
             assert out.all() and t.size() == n
             plan.close()
+
+
+@pytest.mark.parametrize("width", [8, 16, 64])
+def test_lanes_need_many_keys_and_room(width):
+    """Groups below as many keys as the one-lane grid has lanes, and where the
+    table has less than 16 slots a key."""
+    lanes = torch.cuda.get_device_properties(0).multi_processor_count * 6 * 256
+    for n, cap, form in ((lanes - 1, 16 * lanes, "groups"), (lanes, 16 * lanes, "lanes"),
+                         (lanes, 16 * lanes - width, "groups"), (4096, 1 << 20, "groups"), (40000, 1 << 20, "groups")):
+        with b.Table("bucketed", capacity=cap, nhash=3, bucket_slots=width) as t:
+            r = served(t, Oracle(), inputs.uniform_keys(n, seed=n))
+            assert r == {"bucketed_fop": 1, f"bucketed_fop.{form}": 1}, (n, cap)
