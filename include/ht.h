@@ -535,9 +535,10 @@ int ht_timing_enable(int on);
 /* Infrastructure (measurement).  JSON object {"kernel name": [launches,
  * total milliseconds], ...} of the
  * launches timed since ht_timing_enable; waits for their events.  A name with
- * a dot counts the launches of the name before it again that ran one of its
- * kernels: "bucketed_fop.lanes" (one lane per key) and "bucketed_fop.groups"
- * of "bucketed_fop".  HT_EINVAL when buf is NULL or too small. */
+ * a dot tells how many launches of the name before it ran one of its kernels,
+ * with no time of its own: "bucketed_fop.lanes" (one lane per key) and
+ * "bucketed_fop.groups" of "bucketed_fop".  HT_EINVAL when buf is NULL or too
+ * small. */
 int ht_timing_report(char* buf, uint64_t len);
 
 /* ---- roofline probes: memory-system reference kernels ------------------- */

@@ -582,7 +582,8 @@ def ht_timing_enable(on: bool = True) -> None:
 
 def ht_timing_report() -> dict:
     """{kernel: (launches, total_ms)} of the launches timed so far; a name with
-    a dot is the part of the name before it that one of its kernels served."""
+    a dot counts the launches of the name before it that ran one of its kernels
+    (no time of its own, so that the times add up)."""
     import json
     buf = C.create_string_buffer(1 << 16)
     _check(load().ht_timing_report(buf, len(buf)), "ht_timing_report")

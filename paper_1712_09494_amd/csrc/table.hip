@@ -146,13 +146,10 @@ void resolve_timings() {
   for (auto& p : g_pending) {
     float ms = 0.f;
     if (hipEventSynchronize(p.b) == hipSuccess && hipEventElapsedTime(&ms, p.a, p.b) == hipSuccess) {
-      const auto add = [&](const std::string& key) {
-        auto& e = g_acc[key];
-        e.first += 1;
-        e.second += ms;
-      };
-      add(p.name);
-      if (p.form) add(std::string(p.name) + "." + p.form);
+      auto& e = g_acc[p.name];
+      e.first += 1;
+      e.second += ms;
+      if (p.form) g_acc[std::string(p.name) + "." + p.form].first += 1;   // its time once, above
     }
     (void)hipEventDestroy(p.a);
     (void)hipEventDestroy(p.b);

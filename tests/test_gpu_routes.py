@@ -41,6 +41,13 @@ def test_names_tell_lanes_from_groups():
                       (dict(flags=b.HT_FLAG_BUCKETED_ONE_LANE), {"bucketed_lane_fop"})):
         with b.Table("bucketed", capacity=40000, nhash=3, bucket_slots=16, **kw) as t:
             assert served(t, Oracle(), keys) == dict.fromkeys(names, 1)
+    # the form's time is in the name before the dot, once
+    with b.Table("bucketed", capacity=40000, nhash=3, bucket_slots=16) as t:
+        b.ht_timing_enable(True)
+        t.find_or_put(dev(keys))
+        r = b.ht_timing_report()
+        b.ht_timing_enable(False)
+        assert r["bucketed_fop"][1] > 0 and r["bucketed_fop.groups"] == (1, 0.0)
     n = 1 << 20                                # lanes, whichever rule chooses them
     with b.Table("bucketed", capacity=40 * n, nhash=3, bucket_slots=16) as t:
         r = served(t, Oracle(), inputs.uniform_keys(n, seed=2))
