@@ -25,6 +25,7 @@ struct TileJob {
   uint32_t tiles;
   uint32_t shift;           // log2 of the slots of a tile
   uint32_t run_lanes;       // lanes that serve one run (a power of two)
+  uint32_t run_most;        // longest run that keys without copies make
 };
 
 // An item of a many-table launch: a chunk or a tile of a job (tiles == 0: the

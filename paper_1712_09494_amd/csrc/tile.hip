@@ -6,7 +6,7 @@
 namespace ht {
 
 template <uint32_t C>
-__global__ __launch_bounds__(kTileBlock) void tile_partition_kernel(TileJob j) {
+__global__ __launch_bounds__(kTileBlock, C == 4096 ? 8 : 4) void tile_partition_kernel(TileJob j) {
   __shared__ TilePartLds<C> l;
   tile_partition_chunk<C>(j, blockIdx.x, l);
 }
@@ -36,8 +36,8 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
          __builtin_amdgcn_readfirstlane((uint32_t)x);
 }
 
-__global__ __launch_bounds__(kTileBlock) void tile_multi_partition_kernel(const TileJob* __restrict__ jobs,
-                                                                          const uint64_t* __restrict__ items) {
+__global__ __launch_bounds__(kTileBlock, 8) void tile_multi_partition_kernel(const TileJob* __restrict__ jobs,
+                                                                             const uint64_t* __restrict__ items) {
   __shared__ TilePartLds<4096> l;
   const uint64_t it = uniform64(items[blockIdx.x]);
   tile_partition_chunk<4096>(jobs[it >> 32], (uint32_t)it, l);
@@ -111,6 +111,7 @@ TileJob tile_job(const DevTable& t, const uint64_t* keys, uint64_t n, uint8_t* o
   j.tiles = s.tiles;
   j.shift = s.shift;
   j.run_lanes = s.run_lanes;
+  j.run_most = 2 * (s.chunk / (s.tiles ? s.tiles : 1)) + 16;
   return j;
 }
 

@@ -34,6 +34,7 @@ namespace ht {
 
 constexpr uint32_t kTileBlock = 1024;       // threads of the tile kernels
 constexpr uint32_t kTileMore = 0xff;        // flag of a key that goes on at h_2
+constexpr uint32_t kTileCopy = 0xfe;        // flag of a copy left out by the partition
 
 // First slot of key k's h_1 bucket.
 __device__ __forceinline__ uint64_t tile_home(const DevTable& t, uint64_t k) {
@@ -59,11 +60,15 @@ struct TilePartLds {
   uint16_t idx[C];
   uint32_t hist[kTileMax];
   uint32_t wsum[kTileBlock / kWave];
+  uint32_t crowded;         // a run far longer than keys without copies make
+  uint32_t ncopy;
 };
 
-// Sort chunk `c` of the job's batch by tile.
-template <uint32_t C>
-__device__ __forceinline__ void tile_partition_chunk(const TileJob& j, uint32_t c, TilePartLds<C>& l) {
+// Sort chunk `c` of the job's batch by tile.  COPIES: leave copies out (see
+// tile_partition_chunk).  Without it the answer is false, and nothing is
+// stored, when a run is too long.
+template <uint32_t C, bool COPIES>
+__device__ __forceinline__ bool tile_sort_chunk(const TileJob& j, uint32_t c, TilePartLds<C>& l) {
   constexpr uint32_t PER = C / kTileBlock;
   const uint32_t tid = threadIdx.x;
   const uint64_t base = (uint64_t)c * C;
@@ -75,13 +80,36 @@ __device__ __forceinline__ void tile_partition_chunk(const TileJob& j, uint32_t 
     k[r] = i < m ? j.keys[base + i] : 0;
   }
   for (uint32_t i = tid; i < j.tiles; i += kTileBlock) l.hist[i] = 0;
+  if (tid == 0) l.crowded = l.ncopy = 0;
+  uint32_t rank[PER];                        // place in its run; of a copy the place of the key it copies
+  uint32_t copies = 0;                       // bit r: key r is a copy
+  if constexpr (COPIES) {
+    // l.key: the chunk in its order, l.idx: the words that keys share by hash
+    uint32_t word[PER];
+#pragma unroll
+    for (uint32_t r = 0; r < PER; ++r) {
+      const uint32_t i = r * kTileBlock + tid;
+      word[r] = (uint32_t)mix64(k[r] ^ (j.t.stash_seed + c)) & (C - 1);
+      if (i < m) {
+        l.key[i] = k[r];
+        l.idx[word[r]] = (uint16_t)i;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < PER; ++r) {
+      const uint32_t i = r * kTileBlock + tid;
+      rank[r] = i < m ? l.idx[word[r]] : i;
+      if (rank[r] != i && l.key[rank[r]] == k[r]) copies |= 1u << r;
+    }
+  }
   __syncthreads();
-  uint32_t tl[PER], rank[PER];
+  uint32_t tl[PER];
 #pragma unroll
   for (uint32_t r = 0; r < PER; ++r) {
     tl[r] = (uint32_t)(tile_home(j.t, k[r]) >> j.shift);
-    rank[r] = 0;
-    if (r * kTileBlock + tid < m)
+    if (!COPIES) rank[r] = 0;
+    if (r * kTileBlock + tid < m && !(COPIES && copies >> r & 1u))
       rank[r] = __hip_atomic_fetch_add(&l.hist[tl[r]], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
   __syncthreads();
@@ -90,13 +118,23 @@ __device__ __forceinline__ void tile_partition_chunk(const TileJob& j, uint32_t 
   const uint32_t per = (j.tiles + kTileBlock - 1) / kTileBlock;
   const uint32_t a = tid * per < j.tiles ? tid * per : j.tiles;
   const uint32_t z = a + per < j.tiles ? a + per : j.tiles;
-  uint32_t mine = 0;
-  for (uint32_t i = a; i < z; ++i) mine += l.hist[i];
+  uint32_t mine = 0, most = 0;
+  for (uint32_t i = a; i < z; ++i) {
+    const uint32_t v = l.hist[i];
+    mine += v;
+    most = v > most ? v : most;
+  }
   const uint32_t incl = tile_wave_inclusive(mine);
   if (lane_id() == kWave - 1) l.wsum[tid / kWave] = incl;
+  if (!COPIES && most > j.run_most) l.crowded = 1;
   __syncthreads();
-  uint32_t run = incl - mine;
+  if (!COPIES && l.crowded) return false;
+  uint32_t run = incl - mine, total = m;     // total: keys in runs
   for (uint32_t w = 0; w < tid / kWave; ++w) run += l.wsum[w];
+  if constexpr (COPIES) {
+    total = 0;
+    for (uint32_t w = 0; w < kTileBlock / kWave; ++w) total += l.wsum[w];
+  }
   uint16_t* off = j.off + (uint64_t)c * (j.tiles + 1);
   for (uint32_t i = a; i < z; ++i) {
     const uint32_t v = l.hist[i];
@@ -104,14 +142,19 @@ __device__ __forceinline__ void tile_partition_chunk(const TileJob& j, uint32_t 
     off[i] = (uint16_t)run;
     run += v;
   }
-  if (tid == 0) off[j.tiles] = (uint16_t)m;
+  if (tid == 0) off[j.tiles] = (uint16_t)total;
   __syncthreads();
 #pragma unroll
   for (uint32_t r = 0; r < PER; ++r) {
     const uint32_t i = r * kTileBlock + tid;
     if (i < m) {
-      const uint32_t p = l.hist[tl[r]] + rank[r];
-      l.key[p] = k[r];
+      uint32_t p = l.hist[tl[r]] + rank[r];
+      uint64_t key = k[r];
+      if (COPIES && copies >> r & 1u) {
+        p = total + __hip_atomic_fetch_add(&l.ncopy, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        key = rank[r];
+      }
+      l.key[p] = key;
       l.idx[p] = (uint16_t)i;
     }
   }
@@ -122,8 +165,25 @@ __device__ __forceinline__ void tile_partition_chunk(const TileJob& j, uint32_t 
     if (i < m) {
       j.skey[base + i] = l.key[i];
       j.sidx[base + i] = l.idx[i];
+      if (COPIES && i >= total) j.sflag[base + i] = (uint8_t)kTileCopy;
     }
   }
+  return true;
+}
+
+// A run far longer than its share comes from copies of a few keys, and would
+// make one block of the tile pass the time of the whole call: such a chunk is
+// sorted without its copies.  Each key writes its place in the chunk to an LDS
+// word that is its by hash, and the keys that read another place with their
+// own key there are copies: they go behind the runs, with the place of the key
+// they copy, and the finish pass gives them its answer (copies of one key, 16
+// bytes of table each: 2^20 in 731 us with every copy in its run and 33 so,
+// 2^24 in 16.7 and 0.36 ms).
+template <uint32_t C>
+__device__ __forceinline__ void tile_partition_chunk(const TileJob& j, uint32_t c, TilePartLds<C>& l) {
+  if (tile_sort_chunk<C, false>(j, c, l)) return;
+  __syncthreads();
+  tile_sort_chunk<C, true>(j, c, l);
 }
 
 // ---- tile ---------------------------------------------------------------------
@@ -255,6 +315,7 @@ struct TileFinishLds {
   uint32_t meet[kTileBlock / kWave][kMeetPlaces];
   uint32_t nmore;
   uint32_t nnew;
+  uint32_t ncopy;
 };
 
 // Finish chunk `c`: flags back into batch order, and the rest of the keys
@@ -274,12 +335,13 @@ __device__ __forceinline__ void tile_finish_chunk(const TileJob& j, uint32_t c, 
     x[r] = i < m ? j.sidx[base + i] : 0u;
     k[r] = i < m ? j.skey[base + i] : 0u;
   }
-  if (tid == 0) l.nmore = l.nnew = 0;
+  if (tid == 0) l.nmore = l.nnew = l.ncopy = 0;
   __syncthreads();
 #pragma unroll
   for (uint32_t r = 0; r < PER; ++r) {
     const bool in = r * kTileBlock + tid < m;
     const bool more = in && f[r] == kTileMore;
+    const bool copy = in && f[r] == kTileCopy;
     const uint64_t mm = ballot(more);
     uint32_t at = 0;
     if (mm && lane_id() == 0)
@@ -288,6 +350,8 @@ __device__ __forceinline__ void tile_finish_chunk(const TileJob& j, uint32_t c, 
     if (more) {
       l.mkey[at] = k[r];
       l.midx[at] = (uint16_t)x[r];
+    } else if (copy) {
+      l.ncopy = 1;
     } else if (in) {
       l.flag[x[r]] = (uint8_t)f[r];
     }
@@ -302,8 +366,16 @@ __device__ __forceinline__ void tile_finish_chunk(const TileJob& j, uint32_t c, 
     nnew += r == 1;
     l.flag[l.midx[e]] = (uint8_t)r;
   }
-  block_count(j.t.ctr->size, nnew, &l.nnew, c);      // a barrier: every flag is in place
+  block_count(j.t.ctr->size, nnew, &l.nnew, c);      // a barrier: every flag but the copies' is in place
   if (!j.out) return;
+  if (l.ncopy) {
+    // a copy: present, unless the key could not be kept in the table (read
+    // again, so that no register waits for this)
+    for (uint32_t i = tid; i < m; i += kTileBlock)
+      if (j.sflag[base + i] == kTileCopy)
+        l.flag[j.sidx[base + i]] = l.flag[(uint16_t)j.skey[base + i]] == 2 ? 2 : 0;
+    __syncthreads();
+  }
   uint8_t* out = j.out + base;
   uint32_t done = 0;
   if ((reinterpret_cast<uintptr_t>(out) & 3) == 0) {
