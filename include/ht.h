@@ -377,8 +377,10 @@ int ht_chain_histogram(ht_table* t, uint64_t* out, hipStream_t stream);
 
 /* Infrastructure.  Reserve scratch for batches up to max_batch keys
  * (allocates, synchronises the device).  A bucketed table of single-word keys
- * reserves the workspace of a large first batch (11 bytes a key) when there
- * is room. */
+ * reserves the workspace that any first batch of 2^18 to max_batch keys can
+ * need (up to 12 bytes a key) when there is room, and calls within the
+ * reservation allocate nothing: without the workspace they run the direct
+ * kernels.  ht_rebuild keeps the reservation. */
 int ht_reserve(ht_table* t, uint64_t max_batch);
 
 /* Infrastructure.  Human-readable text of a status code (a static string;

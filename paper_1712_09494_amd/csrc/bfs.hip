@@ -726,7 +726,7 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
         hipLaunchKernelGGL(bfs_write_kernel, dim3(gw), dim3(kBlock), 0, s, m, fr, nf, a, z, goff, bt);
         HT_HIP(hipGetLastError());
         HT_HIP(fop.mark(s));
-        rc = do_find_or_put(t, bt, n, fl, s, nullptr, true);
+        rc = do_find_or_put(t, bt, n, fl, s, FopMode{nullptr, true, true});
         if (rc) break;
         HT_HIP(fop.mark(s));
         const uint32_t gs = (uint32_t)std::min<uint64_t>((n + 4095) / 4096, grid);

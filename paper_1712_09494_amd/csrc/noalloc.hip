@@ -72,7 +72,7 @@ extern "C" int ht_find_or_put_noalloc(ht_table* t, const uint64_t* d_keys, uint6
   QuietLaunches quiet;
   // bucketed tables and the single-pass Cuckoo ablation use no scratch at all
   if (t->cfg.kind == HT_BUCKETED || (t->cfg.flags & HT_FLAG_CUCKOO_SINGLE_PASS))
-    return do_find_or_put(t, d_keys, n, d_out_is_new, s);
+    return do_find_or_put(t, d_keys, n, d_out_is_new, s, FopMode{nullptr, false, false});
   if ((uint64_t)max_blocks(t) * (kBlock / kWave) > 2 * kWcntWords)
     return fail(HT_EINVAL, "device has more wave slots than the static scratch counts");
   uint64_t* base = nullptr;
@@ -90,5 +90,5 @@ extern "C" int ht_find_or_put_noalloc(ht_table* t, const uint64_t* d_keys, uint6
   // fill kernel: no memset node when the caller captures a graph).  The lists
   // and counts are written before they are read.
   HT_HIP(fill_words(sc.dset, sc.dset_mask + 1, kEmpty, s));
-  return do_find_or_put(t, d_keys, n, d_out_is_new, s, &sc);
+  return do_find_or_put(t, d_keys, n, d_out_is_new, s, FopMode{&sc, false, false});
 }

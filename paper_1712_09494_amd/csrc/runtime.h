@@ -49,9 +49,11 @@ struct ht_table {
   uint32_t* dirty_cnt = nullptr;
   uint64_t* dirty_desc = nullptr;
   uint64_t dirty_stride = 0;
-  // workspace of the tiled find-or-put
+  // workspace of the tiled find-or-put, and the batch up to which calls find it
+  // as it is (one that could not be allocated for it stays away)
   void* tile_ws = nullptr;
   size_t tile_bytes = 0;
+  uint64_t tile_n = 0;
   uint64_t puts = 0;           // keys handed to find-or-put since the table was empty
   // scripted hashes
   ht::ScriptRow* script = nullptr;
@@ -79,11 +81,18 @@ int reserve_scratch(ht_table* t, uint64_t n);
 void free_explore(ht_table* t);
 ht::DevTable launch_view(const ht_table* t);
 ht::CuckooScratch scratch_view(const ht_table* t, uint64_t n);   // per_wave left for the caller
-// `fixed`: scratch provided by the caller (Cuckoo tables of single-word keys;
-// per_wave is set here), instead of the table's own.  `repeats`: most of the
-// keys are known to be stored already or repeated in the batch.
+struct FopMode {
+  // scratch provided by the caller (Cuckoo tables of single-word keys; per_wave
+  // is set here), instead of the table's own
+  const ht::CuckooScratch* fixed = nullptr;
+  // most of the keys are known to be stored already or repeated in the batch
+  bool repeats = false;
+  // the table's own scratch may be used, and grown for a batch beyond what was
+  // reserved; without it (and without `fixed`) only kernels that need none run
+  bool scratch = true;
+};
 int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t s,
-                   const ht::CuckooScratch* fixed = nullptr, bool repeats = false);
+                   const FopMode& mode = FopMode());
 uint64_t pow2_at_least(uint64_t x);
 extern thread_local bool g_quiet;   // set: launches create no timing events
 int do_query(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t s);

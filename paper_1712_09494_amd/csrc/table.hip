@@ -250,9 +250,6 @@ int clear_async(ht_table* t, hipStream_t s) {
 }
 
 int free_scratch(ht_table* t) {
-  if (t->tile_ws) (void)hipFree(t->tile_ws);
-  t->tile_ws = nullptr;
-  t->tile_bytes = 0;
   if (t->dset) (void)hipFree(t->dset);
   t->dset = nullptr;
   t->wkey = nullptr;
@@ -334,21 +331,34 @@ static bool tile_table(const ht_table* t) {
 // lines (2^20 keys, direct and tiled: 99 and 98 us at 9 bytes, 78 and 59 at
 // 10, 66 and 41 at 16, 59 and 38 at 32, 57 and 48 at 64; 16-slot buckets at 16
 // bytes 66 and 47).  At least 2^18 keys (2^18: 45 and 32 us at 16 bytes, 29
-// and 24 at 64; 2^17: 33 and 31, 21 and 20), with a tenth more room below
-// 2^20 (2^18 at 9 bytes: 77 and 106 us, the keys of full buckets), at most
-// 2^25 (369 MB of workspace) and kTileMax tiles.  The gain is in
-// the compare-and-swaps of new keys: a batch of keys already stored takes 27
+// and 24 at 64; 2^17: 33 and 31, 21 and 20), with a fifth more room below
+// 2^20 (2^18 at 9 bytes: 77 and 106 us, the keys of full buckets), and at most
+// kTileMax tiles (2^25 slots, so that at most 29.8 M keys come this way, with
+// 360 MB of workspace).  The gain is in the compare-and-swaps of new keys: a batch of keys already stored takes 27
 // us direct and 39 tiled (2^20 keys at 16 bytes), so the batch has to be
 // larger than all that was put before it since the table was empty.  A batch
 // of few different keys is mostly such keys, but the room that the rule asks
 // for is only there when the table was made a hundred times too large for them
 // (10,000 different keys, 8-slot buckets: 2^20 keys 23 and 35 us, 2^22 49 and
 // 87; 64-slot buckets 73 and 36, 255 and 90).
-static bool tile_rule(const ht_table* t, uint64_t n) {
-  if (!tile_table(t) || n < (1ull << 18) || n > (1ull << 25) || t->puts >= n) return false;
+static bool tile_fits(const ht_table* t, uint64_t n) {
   const uint64_t bytes = t->nslots * 8;
-  return bytes >= (n < (1ull << 20) ? 11 * n : 9 * n) && bytes <= 64 * n &&
+  return tile_table(t) && n >= (1ull << 18) && bytes / (n < (1ull << 20) ? 11 : 9) >= n && bytes / 64 <= n &&
          t->nslots <= (uint64_t)kTileMax * kTileSlots;
+}
+
+static bool tile_rule(const ht_table* t, uint64_t n) { return tile_fits(t, n) && t->puts < n; }
+
+// The most workspace that a call of at most n keys can need: of the largest
+// batch that fits, or of the largest one in the smaller chunks, which has more
+// run starts (2^22 slots: 2^21 keys 23.3 MB, one key less 23.6 MB).
+static size_t tile_most(const ht_table* t, uint64_t n) {
+  const uint64_t room = t->nslots * 8;
+  uint64_t m = std::min(n, room / 9);
+  if (m < (1ull << 20)) m = std::min(m, room / 11);
+  if (!tile_fits(t, m)) return 0;
+  const size_t least = tile_shape(t->nslots, std::min(m, kTileLongChunks - 1)).bytes;
+  return std::max(least, tile_shape(t->nslots, m).bytes);
 }
 
 // Whether a table of a many-table plan is filled by the tiled passes: their
@@ -356,8 +366,7 @@ static bool tile_rule(const ht_table* t, uint64_t n) {
 // table has room for it and is not large against it.
 static bool plan_tile_rule(const ht_table* t, uint64_t n) {
   const uint64_t bytes = t->nslots * 8;
-  return tile_table(t) && n >= 64 && n <= (1ull << 25) && bytes >= 9 * n && bytes <= 64 * n &&
-         t->nslots <= (uint64_t)kTileMax * kTileSlots;
+  return tile_table(t) && n >= 64 && bytes / 9 >= n && bytes / 64 <= n && t->nslots <= (uint64_t)kTileMax * kTileSlots;
 }
 
 // Whether a find-or-put probes with one lane per key instead of the lane
@@ -406,25 +415,42 @@ static bool cuckoo_whole_rule(const ht_table* t, uint64_t n) {
   return n <= 4096 || (n <= 8192 && t->puts < n);
 }
 
-// Workspace of the tiled passes; false (the direct kernels serve the call)
-// when it cannot be allocated or the stream is being captured.
-static bool tile_workspace(ht_table* t, size_t bytes, hipStream_t s) {
+static bool capturing(hipStream_t s) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return false;
-  }
-  if (bytes <= t->tile_bytes) return true;
+  if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) return false;
+  (void)hipGetLastError();
+  return true;
+}
+
+static void free_tile(ht_table* t) {
   if (t->tile_ws) (void)hipFree(t->tile_ws);     // waits for the work that uses it
   t->tile_ws = nullptr;
   t->tile_bytes = 0;
+}
+
+// Workspace of the tiled passes for calls of up to n keys, where there is
+// room: without it the direct kernels serve them.
+static void reserve_tile(ht_table* t, uint64_t n) {
+  t->tile_n = std::max(t->tile_n, n);
+  const size_t bytes = tile_most(t, t->tile_n);
+  if (bytes <= t->tile_bytes) return;
+  free_tile(t);
   if (hipMalloc(&t->tile_ws, bytes) != hipSuccess) {
     (void)hipGetLastError();
     t->tile_ws = nullptr;
-    return false;
+    return;
   }
   t->tile_bytes = bytes;
-  return true;
+}
+
+// Whether the workspace serves a call of n keys that needs `bytes` of it.  A
+// batch beyond what was reserved grows it; nothing is allocated under capture,
+// and a captured call takes the direct kernels, whose replays do not depend on
+// a workspace that later calls may move.
+static bool tile_ready(ht_table* t, uint64_t n, size_t bytes, hipStream_t s) {
+  if (capturing(s)) return false;
+  if (n > t->tile_n) reserve_tile(t, n);
+  return bytes <= t->tile_bytes;
 }
 
 int validate_config(const ht_config* c) {
@@ -618,16 +644,16 @@ static int tiled_find_or_put(ht_table* t, const DevTable& d, const uint64_t* key
 }
 
 int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t s,
-                   const CuckooScratch* fixed, bool repeats) {
+                   const FopMode& mode) {
   if (t->cfg.key_words > 1) {
-    if (fixed) return fail(HT_EINVAL, "state-vector tables take no caller scratch");
+    if (mode.fixed) return fail(HT_EINVAL, "state-vector tables take no caller scratch");
     return vec_find_or_put(t, keys, n, out, s);
   }
   const DevTable d = launch_view(t);
   const bool scripted = is_scripted(t);
   const uint32_t R = t->cfg.keys_per_group;
   const bool whole = tile_whole_rule(t, n), cwhole = cuckoo_whole_rule(t, n);
-  const bool tiled = !repeats && !g_quiet && tile_rule(t, n);
+  const bool tiled = !mode.repeats && mode.scratch && tile_rule(t, n);
   t->puts += n;
   if (whole) {
     KernelTimer kt("tile_whole", s);
@@ -636,10 +662,10 @@ int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, 
   }
   if (tiled) {
     const TileShape sh = tile_shape(t->nslots, n);
-    if (tile_workspace(t, sh.bytes, s)) return tiled_find_or_put(t, d, keys, n, out, sh, s);
+    if (tile_ready(t, n, sh.bytes, s)) return tiled_find_or_put(t, d, keys, n, out, sh, s);
   }
   const bool one_lane = (t->cfg.flags & HT_FLAG_BUCKETED_ONE_LANE) != 0;
-  if (t->cfg.kind == HT_BUCKETED && (one_lane || lane_rule(t, n, repeats))) {
+  if (t->cfg.kind == HT_BUCKETED && (one_lane || lane_rule(t, n, mode.repeats))) {
     const uint64_t blocks = std::min<uint64_t>((n + kBlock - 1) / kBlock, atomic_grid_blocks(t));
     KernelTimer kt(one_lane ? "bucketed_lane_fop" : "bucketed_fop", s, one_lane ? nullptr : "lanes");
     HT_HIP(bucketed_lane_find_or_put(d, keys, n, out, (uint32_t)blocks, scripted, s));
@@ -666,8 +692,8 @@ int do_find_or_put(ht_table* t, const uint64_t* keys, uint64_t n, uint8_t* out, 
     return HT_OK;
   }
   CuckooScratch sc{};
-  if (fixed) {
-    sc = *fixed;                  // scratch the caller provides (the allocation-free call)
+  if (mode.fixed) {
+    sc = *mode.fixed;             // scratch the caller provides (the allocation-free call)
   } else {
     int rc = reserve_scratch(t, n);
     if (rc != HT_OK) return rc;
@@ -820,6 +846,7 @@ int ht_create(const ht_config* cfg, ht_table** out) {
     if (e != hipSuccess) rc = hip_fail(e, "hipDeviceSynchronize");
   }
   if (rc) {
+    free_tile(t);
     free_scratch(t);
     free_storage(t);
     delete t;
@@ -840,6 +867,7 @@ int ht_create_simple(uint32_t kind, uint64_t capacity, uint32_t nhash, ht_table*
 int ht_destroy(ht_table* t) {
   if (!t) return fail(HT_EINVAL, "table is NULL");
   (void)hipDeviceSynchronize();
+  free_tile(t);
   free_scratch(t);
   free_explore(t);
   free_storage(t);
@@ -1157,7 +1185,7 @@ int ht_rebuild(ht_table* t, uint64_t new_capacity, hipStream_t s) {
   // The old storage stays untouched until the members are all placed in the
   // new one: allocate first, and on any failure put the old table back.
   const ht_config old_cfg = t->cfg, old_user = t->user_cfg;
-  const uint64_t old_nslots = t->nslots;
+  const uint64_t old_nslots = t->nslots, reserved = t->tile_n;
   const DevTable old_dev = t->dev;
   void* const old_storage = t->storage;
   unsigned long long* const old_misc = t->misc;
@@ -1196,13 +1224,13 @@ int ht_rebuild(ht_table* t, uint64_t new_capacity, hipStream_t s) {
   }
   (void)hipStreamSynchronize(s);
   (void)hipFree(buf);
-  if (rc) {
-    (void)hipFree(t->storage);
-    restore();
-    return rc;
-  }
-  (void)hipFree(old_storage);
-  return HT_OK;
+  (void)hipFree(rc ? t->storage : old_storage);
+  if (rc) restore();
+  // the reservation, for the table's present size, and no more than it
+  if (t->tile_n > reserved) free_tile(t);
+  t->tile_n = reserved;
+  reserve_tile(t, reserved);
+  return rc;
 }
 
 int ht_stats(ht_table* t, ht_stats_t* out, hipStream_t s) {
@@ -1284,9 +1312,8 @@ int ht_chain_histogram(ht_table* t, uint64_t* out, hipStream_t s) {
 int ht_reserve(ht_table* t, uint64_t max_batch) {
   int rc = check_table(t);
   if (rc) return rc;
-  // the tiled passes' workspace, if such a batch would use it (a call without
-  // it allocates it, or runs the direct kernels)
-  if (tile_rule(t, max_batch)) (void)tile_workspace(t, tile_shape(t->nslots, max_batch).bytes, nullptr);
+  // the tiled passes' workspace (under capture such calls run the direct kernels)
+  if (!capturing(nullptr)) reserve_tile(t, max_batch);
   return reserve_scratch(t, max_batch);
 }
 

@@ -39,6 +39,8 @@ struct TileShape {
   size_t bytes;
 };
 
+constexpr uint64_t kTileLongChunks = 1ull << 21;   // chunks of 8192 keys from so many keys on
+
 // `min_tiles`: tiles are made smaller (to 2048 slots) while there are fewer;
 // `chunk`: 4096 or 8192 keys, 0 to choose by n.
 TileShape tile_shape(uint64_t nslots, uint64_t n, uint32_t min_tiles = 512, uint32_t chunk = 0);

@@ -80,7 +80,7 @@ TileShape tile_shape(uint64_t nslots, uint64_t n, uint32_t min_tiles, uint32_t c
   s.shift = 13;
   while (s.shift > 11 && (nslots >> s.shift) < min_tiles) --s.shift;
   s.tiles = (uint32_t)((nslots + (1ull << s.shift) - 1) >> s.shift);
-  s.chunk = chunk ? chunk : n >= (1ull << 21) ? 8192 : 4096;
+  s.chunk = chunk ? chunk : n >= kTileLongChunks ? 8192 : 4096;
   s.chunks = (uint32_t)((n + s.chunk - 1) / s.chunk);
   const uint64_t len = s.chunk / (s.tiles ? s.tiles : 1);
   s.run_lanes = 1;
