@@ -419,7 +419,8 @@ int ht_server_run(ht_server* s, ht_request* reqs, uint32_t nreq, ht_server_stats
           // vector tables: their own kernels (the many-table launches take single-word keys)
           err = r.op == HT_OP_FIND_OR_PUT ? do_find_or_put(tb, dk, r.n, dflag, st) : do_query(tb, dk, r.n, dflag, st);
         } else if (r.op == HT_OP_FIND_OR_PUT && tb->cfg.kind == HT_BUCKETED && s->cfg.merge > 1) {
-          specs.push_back(MultiSpec{launch_view(tb), dk, dflag, r.n});
+          specs.push_back(MultiSpec{launch_view(tb), dk, dflag, r.n, false});
+          tb->puts += r.n;
         } else if (r.op == HT_OP_FIND_OR_PUT && s->cfg.merge > 1) {
           MultiCuckooSpec cs{};
           cs.t = launch_view(tb);
@@ -430,6 +431,7 @@ int ht_server_run(ht_server* s, ht_request* reqs, uint32_t nreq, ht_server_stats
           cs.max_regions = (uint64_t)max_blocks(tb) * (kBlock / kWave);
           cs.paper = (tb->cfg.flags & HT_FLAG_CUCKOO_PAPER_ORDER) != 0;
           cspecs.push_back(cs);
+          tb->puts += r.n;
         } else if (r.op == HT_OP_FIND_OR_PUT) {
           err = do_find_or_put(tb, dk, r.n, dflag, st);
         } else {
