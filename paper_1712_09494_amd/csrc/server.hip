@@ -253,10 +253,11 @@ int ht_server_run(ht_server* s, ht_request* reqs, uint32_t nreq, ht_server_stats
     sl.offs.clear();
     sl.busy = false;
   }
-  // everything that allocates happens before the clock starts
+  // everything that allocates happens before the clock starts (requests that
+  // share many-table launches take no workspace of a bucketed table)
   for (uint32_t t = 0; t < nt; ++t)
-    if ((s->tables[t]->cfg.kind == HT_CUCKOO || s->tables[t]->cfg.key_words > 1) && need[t]) {
-      int rc = reserve_scratch(s->tables[t], need[t]);
+    if (need[t]) {
+      int rc = s->cfg.merge > 1 ? reserve_scratch(s->tables[t], need[t]) : ht_reserve(s->tables[t], need[t]);
       if (rc) return rc;
     }
   const uint32_t cap_items = (uint32_t)(s->cfg.merge * multi_items_for(std::max<uint64_t>(max_n, 1)));

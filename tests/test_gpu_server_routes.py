@@ -36,3 +36,25 @@ def test_merged_requests_count_as_puts():
         assert name in r and not {"tile_insert", "tile_whole", "cuckoo_whole"} & set(r), r
         assert t.size() == k.size
         t.close()
+
+
+def test_a_run_reserves_what_unmerged_requests_need():
+    n = 1 << 19
+    first, keys = inputs.uniform_keys(n, seed=1), inputs.uniform_keys(n, seed=1, start=n)
+    k, out = dev(keys), torch.empty(n, dtype=torch.uint8, device="cuda")
+    with b.Table("bucketed", capacity=3 * n, nhash=3, bucket_slots=8) as t:
+        srv = b.Server([t], merge=1)
+        o = srv.run([("put", 0, pinned(first[:1000]), 0.0), ("put", 0, pinned(first[:900]), 0.0)])[0]
+        assert o[0].all() and not o[1].any()
+        # the table holds as much as this request brings: direct kernels, and the workspace is there all the same
+        t.find_or_put(dev(first))
+        b.ht_timing_enable(True)
+        o = srv.run([("put", 0, pinned(keys), 0.0)])[0]
+        names = set(b.ht_timing_report())
+        b.ht_timing_enable(False)
+        assert "tile_insert" not in names and o[0].all()
+        srv.close()
+        t.clear()
+        before = free_bytes()
+        assert "tile_insert" in routes(lambda: t.find_or_put(k, out))
+        assert free_bytes() == before and t.size() == n
