@@ -30,7 +30,7 @@
  *     on one stream (or synchronised by the caller); different tables are
  *     independent;
  *   - the table owns only its own device storage (slots, stash, overflow list,
- *     counters and scratch);
+ *     counters, scratch, and the buffers it keeps of its last exploration);
  *   - n == 0 is a no-op returning HT_OK; a NULL pointer with n > 0 returns
  *     HT_EINVAL; nothing is launched when an argument is rejected;
  *   - a call never waits for the device unless it says "synchronises".
@@ -414,7 +414,9 @@ typedef struct {
  * batch, and the states reported new become the next frontier, in batch
  * order.  Host arrays (may be NULL, else `levels` entries): batch_sizes[L]
  * successors generated, new_counts[L] states new at level L, fop_ms[L] the
- * find-or-put time (HIP events).  Allocates its buffers; synchronises. */
+ * find-or-put time (HIP events).  Allocates its buffers, of which up to 1 GiB
+ * stay with the table for its next exploration (until ht_rebuild, ht_destroy,
+ * or an allocation for the table that finds no other room); synchronises. */
 int ht_bfs_explore(ht_table* t, const ht_bfs_model* model, uint64_t initial, uint32_t levels,
                    uint64_t* batch_sizes, uint64_t* new_counts, double* fop_ms, hipStream_t stream);
 

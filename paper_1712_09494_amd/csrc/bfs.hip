@@ -37,6 +37,7 @@
 // never stored: a level moves the frontier, the masks and the new states.
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <vector>
 
 #include "bucketed_dev.h"
@@ -494,15 +495,19 @@ struct Buf {
     bytes = need;
     return HT_OK;
   }
-  ~Buf() {
+  void drop() {
     if (p) (void)hipFree(p);
+    p = nullptr;
+    bytes = 0;
   }
+  ~Buf() { drop(); }
 };
 
 }  // namespace
 
 // Buffers of an exploration, kept with the table for its next one while they
-// are small (kKeepBytes) and given back with it.
+// are small (kKeepBytes); given back with it, by a rebuild, and when an
+// allocation for the table finds no room.
 struct ht_explore_ws {
   int device = 0;
   Buf frontier, next, batch, flags, gcounts, goffsets, gnews, tmp, nsel, masks, lists, slices;
@@ -525,22 +530,25 @@ namespace {
 constexpr size_t kKeepBytes = 1ull << 30;
 
 // The table's exploration buffers for one call: those it kept, if they lie on
-// the current device, else new ones.  Afterwards they stay with the table
-// when they are small and the call went well.
+// the current device, else new ones.  The call takes them from the table, and
+// they go back to it afterwards when they are small and the call went well.
 struct ExploreHold {
   ht_table* t;
+  std::unique_ptr<ht_explore_ws> ws;
   bool keep = false;
-  explicit ExploreHold(ht_table* table) : t(table) {
+  explicit ExploreHold(ht_table* table) : t(table), ws(table->explore) {
+    t->explore = nullptr;
     int dev = 0;
     (void)hipGetDevice(&dev);
-    if (t->explore && t->explore->device != dev) free_explore(t);
-    if (!t->explore) {
-      t->explore = new ht_explore_ws();
-      t->explore->device = dev;
-    }
+    if (ws && ws->device == dev) return;
+    ws.reset();
+    ws.reset(new ht_explore_ws());
+    ws->device = dev;
   }
   ~ExploreHold() {
-    if (!keep || t->explore->bytes() > kKeepBytes) free_explore(t);
+    if (!keep || ws->bytes() > kKeepBytes) return;
+    free_explore(t);
+    t->explore = ws.release();
   }
 };
 
@@ -608,7 +616,7 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
     for (int q = 0; q < 16; ++q)
       if (m.lcnt[p][q] > 4) return fail(HT_EINVAL, "more than 4 local transitions");
   ExploreHold hold(t);
-  ht_explore_ws& ws = *t->explore;
+  ht_explore_ws& ws = *hold.ws;
   Buf &frontier = ws.frontier, &next = ws.next, &batch = ws.batch, &flags = ws.flags, &gcounts = ws.gcounts,
       &goffsets = ws.goffsets, &gnews = ws.gnews, &tmp = ws.tmp, &nsel = ws.nsel, &masks = ws.masks, &lists = ws.lists,
       &slices = ws.slices;

@@ -208,6 +208,24 @@ int free_storage(ht_table* t) {
   return HT_OK;
 }
 
+static void free_tile(ht_table* t) {
+  if (t->tile_ws) (void)hipFree(t->tile_ws);     // waits for the work that uses it
+  t->tile_ws = nullptr;
+  t->tile_bytes = 0;
+}
+
+// Device memory that the table cannot do without: where there is no room, what
+// it keeps for speed alone (exploration buffers, the tiled passes' workspace)
+// makes some.
+static hipError_t table_malloc(ht_table* t, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess || !(t->explore || t->tile_ws)) return e;
+  (void)hipGetLastError();
+  free_explore(t);
+  free_tile(t);
+  return hipMalloc(p, bytes);
+}
+
 // Allocate slots/stash/overflow/counters for t->nslots and clear them.
 int alloc_storage(ht_table* t) {
   const size_t slot_bytes = align_up(t->nslots * 8, 256);
@@ -222,7 +240,7 @@ int alloc_storage(ht_table* t) {
   const size_t arena_bytes = align_up(t->dev.arena_cap * kSpread * W * 8, 256);
   const size_t total = slot_bytes + stash_bytes + ovf_bytes + ctr_bytes + misc_bytes + arena_bytes;
   void* p = nullptr;
-  hipError_t e = hipMalloc(&p, total);
+  hipError_t e = table_malloc(t, &p, total);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(HT_ENOMEM, std::string("hipMalloc of table storage failed: ") + hipGetErrorString(e));
@@ -289,7 +307,7 @@ int reserve_scratch(ht_table* t, uint64_t n) {
   const size_t b_rec = align_up(nw * stride * 8, 256);
   const size_t b_defer = defer ? b_dset + b_rec + b_c + 256 : 0;
   void* p = nullptr;
-  hipError_t e = hipMalloc(&p, b_dset + 2 * b_k + b_c + b_defer);
+  hipError_t e = table_malloc(t, &p, b_dset + 2 * b_k + b_c + b_defer);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(HT_ENOMEM, std::string("hipMalloc of find-or-put scratch failed: ") + hipGetErrorString(e));
@@ -420,12 +438,6 @@ static bool capturing(hipStream_t s) {
   if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) return false;
   (void)hipGetLastError();
   return true;
-}
-
-static void free_tile(ht_table* t) {
-  if (t->tile_ws) (void)hipFree(t->tile_ws);     // waits for the work that uses it
-  t->tile_ws = nullptr;
-  t->tile_bytes = 0;
 }
 
 // Workspace of the tiled passes for calls of up to n keys, where there is
@@ -785,7 +797,7 @@ int dump_members(ht_table* t, uint64_t** d_buf, uint64_t* count, hipStream_t s) 
   if (rc) return rc;
   const uint64_t upper = spread_sum(h.size) + ovf.size() + 1;
   uint64_t* buf = nullptr;
-  hipError_t e = hipMalloc(&buf, std::max<uint64_t>(upper, 1) * 8 * t->cfg.key_words);
+  hipError_t e = table_malloc(t, reinterpret_cast<void**>(&buf), std::max<uint64_t>(upper, 1) * 8 * t->cfg.key_words);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(HT_ENOMEM, "hipMalloc of dump buffer failed");
@@ -1176,6 +1188,7 @@ int ht_rebuild(ht_table* t, uint64_t new_capacity, hipStream_t s) {
   if (t->cfg.key_words > 1 && new_capacity &&
       new_capacity + t->dev.stash_slots + t->dev.overflow_slots + 64 >= (1ull << (kArenaBits - 1)))
     return fail(HT_EINVAL, "vector table capacity above 2^33 entries");
+  free_explore(t);     // room for the old and the new storage
   // every member (slots, stash, overflow list, the all-ones key) to a device buffer
   uint64_t* buf = nullptr;
   uint64_t n = 0;
