@@ -470,28 +470,25 @@ struct Buf {
   void* p = nullptr;
   size_t bytes = 0;
   // Room for `need` bytes; the first `keep` bytes of the old contents stay
-  // (copied on stream s, which is waited for).
+  // (copied on stream s, which is waited for), also when there is no room.
   int ensure(size_t need, size_t keep = 0, hipStream_t s = nullptr) {
     if (need <= bytes) return HT_OK;
-    void* old = p;
-    if (!keep) {
-      if (old) (void)hipFree(old);
-      old = nullptr;
-    }
-    p = nullptr;
-    bytes = 0;
-    hipError_t e = hipMalloc(&p, need);
-    if (e == hipSuccess && old) {
-      e = hipMemcpyAsync(p, old, keep, hipMemcpyDeviceToDevice, s);
-      if (e == hipSuccess) e = hipStreamSynchronize(s);
-    }
-    if (old) (void)hipFree(old);
-    if (e != hipSuccess) {
+    if (!keep) drop();
+    void* q = nullptr;
+    if (hipMalloc(&q, need) != hipSuccess) {
       (void)hipGetLastError();
-      if (p) (void)hipFree(p);
-      p = nullptr;
       return fail(HT_ENOMEM, "hipMalloc in breadth-first exploration failed");
     }
+    if (keep) {
+      hipError_t e = hipMemcpyAsync(q, p, keep, hipMemcpyDeviceToDevice, s);
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+      if (e != hipSuccess) {
+        (void)hipFree(q);
+        return hip_fail(e, "copy of an exploration buffer");
+      }
+    }
+    drop();
+    p = q;
     bytes = need;
     return HT_OK;
   }
@@ -746,9 +743,11 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
           HT_HIP(hipMemcpyAsync(&got, ns + q, 8, hipMemcpyDeviceToHost, s));
           HT_HIP(hipStreamSynchronize(s));
           if ((nnew + got) * 8 > next.bytes) {
-            // what the slices so far give for the whole level, and a tenth more
+            // what the slices so far give for the whole level, and a tenth
+            // more; where there is no room for that, what there is
             const uint64_t guess = (uint64_t)((double)(nnew + got) / (double)(q + 1) * (double)nslices * 1.1);
-            rc = next.ensure(std::max<uint64_t>(guess, std::max<uint64_t>(nnew + got, 1)) * 8, nnew * 8, s);
+            rc = next.ensure(std::max<uint64_t>(guess, nnew + got) * 8, nnew * 8, s);
+            if (rc == HT_ENOMEM) rc = next.ensure((nnew + got) * 8, nnew * 8, s);
             if (rc) break;
           }
           HT_HIP(all.mark(s));
