@@ -38,6 +38,7 @@
 #include <algorithm>
 #include <cstring>
 #include <memory>
+#include <new>
 #include <vector>
 
 #include "bucketed_dev.h"
@@ -557,10 +558,12 @@ struct Spans {
   size_t used = 0;
   hipError_t mark(hipStream_t s) {
     if (used == ev.size()) {
-      hipEvent_t e = nullptr;
-      const hipError_t rc = hipEventCreate(&e);
-      if (rc != hipSuccess) return rc;
-      ev.push_back(e);
+      ev.push_back(nullptr);
+      const hipError_t rc = hipEventCreate(&ev.back());
+      if (rc != hipSuccess) {
+        ev.pop_back();
+        return rc;
+      }
     }
     return hipEventRecord(ev[used++], s);
   }
@@ -593,9 +596,8 @@ constexpr uint64_t kCuckooTurns = 4;
 
 }  // namespace
 
-extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_t initial, uint32_t levels,
-                                 uint32_t mode, uint64_t* batch_sizes, uint64_t* new_counts, double* fop_ms,
-                                 double* level_ms, hipStream_t s) {
+static int explore(ht_table* t, const ht_bfs_model* model, uint64_t initial, uint32_t levels, uint32_t mode,
+                   uint64_t* batch_sizes, uint64_t* new_counts, double* fop_ms, double* level_ms, hipStream_t s) {
   int rc = check_table(t);
   if (rc) return rc;
   if (!model) return fail(HT_EINVAL, "model is NULL");
@@ -795,6 +797,16 @@ extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_
   const hipError_t end = hipStreamSynchronize(s);
   hold.keep = rc == HT_OK && end == hipSuccess;
   return rc;
+}
+
+extern "C" int ht_bfs_explore_ex(ht_table* t, const ht_bfs_model* model, uint64_t initial, uint32_t levels,
+                                 uint32_t mode, uint64_t* batch_sizes, uint64_t* new_counts, double* fop_ms,
+                                 double* level_ms, hipStream_t s) {
+  try {
+    return explore(t, model, initial, levels, mode, batch_sizes, new_counts, fop_ms, level_ms, s);
+  } catch (const std::bad_alloc&) {
+    return fail(HT_ENOMEM, "host memory for the breadth-first exploration");
+  }
 }
 
 extern "C" int ht_bfs_explore(ht_table* t, const ht_bfs_model* model, uint64_t initial, uint32_t levels,
