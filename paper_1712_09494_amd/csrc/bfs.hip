@@ -104,17 +104,6 @@ __device__ __forceinline__ uint32_t successor_count(const BfsModelDev& m, const 
   return c;
 }
 
-// Inclusive prefix sum of `v` over the wave.
-__device__ __forceinline__ uint32_t wave_inclusive32(uint32_t v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint32_t o = shfl32(v, lane >= off ? lane - off : lane);
-    if (lane >= off) v += o;
-  }
-  return v;
-}
-
 // Successors of each group of 64 frontier states.
 __global__ __launch_bounds__(kBlock) void bfs_count_kernel(BfsModelDev m, const uint64_t* __restrict__ f, uint64_t nf,
                                                            unsigned long long* __restrict__ gcnt) {

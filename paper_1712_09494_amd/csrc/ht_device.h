@@ -307,6 +307,17 @@ __device__ __forceinline__ void wave_count(unsigned long long* spread, unsigned 
   if (lane_id() == 0 && s) add_agent(&spread[(salt % kSpread) * kLineWords], s);
 }
 
+// Inclusive prefix sum of `v` over the wave.
+__device__ __forceinline__ uint32_t wave_inclusive32(uint32_t v) {
+  const int lane = lane_id();
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint32_t o = shfl32(v, lane >= off ? lane - off : lane);
+    if (lane >= off) v += o;
+  }
+  return v;
+}
+
 // Copies of one key in a wave.  Each active lane leaves its number and 26 bits
 // of its key's hash at one of the wave's kMeetPlaces words in LDS and reads the
 // word back: the lane named there (`lead`) stands for every lane with its key,

@@ -41,17 +41,6 @@ __device__ __forceinline__ uint64_t tile_home(const DevTable& t, uint64_t k) {
   return hidx<false>(t, k, 0) * t.bucket_slots;
 }
 
-// Inclusive prefix sum of `v` over the wave.
-__device__ __forceinline__ uint32_t tile_wave_inclusive(uint32_t v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint32_t o = shfl32(v, lane >= off ? lane - off : lane);
-    if (lane >= off) v += o;
-  }
-  return v;
-}
-
 // ---- partition ---------------------------------------------------------------
 
 template <uint32_t C>
@@ -124,7 +113,7 @@ __device__ __forceinline__ bool tile_sort_chunk(const TileJob& j, uint32_t c, Ti
     mine += v;
     most = v > most ? v : most;
   }
-  const uint32_t incl = tile_wave_inclusive(mine);
+  const uint32_t incl = wave_inclusive32(mine);
   if (lane_id() == kWave - 1) l.wsum[tid / kWave] = incl;
   if (!COPIES && most > j.run_most) l.crowded = 1;
   __syncthreads();
