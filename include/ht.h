@@ -107,11 +107,13 @@ enum {
   HT_FLAG_CUCKOO_SINGLE_PASS = 1u << 4,
   /* Bucketed, single-word keys: probe with one lane per key (each lane reads
    * its buckets eight slots at a time and compare-and-swaps the first empty
-   * slot) in every call.  Without the flag a find-or-put takes the faster of
-   * this and a group of B/4 lanes sharing each bucket (Sec. 4.2); a nonzero
-   * keys_per_group or HT_FLAG_BUCKETED_ATOMIC_LOADS asks for the groups.
-   * Same table, probe sequence and results; a wave serves 64 keys per turn
-   * instead of 256/B.  The many-table launch always probes this way. */
+   * slot) in every call.  Without the flag a find-or-put takes what is the
+   * faster for its batch: this, a group of B/4 lanes sharing each bucket
+   * (Sec. 4.2), or for a table's first batch passes that insert in LDS; a
+   * nonzero keys_per_group or HT_FLAG_BUCKETED_ATOMIC_LOADS asks for the
+   * groups.  Same table, probe sequence and results; a wave serves 64 keys per
+   * turn instead of 256/B.  The persistent kernel of the many-table launches
+   * always probes this way. */
   HT_FLAG_BUCKETED_ONE_LANE = 1u << 5,
   /* Measurement: record each Cuckoo eviction chain's number of exchanges in
    * a histogram read by ht_chain_histogram (one extra atomic per chain). */
@@ -141,7 +143,8 @@ typedef struct {
                               line of 64-bit keys).  Ignored by cuckoo */
   uint32_t keys_per_group; /* keys each lane group (bucketed) or lane (cuckoo)
                               keeps in flight: 1, 2 or 4; 0 = 1, and bucketed
-                              find-or-puts may probe with one lane per key.
+                              find-or-puts need not run lane groups (a nonzero
+                              value asks for them in every call).
                               Bucketed lane-group queries use at least 2 */
   uint32_t stash_slots;    /* stash size (power of two, <= 65536); 0 = 1024 */
   uint32_t max_chain;      /* cuckoo eviction bound; 0 = 8 * ceil(log2 capacity) */
@@ -280,14 +283,18 @@ typedef struct ht_multi_plan ht_multi_plan;
  * many times.  Prepare a many-table find-or-put: validates the arguments (as
  * ht_find_or_put_multi), reserves each Cuckoo and state-vector table's
  * scratch for its batch, and copies the tables' descriptors and work-item
- * lists to the device (allocates, synchronises).  The key and flag buffers
- * must stay valid for every launch of the plan. */
+ * lists to the device (allocates, synchronises).  For bucketed tables with
+ * 9 to 64 bytes of slots per key it holds a workspace of up to 12 bytes a key
+ * until it is destroyed (where there is no room, launches do without).  The
+ * key and flag buffers must stay valid for every launch of the plan. */
 int ht_multi_plan_create(ht_table* const* t, const uint64_t* const* d_keys,
                          const uint64_t* n, uint8_t* const* d_out_is_new,
                          uint32_t ntables, ht_multi_plan** out);
 
 /* The find-or-put of Sec. 5 (Sec. 4.1 and 4.2 insertion) of every table of
- * the plan.  Run the plan on `stream`: one persistent kernel for the bucketed tables,
+ * the plan.  Run the plan on `stream`: one persistent kernel for the bucketed
+ * tables (or, while the tables that the workspace serves hold less than the
+ * launch brings, one for the others and three passes that insert in LDS),
  * then three phase kernels covering every Cuckoo table, then each
  * state-vector table's own kernels.
  * Allocates nothing, uses no memset and does not synchronise, so it may be

@@ -70,7 +70,7 @@ hipError_t bucketed_query(const DevTable& t, const uint64_t* keys, uint64_t n, u
 #undef HT_QRY
 }
 
-// One lane per key (HT_FLAG_BUCKETED_ONE_LANE).
+// One lane per key.
 hipError_t bucketed_lane_find_or_put(const DevTable& t, const uint64_t* keys, uint64_t n, uint8_t* out,
                                      uint32_t grid, bool scripted, hipStream_t s) {
   const uint32_t lds = lds_left(t, sizeof(MeetLds));

@@ -1,7 +1,7 @@
 // Bucketed (GPUexplore-style) table: find-or-put and query kernels, by lane
-// groups as the paper has it and, further down, by one lane per key, which is
-// what a table runs unless its batch or its flags are better served by groups
-// (lane_rule in table.hip).
+// groups as the paper has it and, further down, by one lane per key, which
+// serves queries, large batches into roomy tables (lane_rule in table.hip) and
+// the many-table launches.
 //
 // Paper Sec. 4.2 / Fig. 4: a key is hashed with h_1 to a bucket; the whole
 // bucket is read cooperatively, one slot share per lane; the lanes vote

@@ -17,7 +17,9 @@
 // 6.77 ms).  Tables may
 // mix bucket widths and hash counts; each uses its own storage, so the
 // results equal one find-or-put call per table.  The launch allocates nothing and uses no
-// memset, so it can be captured in a HIP graph.
+// memset, so it can be captured in a HIP graph.  A plan has a second way to fill
+// the tables that its batches are large against (build_tiled): the passes of
+// tile_dev.h over all of them, and the persistent launch for the others.
 //
 // The Cuckoo tables of a many-table call run their three phases (probe and
 // place, evict, scrub) as three launches over all of them: the phases need a

@@ -5,12 +5,12 @@ throughput over a grid of bucket widths B (bucketed: 8/16/32/64) and hash
 counts c (2..4, both designs), on a seeded random workload of the table's
 shape, and keeps the fastest configuration that stores every key without
 overflow.  Candidates are timed in the launch the many-table fill uses (a
-plan over the one table: the persistent kernel for bucketed tables, the
-three phase kernels for Cuckoo tables), so the choice is made on the kernel
-that runs it.  That launch probes with one lane per key and sizes its work
-items for the whole grid, so it has no keys-per-wave parameter: the
-keys-per-group axis (R = 1/2/4) applies only to the single-table calls and is
-swept there with ``single_table=True``.  Results are cached in a JSON file
+plan over the one table: for bucketed tables the tiled passes or the
+persistent kernel, whichever the plan takes for the empty table, the three
+phase kernels for Cuckoo tables), so the choice is made on the kernels that
+run it.  Those have no keys-per-wave parameter: the keys-per-group axis
+(R = 1/2/4, which asks for the lane groups in every call) applies only to the
+single-table calls and is swept there with ``single_table=True``.  Results are cached in a JSON file
 keyed by (kind, floor(log2 capacity), load factor rounded to 0.1), so tables
 of similar shape reuse one measurement.
 
