@@ -241,7 +241,6 @@ void bfs_fused_kernel(BfsModelDev m, DevTable t, const uint64_t* __restrict__ f,
   const uint64_t first = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   const int lane = lane_id();
-  __shared__ MeetLds meet;
   unsigned long long placed = 0, gen = 0;
   for (uint64_t i0 = first - lane; i0 < nf; i0 += stride) {
     const uint64_t i = i0 + lane;
@@ -249,7 +248,7 @@ void bfs_fused_kernel(BfsModelDev m, DevTable t, const uint64_t* __restrict__ f,
     uint32_t k = 0, nnew = 0;
     if (i < nf) {
       for_each_successor(m, model, f[i], [&](uint64_t succ) {
-        const uint32_t r = lane_find_or_put<false>(t, succ, meet.wave[threadIdx.x / kWave]);
+        const uint32_t r = lane_find_or_put<false, false>(t, succ, nullptr);
         if (r) {                   // 1 = stored, 2 = kept on the overflow list: new either way
           if (k < 64) m0 |= 1ull << k;
           else m1 |= 1ull << (k - 64);

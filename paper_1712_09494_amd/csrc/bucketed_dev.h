@@ -357,12 +357,16 @@ __device__ __forceinline__ bool eight_slots(const uint64_t (&x)[8], uint64_t k, 
 // compare-and-swaps of one slot are served one after another, 11 ns each
 // (2^18 copies of one key into an empty table: 2939 us with one per lane, 56
 // so; all keys different: 41 either way; a fill of 2^26 keys in batches of 2^20
-// 3476 and 3497).  The lanes meet while their slots are on the way.
+// 3476 and 3497).  The lanes meet while their slots are on the way.  Without
+// MEET (the fused exploration, whose lanes come to copies of a state at
+// different times: four levels 960 us, 993 with) `meet` is not used.
+template <bool MEET>
 __device__ __forceinline__ uint32_t eight_put(uint64_t* p, uint64_t k, uint32_t* meet, uint32_t hash) {
   uint64_t x[8];
   load8(p, x);
-  const Meeting with = wave_meet(meet, hash);
-  const bool any = ballot(with.maybe) != 0;
+  Meeting with{0, false};
+  if constexpr (MEET) with = wave_meet(meet, hash);
+  const bool any = MEET && ballot(with.maybe) != 0;
   const bool copy = any && shfl64(k, with.lead) == k && with.maybe;
   uint32_t em;
   uint32_t r = eight_slots(x, k, em) ? 0u : 2u;
@@ -391,14 +395,14 @@ __device__ __forceinline__ uint32_t eight_query(const uint64_t* p, uint64_t k) {
 
 // Find-or-put of key k from slot c0 of bucket b, position j of its probe
 // sequence, on.
-template <bool SCRIPTED>
+template <bool SCRIPTED, bool MEET = true>
 __device__ __forceinline__ uint32_t lane_put_from(const DevTable& t, uint64_t k, uint32_t j, uint64_t b, uint32_t c0,
                                                   uint32_t* meet) {
   const uint32_t B = t.bucket_slots;
   const uint32_t nseq = t.nhash + t.walk;
   for (;;) {
     for (; c0 < B; c0 += 8) {
-      const uint32_t r = eight_put(t.slots + b * B + c0, k, meet, (uint32_t)b);
+      const uint32_t r = eight_put<MEET>(t.slots + b * B + c0, k, meet, (uint32_t)b);
       if (r != 2) return r;
     }
     if (++j >= nseq) return stash_put(t, k);   // every bucket of the sequence full
@@ -410,12 +414,12 @@ __device__ __forceinline__ uint32_t lane_put_from(const DevTable& t, uint64_t k,
 // Both start with the first eight slots of h_1's bucket on their own: most
 // keys end there, and h_1's constant is a scalar where a lane's own position
 // would load it.
-template <bool SCRIPTED>
+template <bool SCRIPTED, bool MEET = true>
 __device__ __forceinline__ uint32_t lane_find_or_put(const DevTable& t, uint64_t k, uint32_t* meet) {
   if (k == kEmpty) return sentinel_put(t);
   const uint64_t b = hidx<SCRIPTED>(t, k, 0);
-  const uint32_t r = eight_put(t.slots + b * t.bucket_slots, k, meet, (uint32_t)b);
-  return r != 2 ? r : lane_put_from<SCRIPTED>(t, k, 0, b, 8, meet);
+  const uint32_t r = eight_put<MEET>(t.slots + b * t.bucket_slots, k, meet, (uint32_t)b);
+  return r != 2 ? r : lane_put_from<SCRIPTED, MEET>(t, k, 0, b, 8, meet);
 }
 
 template <bool SCRIPTED>
