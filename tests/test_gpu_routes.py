@@ -82,3 +82,26 @@ def test_lanes_need_many_keys_and_room(width):
         with b.Table("bucketed", capacity=cap, nhash=3, bucket_slots=width) as t:
             r = served(t, Oracle(), inputs.uniform_keys(n, seed=n))
             assert r == {"bucketed_fop": 1, f"bucketed_fop.{form}": 1}, (n, cap)
+    # after as many keys as the table has slots (repeats, mostly) room does not matter, and before that a table that
+    # is nearly full by what was put takes groups
+    n = lanes + 77
+    keys = inputs.uniform_keys(n, seed=1)
+    with b.Table("bucketed", capacity=3 * n, nhash=3, bucket_slots=width) as t:
+        o = Oracle()
+        slots, puts = t.stats()["capacity"], 0
+        for k in range(5):
+            r = served(t, o, keys)
+            tiled = {"tile_partition", "tile_insert", "tile_finish"}
+            expect = tiled if k == 0 else {"bucketed_fop", f"bucketed_fop.{'lanes' if puts >= slots else 'groups'}"}
+            assert set(r) == expect, (k, r)
+            puts += n
+    with b.Table("bucketed", capacity=16 * lanes, nhash=3, bucket_slots=width) as t:
+        slots = t.stats()["capacity"]
+        many = dev(inputs.uniform_keys(1 << 20, seed=3))
+        puts = 0
+        while puts <= slots - slots // 8:
+            assert "bucketed_fop.groups" in routes(lambda: t.find_or_put(many[:1000]))
+            r = routes(lambda: t.find_or_put(many[:lanes]))
+            assert ("bucketed_fop.lanes" in r) == (puts + 1000 <= slots - slots // 8), puts
+            puts += 1000 + lanes
+        assert "bucketed_fop.groups" in routes(lambda: t.find_or_put(many[:lanes]))
