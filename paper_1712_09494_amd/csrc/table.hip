@@ -388,31 +388,36 @@ static bool plan_tile_rule(const ht_table* t, uint64_t n) {
 }
 
 // Whether a find-or-put probes with one lane per key instead of the lane groups
-// of Sec. 4.2, when neither is asked for: when its keys fill the grid of one
-// lane per key, the table has 16 slots or more for each, and seven eighths of
-// its slots would hold all that was put before it.  Then a lane's eight-slot
-// steps wait behind enough other waves, and the keys in flight rarely meet in a
-// bucket (new keys, and keys stored before, by groups and by lanes, at load
-// factors 0.3, 0.6 and 0.8; 2^20 keys, 2^26 slots: 8-slot buckets 57 62 87 and
-// 57 59 81 us, 30 32 40 and 27 30 34; 16 slots 58 71 99 and 57 67 91; 64 slots
-// 141 140 163 and 87 124 164, 104 104 103 and 32 47 66).  Fewer keys run
-// groups, which read a bucket at once (2^16 keys, 2^22 slots, load factors 0.3
-// and 0.8: 8 slots 11.7 18.7 and 11.2 20.8, 16 slots 11.8 16.1 and 12.3 21.4,
-// 64 slots 17.9 19.4 and 16.2 33.2; 64-slot buckets nearly full 58 and 258),
-// and so do keys that crowd the table: each bucket's new keys take its next
-// slot one after another, and lanes bring more of them at once, or walk through
-// full buckets (load factor 0.93: 16 slots 283 and 323, 64 slots 315 and 440;
-// 2^18 keys into 2^19 empty slots: 8 slots 41 and 41, 16 slots 38 and 63, 64
-// slots 76 and 175).  Repeats need no such room, neither those of an
-// exploration (18.8 against 19.8 ms for seven levels) nor the keys of a table
-// that was handed more of them than it has slots (2^26 keys in batches of 2^20,
-// each a hundred or a thousand times: 38.0 and 39.8 G keys/s by groups, 45.2
-// and 47.6 by lanes).
+// of Sec. 4.2, when neither is asked for: when it has a key for every lane of
+// four blocks per compute unit, the table has 16 slots or more for each, and
+// three quarters of its slots would hold all that was put before it (seven
+// eighths where the call fills the grid of six blocks). Then a lane's eight-
+// slot steps wait behind enough other waves, and the keys in flight rarely meet
+// in a bucket (new keys by groups and by lanes, at load factors 0.3, 0.6 and
+// 0.8; 2^26 slots, 2^18 keys: 8-slot buckets 23.8 25.0 31.0 and 21.7 23.6 30.0
+// us, 16 slots 23.3 25.3 31.1 and 21.4 25.2 34.8, 64 slots 40 41 47 and 29 38
+// 57; 2^20 keys: 8 slots 57 62 87 and 57 59 81, 16 slots 58 71 99 and 57 67 91,
+// 64 slots 141 140 163 and 87 124 164). Fewer keys run groups, which read a
+// bucket at once (2^16 keys, 2^22 slots, load factors 0.3 and 0.8: 8 slots 11.7
+// 18.7 and 11.2 20.8, 16 slots 11.8 16.1 and 12.3 21.4, 64 slots 17.9 19.4 and
+// 16.2 33.2; 64-slot buckets nearly full 58 and 258), and so do keys that crowd
+// the table: each bucket's new keys take its next slot one after another, and
+// lanes bring more of them at once, or walk through full buckets (2^18 keys
+// into 2^19 empty slots: 8 slots 41 and 41, 16 slots 38 and 63, 64 slots 76 and
+// 175; 2^20 keys at load factor 0.93: 16 slots 283 and 323, 64 slots 315 and
+// 440). Repeats need no such room, neither those of an exploration (18.8
+// against 19.8 ms for seven levels) nor, in calls that fill the grid, the keys
+// of a table that was handed more of them than it has slots (2^26 keys in
+// batches of 2^20, each a hundred or a thousand times: 38.0 and 39.8 G keys/s
+// by groups, 45.2 and 47.6 by lanes; 2^20 stored keys, 2^26 slots: 8 slots 30
+// to 40 us and 27 to 34, 64 slots 104 and 32 to 66; 2^18 in 2^22 slots at load
+// factor 0.8: 16 slots 14.1 and 16.1).
 static bool lane_rule(const ht_table* t, uint64_t n, uint64_t before, bool repeats) {
   if (t->user_cfg.keys_per_group || (t->cfg.flags & HT_FLAG_BUCKETED_ATOMIC_LOADS)) return false;
   if (repeats) return t->cfg.bucket_slots == 8 || n >= 512ull * t->cfg.bucket_slots;
-  if (n < (uint64_t)atomic_grid_blocks(t) * kBlock) return false;
-  return before >= t->nslots || (t->nslots / 16 >= n && before <= t->nslots - t->nslots / 8);
+  const bool fills = n >= (uint64_t)atomic_grid_blocks(t) * kBlock;
+  if (before >= t->nslots) return fills;
+  return n >= 4ull * t->cus * kBlock && t->nslots / 16 >= n && before <= t->nslots / 8 * (fills ? 7 : 6);
 }
 
 // Whether one block does the call with the whole table in LDS: a batch that

@@ -74,34 +74,32 @@ def test_keys_per_group_asks_for_the_groups(width, per_group):
 
 @pytest.mark.parametrize("width", [8, 16, 64])
 def test_lanes_need_many_keys_and_room(width):
-    """Groups below as many keys as the one-lane grid has lanes, and where the
-    table has less than 16 slots a key."""
-    lanes = torch.cuda.get_device_properties(0).multi_processor_count * 6 * 256
+    """Groups below a key for each lane of four blocks per compute unit, where
+    the table has less than 16 slots a key, and where three quarters of its
+    slots (seven eighths for a full grid) would not hold what was put; lanes again once it was handed as many
+    keys as it has slots, for calls that fill the grid of six blocks."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    lanes, full = cus * 4 * 256, cus * 6 * 256
     for n, cap, form in ((lanes - 1, 16 * lanes, "groups"), (lanes, 16 * lanes, "lanes"),
                          (lanes, 16 * lanes - width, "groups"), (4096, 1 << 20, "groups"), (40000, 1 << 20, "groups")):
         with b.Table("bucketed", capacity=cap, nhash=3, bucket_slots=width) as t:
             r = served(t, Oracle(), inputs.uniform_keys(n, seed=n))
             assert r == {"bucketed_fop": 1, f"bucketed_fop.{form}": 1}, (n, cap)
-    # after as many keys as the table has slots (repeats, mostly) room does not matter, and before that a table that
-    # is nearly full by what was put takes groups
-    n = lanes + 77
-    keys = inputs.uniform_keys(n, seed=1)
-    with b.Table("bucketed", capacity=3 * n, nhash=3, bucket_slots=width) as t:
-        o = Oracle()
-        slots, puts = t.stats()["capacity"], 0
-        for k in range(5):
-            r = served(t, o, keys)
-            tiled = {"tile_partition", "tile_insert", "tile_finish"}
-            expect = tiled if k == 0 else {"bucketed_fop", f"bucketed_fop.{'lanes' if puts >= slots else 'groups'}"}
-            assert set(r) == expect, (k, r)
-            puts += n
-    with b.Table("bucketed", capacity=16 * lanes, nhash=3, bucket_slots=width) as t:
-        slots = t.stats()["capacity"]
-        many = dev(inputs.uniform_keys(1 << 20, seed=3))
-        puts = 0
-        while puts <= slots - slots // 8:
-            assert "bucketed_fop.groups" in routes(lambda: t.find_or_put(many[:1000]))
-            r = routes(lambda: t.find_or_put(many[:lanes]))
-            assert ("bucketed_fop.lanes" in r) == (puts + 1000 <= slots - slots // 8), puts
-            puts += 1000 + lanes
-        assert "bucketed_fop.groups" in routes(lambda: t.find_or_put(many[:lanes]))
+    for n in (full, full - 1):
+        keys = inputs.uniform_keys(n, seed=1)
+        with b.Table("bucketed", capacity=3 * n, nhash=3, bucket_slots=width) as t:
+            o = Oracle()
+            slots, puts = t.stats()["capacity"], 0
+            for k in range(5):
+                r = served(t, o, keys)
+                form = "lanes" if puts >= slots and n == full else "groups"
+                assert set(r) == ({"bucketed_fop", f"bucketed_fop.{form}"} if k else
+                                  {"tile_partition", "tile_insert", "tile_finish"}), (k, r)
+                puts += n
+    for n, eighths in ((lanes, 6), (full, 7)):
+        with b.Table("bucketed", capacity=16 * n, nhash=3, bucket_slots=width) as t:
+            most = t.stats()["capacity"] // 8 * eighths
+            keys = dev(inputs.uniform_keys(n, seed=3))
+            for puts in range(0, 16 * n, n):
+                r = routes(lambda: t.find_or_put(keys))
+                assert ("bucketed_fop.lanes" in r) == (puts <= most) and "bucketed_fop" in r, (puts, r)
