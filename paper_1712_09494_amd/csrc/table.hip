@@ -397,10 +397,17 @@ static bool plan_tile_rule(const ht_table* t, uint64_t n) {
 // 0.8; 2^26 slots, 2^18 keys: 8-slot buckets 23.8 25.0 31.0 and 21.7 23.6 30.0
 // us, 16 slots 23.3 25.3 31.1 and 21.4 25.2 34.8, 64 slots 40 41 47 and 29 38
 // 57; 2^20 keys: 8 slots 57 62 87 and 57 59 81, 16 slots 58 71 99 and 57 67 91,
-// 64 slots 141 140 163 and 87 124 164). Fewer keys run groups, which read a
-// bucket at once (2^16 keys, 2^22 slots, load factors 0.3 and 0.8: 8 slots 11.7
-// 18.7 and 11.2 20.8, 16 slots 11.8 16.1 and 12.3 21.4, 64 slots 17.9 19.4 and
-// 16.2 33.2; 64-slot buckets nearly full 58 and 258), and so do keys that crowd
+// 64 slots 141 140 163 and 87 124 164). From one block per unit on, lanes where
+// the table has 64 slots for each key and half of them would hold what was put:
+// most keys end at their first eight slots (calls of 2^16 keys one after another
+// up to load factor 0.3, to 0.5 and to 0.7, 2^26 slots: 8 slots 8.6 9.7 11.6 and
+// 8.2 9.5 11.4 us, 16 slots 9.6 9.8 10.8 and 8.5 9.5 11.8, 64 slots 16.2 16.0
+// 16.2 and 9.2 12.5 16.3; 2^17 keys, 2^22 slots, which are 32 a key: 8 slots
+// 13.5 14.5 15.0 and 15.3 16.5 17.5). Fewer keys run groups, which read a
+// bucket at once (2^14 keys, 2^26 slots: 16 slots 6.0 5.7 6.6 and 5.9 6.7 8.4,
+// 64 slots 8.3 8.2 8.1 and 6.5 9.4 11.3), fuller tables too (2^16 keys, 2^22
+// slots, load factor 0.8: 8 slots 18.7 and 20.8, 16 slots 16.1 and 21.4, 64
+// slots 19.4 and 33.2, nearly full 58 and 258), and so do keys that crowd
 // the table: each bucket's new keys take its next slot one after another, and
 // lanes bring more of them at once, or walk through full buckets (2^18 keys
 // into 2^19 empty slots: 8 slots 41 and 41, 16 slots 38 and 63, 64 slots 76 and
@@ -417,7 +424,9 @@ static bool lane_rule(const ht_table* t, uint64_t n, uint64_t before, bool repea
   if (repeats) return t->cfg.bucket_slots == 8 || n >= 512ull * t->cfg.bucket_slots;
   const bool fills = n >= (uint64_t)atomic_grid_blocks(t) * kBlock;
   if (before >= t->nslots) return fills;
-  return n >= 4ull * t->cus * kBlock && t->nslots / 16 >= n && before <= t->nslots / 8 * (fills ? 7 : 6);
+  const uint64_t block_each = (uint64_t)t->cus * kBlock;
+  if (n >= block_each && t->nslots / 64 >= n && before <= t->nslots / 2) return true;
+  return n >= 4 * block_each && t->nslots / 16 >= n && before <= t->nslots / 8 * (fills ? 7 : 6);
 }
 
 // Whether one block does the call with the whole table in LDS: a batch that

@@ -103,3 +103,22 @@ def test_lanes_need_many_keys_and_room(width):
             for puts in range(0, 16 * n, n):
                 r = routes(lambda: t.find_or_put(keys))
                 assert ("bucketed_fop.lanes" in r) == (puts <= most) and "bucketed_fop" in r, (puts, r)
+
+
+@pytest.mark.parametrize("width", [8, 16, 64])
+def test_lanes_from_a_block_per_unit_in_a_roomy_table(width):
+    """Lanes also from one block per compute unit on, where the table has 64
+    slots a key and half of its slots would hold what was put."""
+    n = torch.cuda.get_device_properties(0).multi_processor_count * 256
+    for m, cap, form in ((n, 64 * n, "lanes"), (n - 1, 64 * n, "groups"), (n, 64 * n - width, "groups")):
+        with b.Table("bucketed", capacity=cap, nhash=3, bucket_slots=width) as t:
+            keys = inputs.uniform_keys(m, seed=5)
+            assert t.stats()["capacity"] == cap
+            o, most = Oracle(), cap // 2
+            for puts in range(0, 40 * m, m):
+                if puts % (4 * m) and puts + m < most:
+                    t.find_or_put(dev(keys))
+                    continue
+                r = served(t, o, keys)
+                want = form if puts <= most else "groups"
+                assert r == {"bucketed_fop": 1, f"bucketed_fop.{want}": 1}, (m, cap, puts)
