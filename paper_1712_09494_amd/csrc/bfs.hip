@@ -24,7 +24,8 @@
 // half a GB whatever the level's size; a whole level at once took 12.2 GB for
 // the 715 M successors of the 7-level workload's last level, and allocating
 // memory that has been used before costs about 30 ms per GB (it is cleared
-// first): 395 ms for an exploration whose kernels run 25 ms.  The last level's
+// first): an exploration whose kernels run 25 ms took 395 ms on one machine,
+// 349 on another and 28 while there was unused memory.  The last level's
 // new states are counted and not written: there is no level to read them.
 //
 // Fused levels (successor generation and hash table access in one kernel, as
@@ -575,7 +576,7 @@ struct Spans {
 // workload's split bucketed levels, device time and whole call: 4096 groups
 // 28.4 and 31.1 ms, 8192 26.4 and 28.2, 16384 25.4 and 27.7, 32768 24.9 and
 // 28.9 (its buffers no longer stay with the table), whole levels 24.3 and
-// 28.1 before memory has to be cleared, 395 after.  Fused Cuckoo: four groups
+// 28.1 while there is unused memory (349 to 395 after).  Fused Cuckoo: four groups
 // for each wave of the probe grid (at most 2.3 GB of lists).  Its fused levels
 // of a 6-level exploration: 5.25 ms a call at three turns of 8 blocks per
 // compute unit, 5.04 at four; four turns of 6 blocks 5.20.
