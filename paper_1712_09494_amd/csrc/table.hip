@@ -388,45 +388,50 @@ static bool plan_tile_rule(const ht_table* t, uint64_t n) {
 }
 
 // Whether a find-or-put probes with one lane per key instead of the lane groups
-// of Sec. 4.2, when neither is asked for: when it has a key for every lane of
-// four blocks per compute unit, the table has 16 slots or more for each, and
-// three quarters of its slots would hold all that was put before it (seven
-// eighths where the call fills the grid of six blocks). Then a lane's eight-
-// slot steps wait behind enough other waves, and the keys in flight rarely meet
-// in a bucket (new keys by groups and by lanes, at load factors 0.3, 0.6 and
-// 0.8; 2^26 slots, 2^18 keys: 8-slot buckets 23.8 25.0 31.0 and 21.7 23.6 30.0
-// us, 16 slots 23.3 25.3 31.1 and 21.4 25.2 34.8, 64 slots 40 41 47 and 29 38
-// 57; 2^20 keys: 8 slots 57 62 87 and 57 59 81, 16 slots 58 71 99 and 57 67 91,
-// 64 slots 141 140 163 and 87 124 164). From one block per unit on, lanes where
-// the table has 64 slots for each key and half of them would hold what was put:
-// most keys end at their first eight slots (calls of 2^16 keys one after another
-// up to load factor 0.3, to 0.5 and to 0.7, 2^26 slots: 8 slots 8.6 9.7 11.6 and
-// 8.2 9.5 11.4 us, 16 slots 9.6 9.8 10.8 and 8.5 9.5 11.8, 64 slots 16.2 16.0
-// 16.2 and 9.2 12.5 16.3; 2^17 keys, 2^22 slots, which are 32 a key: 8 slots
-// 13.5 14.5 15.0 and 15.3 16.5 17.5). Fewer keys run groups, which read a
-// bucket at once (2^14 keys, 2^26 slots: 16 slots 6.0 5.7 6.6 and 5.9 6.7 8.4,
-// 64 slots 8.3 8.2 8.1 and 6.5 9.4 11.3), fuller tables too (2^16 keys, 2^22
-// slots, load factor 0.8: 8 slots 18.7 and 20.8, 16 slots 16.1 and 21.4, 64
-// slots 19.4 and 33.2, nearly full 58 and 258), and so do keys that crowd
-// the table: each bucket's new keys take its next slot one after another, and
-// lanes bring more of them at once, or walk through full buckets (2^18 keys
-// into 2^19 empty slots: 8 slots 41 and 41, 16 slots 38 and 63, 64 slots 76 and
-// 175; 2^20 keys at load factor 0.93: 16 slots 283 and 323, 64 slots 315 and
-// 440). Repeats need no such room, neither those of an exploration (18.8
-// against 19.8 ms for seven levels) nor, in calls that fill the grid, the keys
-// of a table that was handed more of them than it has slots (2^26 keys in
-// batches of 2^20, each a hundred or a thousand times: 38.0 and 39.8 G keys/s
-// by groups, 45.2 and 47.6 by lanes; 2^20 stored keys, 2^26 slots: 8 slots 30
-// to 40 us and 27 to 34, 64 slots 104 and 32 to 66; 2^18 in 2^22 slots at load
-// factor 0.8: 16 slots 14.1 and 16.1).
+// of Sec. 4.2, when neither is asked for. A lane issues less for a key than a
+// group does, the more so the wider the bucket, but takes eight slots at a time,
+// one step after another, which other waves have to hide, and brings more keys
+// at once: new keys of one bucket take its next slot one after another, and in
+// nearly full buckets lanes take many steps. So lanes need keys enough (half a
+// block per compute unit), slots enough for each key in flight, and a table that
+// is full to no more than a share, which is larger the more keys there are.
+// New keys, us a call by groups and by lanes, calls one after another:
+// - keys: 2^15 a call, 64 slots each, load factors to 1/8, 1/4 and 1/2: 8-slot
+//   buckets 10.1 9.8 10.9 and 9.0 9.0 10.5, 16 slots 10.5 10.1 10.4 and 9.4 9.7
+//   11.2, 64 slots 16.2 15.7 15.8 and 13.6 14.1 16.4; 2^14: 8 slots 9.2 8.9 10.1
+//   and 8.9 8.6 9.8, 16 slots 9.6 9.5 9.3 and 9.0 9.1 10.7.
+// - slots for each key in flight, at load factors below 1/8: 98304 keys, 8 slots
+//   each 8-slot buckets 19.3 and 17.0, 16-slot 21.2 and 19.8, 32-slot 29.4 and
+//   28.5, 64-slot 34.8 and 40.0; 16 each 15.3 and 14.1, 19.5 and 16.9, 21.1 and
+//   20.1, 26.5 and 27.1; 32 each 64-slot 22.7 and 20.5; 160000 keys, 16 each
+//   23.4 and 21.0 (16 slots), 23.5 and 24.6 (32), 30.6 and 35.8 (64). Full grids,
+//   400000 keys: 8 each 33.4 and 34.1 (8 slots), 16 each 31.7 and 31.2, 31.5 and
+//   34.0, 37.6 and 41.1, 52.3 and 50.0 (8, 16, 32 and 64 slots), 32 each 32.6 and
+//   31.6, 36.5 and 34.2 (16 and 32 slots).
+// - load factor, from 3/8, 1/2, 5/8 and 3/4 on: 2^16 keys, 64 slots each, 8-slot
+//   buckets 12.4 13.5 14.8 18.1 and 12.2 13.5 15.1 19.1, 16-slot 12.5 12.7 13.5
+//   15.8 and 12.7 13.5 16.2 20.1, 64-slot 18.3 18.3 18.4 19.4 and 17.2 18.8 22.4
+//   31.3; 450000 keys: 33.3 34.2 35.7 42.6 and 32.1 33.6 35.5 44.3, 33.9 35.2 37.7
+//   43.9 and 33.7 35.0 38.4 46.8, 54.0 53.8 54.4 62.5 and 44.2 49.4 56.7 73.7;
+//   2^20 keys: 58.6 61.6 67.5 85.8 and 57.4 58.8 62.9 81.8, 59.8 65.1 77.0 97.5
+//   and 60.2 65.0 72.2 90.0, 139 139 141 164 and 98 114 131 165.
+// Repeats need no such room, neither those of an exploration (18.8 against 19.8
+// ms for seven levels) nor, in calls that fill the grid, the keys of a table that
+// was handed more of them than it has slots (2^26 keys in batches of 2^20, each a
+// hundred or a thousand times: 38.0 and 39.8 G keys/s by groups, 45.2 and 47.6 by
+// lanes; 2^20 stored keys, 2^26 slots: 8 slots 30 to 40 us and 27 to 34, 64 slots
+// 104 and 32 to 66; 2^18 in 2^22 slots at load factor 0.8: 16 slots 14.1 and 16.1).
 static bool lane_rule(const ht_table* t, uint64_t n, uint64_t before, bool repeats) {
+  const uint32_t width = t->cfg.bucket_slots;
   if (t->user_cfg.keys_per_group || (t->cfg.flags & HT_FLAG_BUCKETED_ATOMIC_LOADS)) return false;
-  if (repeats) return t->cfg.bucket_slots == 8 || n >= 512ull * t->cfg.bucket_slots;
-  const bool fills = n >= (uint64_t)atomic_grid_blocks(t) * kBlock;
+  if (repeats) return width == 8 || n >= 512ull * width;
+  const uint64_t block_each = (uint64_t)t->cus * kBlock, grid = (uint64_t)atomic_grid_blocks(t) * kBlock;
+  const bool fills = n >= grid;
   if (before >= t->nslots) return fills;
-  const uint64_t block_each = (uint64_t)t->cus * kBlock;
-  if (n >= block_each && t->nslots / 64 >= n && before <= t->nslots / 2) return true;
-  return n >= 4 * block_each && t->nslots / 16 >= n && before <= t->nslots / 8 * (fills ? 7 : 6);
+  if (n < block_each / 2) return false;
+  const uint32_t room = fills ? (width == 8 || width == 64 ? 16 : 32) : std::min(width, 32u);
+  const uint32_t eighths = n >= 16 * block_each ? 7 : fills || width == 8 ? 5 : n >= block_each ? 4 : 2;
+  return t->nslots / room >= std::min(n, grid) && before <= t->nslots / 8 * eighths;
 }
 
 // Whether one block does the call with the whole table in LDS: a batch that

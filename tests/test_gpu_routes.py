@@ -72,53 +72,46 @@ def test_keys_per_group_asks_for_the_groups(width, per_group):
             plan.close()
 
 
-@pytest.mark.parametrize("width", [8, 16, 64])
-def test_lanes_need_many_keys_and_room(width):
-    """Groups below a key for each lane of four blocks per compute unit, where
-    the table has less than 16 slots a key, and where three quarters of its
-    slots (seven eighths for a full grid) would not hold what was put; lanes again once it was handed as many
-    keys as it has slots, for calls that fill the grid of six blocks."""
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    lanes, full = cus * 4 * 256, cus * 6 * 256
-    for n, cap, form in ((lanes - 1, 16 * lanes, "groups"), (lanes, 16 * lanes, "lanes"),
-                         (lanes, 16 * lanes - width, "groups"), (4096, 1 << 20, "groups"), (40000, 1 << 20, "groups")):
-        with b.Table("bucketed", capacity=cap, nhash=3, bucket_slots=width) as t:
-            r = served(t, Oracle(), inputs.uniform_keys(n, seed=n))
-            assert r == {"bucketed_fop": 1, f"bucketed_fop.{form}": 1}, (n, cap)
-    for n in (full, full - 1):
-        keys = inputs.uniform_keys(n, seed=1)
-        with b.Table("bucketed", capacity=3 * n, nhash=3, bucket_slots=width) as t:
-            o = Oracle()
-            slots, puts = t.stats()["capacity"], 0
-            for k in range(5):
-                r = served(t, o, keys)
-                form = "lanes" if puts >= slots and n == full else "groups"
-                assert set(r) == ({"bucketed_fop", f"bucketed_fop.{form}"} if k else
-                                  {"tile_partition", "tile_insert", "tile_finish"}), (k, r)
-                puts += n
-    for n, eighths in ((lanes, 6), (full, 7)):
-        with b.Table("bucketed", capacity=16 * n, nhash=3, bucket_slots=width) as t:
-            most = t.stats()["capacity"] // 8 * eighths
+def block_each():
+    """Lanes of one block of 256 threads on each compute unit."""
+    return torch.cuda.get_device_properties(0).multi_processor_count * 256
+
+
+@pytest.mark.parametrize("width", [8, 16, 32, 64])
+def test_lanes_need_keys_and_room(width):
+    """Second batches (the tiled passes take first ones): groups below half a
+    block of keys per compute unit, and where the table lacks the slots for
+    each key in flight (six blocks per compute unit at most)."""
+    one, full = block_each(), 6 * block_each()
+    cases = [(one // 2 - 1, 64 * one, "groups"), (one // 2, 64 * one, "lanes"), (4096, 1 << 20, "groups")]
+    room = min(width, 32)
+    for n, slots in ((one, room * one), (4 * one, room * 4 * one), (full - 1, room * full)):
+        cases += [(n, slots, "lanes"), (n, slots - room * width, "groups")]
+    room = 16 if width in (8, 64) else 32
+    for n in (full, 2 * full):
+        cases += [(n, room * full, "lanes"), (n, room * full - width, "groups")]
+    for n, slots, form in cases:
+        with b.Table("bucketed", capacity=slots, nhash=3, bucket_slots=width) as t:
+            assert t.stats()["capacity"] == slots
+            keys, o = inputs.uniform_keys(n, seed=n), Oracle()
+            served(t, o, keys)
+            r = served(t, o, keys)
+            assert r == {"bucketed_fop": 1, f"bucketed_fop.{form}": 1}, (n, slots, r)
+
+
+@pytest.mark.parametrize("width", [8, 16, 32, 64])
+def test_lanes_need_a_table_with_free_slots(width):
+    """Groups once more than a share of the slots was put, larger for more
+    keys; lanes again once the table was handed as many keys as it has slots,
+    for calls that fill the grid of six blocks."""
+    one = block_each()
+    for n, eighths in ((one // 2, 5 if width == 8 else 2), (one, 5 if width == 8 else 4), (6 * one, 5), (16 * one, 7)):
+        with b.Table("bucketed", capacity=32 * n, nhash=3, bucket_slots=width) as t:
+            slots = t.stats()["capacity"]
             keys = dev(inputs.uniform_keys(n, seed=3))
-            for puts in range(0, 16 * n, n):
+            for puts in range(0, 36 * n, n):
                 r = routes(lambda: t.find_or_put(keys))
-                assert ("bucketed_fop.lanes" in r) == (puts <= most) and "bucketed_fop" in r, (puts, r)
-
-
-@pytest.mark.parametrize("width", [8, 16, 64])
-def test_lanes_from_a_block_per_unit_in_a_roomy_table(width):
-    """Lanes also from one block per compute unit on, where the table has 64
-    slots a key and half of its slots would hold what was put."""
-    n = torch.cuda.get_device_properties(0).multi_processor_count * 256
-    for m, cap, form in ((n, 64 * n, "lanes"), (n - 1, 64 * n, "groups"), (n, 64 * n - width, "groups")):
-        with b.Table("bucketed", capacity=cap, nhash=3, bucket_slots=width) as t:
-            keys = inputs.uniform_keys(m, seed=5)
-            assert t.stats()["capacity"] == cap
-            o, most = Oracle(), cap // 2
-            for puts in range(0, 40 * m, m):
-                if puts % (4 * m) and puts + m < most:
-                    t.find_or_put(dev(keys))
-                    continue
-                r = served(t, o, keys)
-                want = form if puts <= most else "groups"
-                assert r == {"bucketed_fop": 1, f"bucketed_fop.{want}": 1}, (m, cap, puts)
+                lanes = puts <= slots // 8 * eighths or (puts >= slots and n >= 6 * one)
+                assert r == {"bucketed_fop": 1, f"bucketed_fop.{'lanes' if lanes else 'groups'}": 1}, (n, puts, r)
+            f = t.find_or_put(keys)
+            assert not f.any() and t.size() == n
